@@ -75,11 +75,16 @@ constexpr size_t kLdsPerCU = 160 * 1024, kLdsPerBlockMax = 64 * 1024, kBitmapLds
 constexpr int kCUs = 256, kMaxBlocksPerCU = 24, kGlobalClassGrid = 1024;
 constexpr int32_t kGroupQMax = 1023;   // the several-per-wavefront bi-greedy kernel counts sent segments in 10 bit planes
 constexpr int kUniGroupSizes = 3;        // group sizes below the largest; the classes between them and the last stay empty
-constexpr int64_t kUniWork[kUniGroupSizes] = {1024, 8192, 262144};        // completion times: most pairs of a configuration run by 1, 4, 16 lanes
+// completion times: most pairs of a configuration run by 1, 2, 4, 8, 16 lanes; larger ones by 32, from 2^kUniTimesGiantLog2 pairs
+// on by 64.  Fewer lanes than this and the deep ring of a group overflows (limits twice as high: 300 configurations of the
+// 100,000 start again in the workspace, 4.65 ms against 4.15), more and lanes wait for their neighbours (limits half as high:
+// 4.45 ms).  64 lanes halve the time of the longest configurations (4 million pairs: 31 ms on 32 lanes, 13 on 64).
+constexpr int64_t kUniTimesWork[kClasses - 1] = {256, 2048, 8192, 32768, 131072};
+constexpr int kUniTimesGiantLog2 = 19;
 constexpr int64_t kUniWorkSched[kUniGroupSizes] = {1024, 65536, 262144};  // schedules: by 1, 8, 16 lanes (measured best on the sweep)
-// uni-greedy completion times: machines of at least this many processors would get a block per configuration.  Off: measured
-// on the large-machine sweep the segment pipeline through the lanes is 2 to 3 times faster (in steady state only a few
-// hundred values lie under the bound of a round); the kernel stays reachable through prs_tuning.
+// uni-greedy completion times: machines of at least this many processors would get a block per configuration.  Off: on the
+// large-machine sweep it is 2 to 3 times slower than the segment pipeline was pair by pair, and that one is now more than 50
+// times faster; the kernel stays reachable through prs_tuning.
 constexpr int32_t kUniWideProcs = INT32_MAX;
 
 struct ClassSpec {
@@ -91,6 +96,7 @@ struct ClassSpec {
     bool lds;                 // state (uni batch) / small arrays and maybe the bitmap (bi general) in LDS
     size_t lds_bytes;
     int32_t lds_bitmap_bytes;
+    RingShape rings;          // kUniTimes
     size_t slot_bytes, slot_offset;
     int grid;
 };
@@ -124,6 +130,15 @@ static void general_spec(ClassSpec &c, int32_t p_cap, int32_t q_cap)
     c.slot_bytes = bi_slot_bytes(p_cap, q_cap, c.lds);
 }
 
+// Rings of a uni-greedy completion-time wavefront in LDS (12 bytes a run): B of a segment, the receivers still combining,
+// has up to 21 runs with 1024 processors, 40 with 15,000, 131 with 45,000 and thousands of segments, and has to fit a ring.
+static RingShape uni_ring_shape(int32_t p_max)
+{
+    if (p_max <= 1024) return RingShape{3413, 32};           // 40 KB: four wavefronts per CU, one per SIMD
+    if (p_max <= 8192) return RingShape{6826, 64};
+    return RingShape{13653, 192};
+}
+
 static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t q_max, const prs_tuning *tuning = nullptr)
 {
     Layout L;
@@ -143,18 +158,30 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
     L.wide.grid = 0; L.wide.slot_bytes = 0; L.wide.slot_offset = 0;
     static const int group_lpc[kClasses - 1] = {1, 2, 4, 8, 16};
     if (model == PRS_UNI) {
-        // classes by number of pairs (1, 4 or 8, 16 or 32 lanes per configuration), all run by one launch,
-        // described by class 0
+        // classes by number of pairs (1, 2, 4, 8, 16 or 32 lanes per configuration; schedules 1, 8, 16 or 32), all run by
+        // one launch, described by class 0
         L.limits.by_work = 1;
-        for (int k = 0; k < kClasses - 1; ++k) {
-            const int g = k < kUniGroupSizes ? k : kUniGroupSizes - 1;
-            L.limits.work[k] = sched ? kUniWorkSched[g] : kUniWork[g];
+        for (int k = 0; k < kClasses - 1; ++k)
+            L.limits.work[k] = sched ? kUniWorkSched[k < kUniGroupSizes ? k : kUniGroupSizes - 1] : kUniTimesWork[k];
+        if (!sched) {
+            L.limits.giant_log2 = kUniTimesGiantLog2;
+            // A batch that leaves lanes without a configuration gives each of its configurations more of them.
+            const int64_t lanes = static_cast<int64_t>(kLdsPerCU / uni_times_lds_bytes(uni_ring_shape(p_max))) * kCUs * kWave;
+            for (int k = 0; k < kClasses - 1; ++k)
+                if (n << (k + 1) <= lanes) L.limits.work[k] = 0;
+            if (n << 6 <= lanes) L.limits.giant_log2 = 0;
         }
         if (tuning) {                                              // never changes a result, only who runs what
             const int64_t a = tuning->uni_group_pairs[0], b = tuning->uni_group_pairs[1], c3 = tuning->uni_group_pairs[2];
             if (a >= 0 && b >= a && c3 >= b) {
-                L.limits.work[0] = a; L.limits.work[1] = b;
-                for (int k = 2; k < kClasses - 1; ++k) L.limits.work[k] = c3;
+                if (sched) {
+                    L.limits.work[0] = a; L.limits.work[1] = b;
+                    for (int k = 2; k < kClasses - 1; ++k) L.limits.work[k] = c3;
+                } else {                                           // 1, 4 and 16 lanes; nothing for 2 and 8
+                    L.limits.work[0] = L.limits.work[1] = a;
+                    L.limits.work[2] = L.limits.work[3] = b;
+                    L.limits.work[4] = c3;
+                }
             }
             if (tuning->uni_wave_log2 > 0 && tuning->uni_wave_log2 < kWorkBuckets) L.limits.giant_log2 = tuning->uni_wave_log2;
         }
@@ -162,8 +189,10 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             ClassSpec &c = L.cls[k];
             c.q_cap = q_max;
             c.kind = sched ? kUniSched : kUniTimes; c.lpc = 0; c.rows_per_group = 0; c.lds = true; c.lds_bitmap_bytes = 0;
-            c.p_cap = (p_max + 15) / 16 * 16;                    // keeps every per-lane array 64-byte aligned
-            c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes();
+            // schedules: keeps every per-lane array 64-byte aligned; times: a ring of p + 4 runs per lane
+            c.p_cap = sched ? (p_max + 15) / 16 * 16 : (p_max + 4 + 15) / 16 * 16;
+            c.rings = uni_ring_shape(p_max);
+            c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes(c.rings);
             c.slot_bytes = k != 0 ? 0 : (sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap));
             int64_t g = static_cast<int64_t>(kLdsPerCU / c.lds_bytes) * kCUs;
             while (g > 1 && static_cast<size_t>(g) * c.slot_bytes > kMaxWorkspace) g /= 2;
@@ -309,6 +338,7 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
         L.lds_p = c.lds ? c.p_cap : 0;
         L.lds_bitmap_bytes = c.lds_bitmap_bytes;
         L.lds_bytes = c.lds_bytes;
+        L.rings = c.rings;
         L.slots = ws + c.slot_offset;
         L.slot_bytes = c.slot_bytes;
         L.slot_p = c.p_cap; L.slot_q = c.q_cap;

@@ -189,6 +189,8 @@ __device__ __forceinline__ int emit_set_bits(int32_t *out, uint32_t w, int base)
     return n;
 }
 
+template <bool B> struct BoolConst { static constexpr bool value = B; };
+
 // ---------------------------------------------------------------- wavefront primitives
 __device__ __forceinline__ int lane_id() { return static_cast<int>(threadIdx.x) & (kWave - 1); }
 

@@ -1,221 +1,336 @@
 // Uni-greedy completion times (Lowery & Langou, Algorithm 1, Section 5) on gfx950: segments pipelined
-// through the lanes of a wavefront.
+// through the lanes of a wavefront, equal ready times handled as one run.
 //
 // Algorithm 1 handles segment k+1 with the final states of segment k as its initial states, but it only
 // ever looks at the smallest of them.  The states of segment k leave in non-decreasing order (the start
 // time t of its pairs never decreases), so segment k+1 can begin as soon as segment k has produced its
-// first values and then follows right behind it.  A configuration is given a group of G lanes
-// (G = 1, 4, 16 or 32, chosen from its number of pairs); lane l of the group runs segments l, l+G, l+2G, ...
-// and reads the stream written by the lane before it (lane 0 reads the stream the last lane wrote one
-// round earlier).  Per iteration every lane whose two smallest remaining values are known performs one
-// pair of its segment:
-//   remaining values of a segment = unread tail of its input stream A (sorted) merged with the unread
-//   tail of B, the values (t + tcomm) + tcomp of its own earlier pairs (sorted as well);
-//   the pair takes the two smallest, t = the larger of them; t + tcomm goes to the output stream.
+// first values and then follows right behind it.  A configuration is given a group of G lanes (1 to 64,
+// chosen from its number of pairs); lane l of the group runs segments l, l+G, l+2G, ... and reads the
+// stream written by the lane before it (lane 0 the stream of the last lane, one round earlier).
+//
+// Many processors share a ready time, and which of them is which does not enter any time.  Streams
+// therefore hold runs (value, how many processors), and a step of a segment takes a whole run: of n
+// processors ready at v, with r = 0 or 1 left over from an earlier value, (r + n) / 2 pairs start at v,
+// send until v + tcomm (a run of the output stream) and combine until (v + tcomm) + tcomp (a run of B, the
+// receivers that come back), and (r + n) mod 2 are left over.  The runs a segment has left are the unread
+// tail of its input stream A merged with the unread tail of B; both are sorted, so a step compares two
+// heads.  On the sweep up to 1024 processors a step stands for 1.9 pairs on average (3 above 512), with
+// tens of thousands of processors for 5 to 130.  Taking a run in two pieces gives the same pairs, so runs
+// of equal value need not be joined; the newest run of a stream is joined with the next one if their values
+// are equal (different start times can round to the same sum), which saves a fifth of the steps.
+//
 // B is not stored: B[i] = stream[i] + tcomp with the same rounding as (t + tcomm) + tcomp.  The root's
-// final state (the largest value of the segment) closes the stream of the segment, so every stream has p
-// entries.  A value not yet produced by the previous segment is at least as large as the last one
-// produced, so a pair is safe as soon as its larger element does not exceed that value.
+// final state (the largest value of the segment) closes the stream of a segment.  A stream is published
+// up to its newest run, which is still open; the value of the open run (0 before the first) is a lower
+// bound of everything that follows, so a reader that has nothing left may take a value of B below it.
 //
-// How far a segment trails the one before it is the number of its receivers that are still combining
-// (the length of B), about p/25 in steady state and up to p/2 in the first segments.  A group much larger
-// than p divided by that lag would leave its first lane waiting for the last one at every round, which is
-// why light configurations get small groups (and a wavefront then works on several of them).
+// Every stream lives in a ring in LDS and nothing of it in global memory: a lane whose ring is full
+// waits for its reader and for its own B.  (With the streams backed by global memory the kernel was bound by
+// the scattered 8-byte stores, about 9 cycles of a CU's store path each.)  The rings of a group can all be
+// full at once only through the last lane, whose reader, the first lane, is a whole round behind: its ring
+// is the deep one.  If it does fill up -- or B outgrows a ring -- no lane of the group moves any more; the
+// configuration then starts again with its rings in the wavefront's workspace slot, p + 4 runs each, which
+// always suffices: a segment cannot have sent more processors than the lane that reads its stream has
+// taken from the stream before it, so at most p are waiting to be read.
 //
-// Streams live in the wavefront's workspace slot (two buffers of p entries per lane, alternating between
-// rounds); the last kRing entries of every stream are also kept in LDS, which serves the reads of a
-// segment that follows closely.  Entries further back (the first lane of a group reading the last one's
-// stream, a long B) are loaded from the workspace one iteration ahead of their use.
+// Measured (pair by pair with streams in global memory -> runs in LDS rings): the 100,000-configuration sweep
+// 11.9 -> 4.1 ms, 64 machines of 1024 to 65536 processors 587 -> 7.4 ms, 986 x 512 segmentations of a short message
+// 10.4 -> 1.9 ms.  A step is about 65 instructions and takes 240 ns with one wavefront per SIMD: what bounds it now is
+// the latency of that chain (LDS read, two compares, two additions).
 #include "prs_device.h"
 #include "prs_launch.h"
 
 namespace prs {
 
-constexpr int kRing = 64;          // stream entries per lane kept in LDS
-constexpr int kNear = kRing - 5;   // entries this close behind the writer are read from LDS in the next iteration
+constexpr int kSpan = 64;                        // steps between two looks for groups that do not move
+constexpr int kRunBytes = 12;                    // a run in a ring: value and count
+constexpr int32_t kRetired = 1 << 30;            // read place of a lane without a segment: its producer need not wait for it
 
-// The ring takes 32 KB; asking for 40 KB keeps it to four wavefronts per CU, one per SIMD: a fifth would share a SIMD,
-// and the configurations that land on the two sharing wavefronts run at half speed (measured: 11.8 against 12.0 ms).
-size_t uni_times_lds_bytes() { return static_cast<size_t>(kRing) * kWave * 8 + 8192; }
-size_t uni_times_slot_bytes(int32_t p_cap) { return static_cast<size_t>(kWave) * 2 * static_cast<size_t>(p_cap) * 8; }
+template <typename T> struct __attribute__((packed, aligned(4))) Run { T v; int32_t n; };
+
+size_t uni_times_lds_bytes(const RingShape &s) { return static_cast<size_t>(s.runs) * kRunBytes; }
+size_t uni_times_slot_bytes(int32_t p_cap) { return static_cast<size_t>(kWave) * static_cast<size_t>(p_cap) * kRunBytes; }
+
+// Value of the lane before this one in its group of G (the last lane's for the first), and of the lane after it: moves
+// inside the vector unit (quad_perm, rotations of a row of 16 or of the wavefront by one lane), no LDS access.
+template <int CTRL> __device__ __forceinline__ int dpp_from(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
+constexpr int kDppRowRor = 0x120, kDppWaveRol1 = 0x134, kDppWaveRor1 = 0x13C;
+
+template <int G> __device__ __forceinline__ int from_previous(int v, int gl)
+{
+    if (G == 2) return dpp_from<0xB1>(v);                            // quad_perm [1,0,3,2]
+    if (G == 4) return dpp_from<0x93>(v);                            // quad_perm [3,0,1,2]
+    if (G == 8) { const int a = dpp_from<kDppRowRor + 1>(v), b = dpp_from<kDppRowRor + 9>(v); return gl == 0 ? b : a; }
+    if (G == 16) return dpp_from<kDppRowRor + 1>(v);
+    if (G == 32) {
+        const int a = dpp_from<kDppWaveRor1>(v);                     // right except for lanes 0 and 32
+        const int lo = __builtin_amdgcn_readlane(v, 31), hi = __builtin_amdgcn_readlane(v, 63);
+        return gl == 0 ? (lane_id() == 0 ? lo : hi) : a;
+    }
+    if (G == 64) return dpp_from<kDppWaveRor1>(v);
+    return v;
+}
+template <int G> __device__ __forceinline__ int from_next(int v, int gl)
+{
+    if (G == 2) return dpp_from<0xB1>(v);
+    if (G == 4) return dpp_from<0x39>(v);                            // quad_perm [1,2,3,0]
+    if (G == 8) { const int a = dpp_from<kDppRowRor + 15>(v), b = dpp_from<kDppRowRor + 7>(v); return gl == 7 ? b : a; }
+    if (G == 16) return dpp_from<kDppRowRor + 15>(v);
+    if (G == 32) {
+        const int a = dpp_from<kDppWaveRol1>(v);
+        const int lo = __builtin_amdgcn_readlane(v, 0), hi = __builtin_amdgcn_readlane(v, 32);
+        return gl == 31 ? (lane_id() == 31 ? lo : hi) : a;
+    }
+    if (G == 64) return dpp_from<kDppWaveRol1>(v);
+    return v;
+}
+
+// v, or a value above every time of a schedule (those stay below 4e18 and 1e300: schedule_fits) if v is not there.  Only
+// the upper half is exchanged.
+template <typename T> __device__ __forceinline__ T or_absent(bool there, T v)
+{
+    uint64_t bits;
+    __builtin_memcpy(&bits, &v, 8);
+    const uint32_t hi = there ? static_cast<uint32_t>(bits >> 32) : 0x7FEFFFFFu;
+    bits = (static_cast<uint64_t>(hi) << 32) | static_cast<uint32_t>(bits);
+    __builtin_memcpy(&v, &bits, 8);
+    return v;
+}
+
+// A place in LDS by its byte address.
+template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) Run<T> *lds_run(int32_t at)
+{
+    return reinterpret_cast<__attribute__((address_space(3))) Run<T> *>(static_cast<uint32_t>(at));
+}
+
+// A ring of `cap` runs at byte addresses base, base + stride, ..., end (exclusive) of LDS or of the workspace slot.
+struct Ring { int32_t base, stride, end, cap; };
+
+// Rings of a wavefront in LDS: the last lane of every group has a deep ring, the others ring.runs_per_lane runs.
+// Both kinds are laid out run by run, the lanes side by side, so that lanes at different places of their rings mostly
+// stay on different banks.
+template <int G> __device__ __forceinline__ Ring lds_ring(int32_t lds, int l, const RingShape &s)
+{
+    constexpr int kGroups = kWave / G, kCols = G == 1 ? 0 : (G >= 8 ? kWave : kWave - kGroups);
+    const int g = l / G, i = l & (G - 1), shallow = kCols * s.runs_per_lane;
+    Ring r;
+    if (i == G - 1) {
+        r.base = lds + (shallow + g) * kRunBytes; r.stride = kGroups * kRunBytes; r.cap = (s.runs - shallow) / kGroups;
+    } else {
+        r.base = lds + (G >= 8 ? l : g * (G - 1) + i) * kRunBytes; r.stride = kCols * kRunBytes; r.cap = s.runs_per_lane;
+    }
+    r.end = r.base + r.cap * r.stride;
+    return r;
+}
+__device__ __forceinline__ Ring slot_ring(int l, int32_t slot_p)
+{
+    Ring r;
+    r.base = l * slot_p * kRunBytes; r.stride = kRunBytes; r.cap = slot_p; r.end = r.base + slot_p * kRunBytes;
+    return r;
+}
+__device__ __forceinline__ int32_t ring_next(const Ring &r, int32_t at)
+{
+    const int32_t n = at + r.stride;
+    return n == r.end ? r.base : n;
+}
 
 // kComp: the segments of a configuration have the sizes its composition gives (Section 8) instead of one size
 // and a smaller last one; every lane keeps the part of the composition that starts at its segment.
 template <typename T, int G, bool kComp>
-__device__ __forceinline__ void uni_times_body(T *ring, const ConfigArrays &cfg, int32_t p_max, int32_t q_max, int model,
-                                               const TimesOut &times, PlanHeader *plan, const int32_t *order, int cls, int part,
-                                               T *slot, int32_t slot_p)
+__device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &shape, const ConfigArrays &cfg, int32_t p_max, int32_t q_max,
+                                               int model, const TimesOut &times, PlanHeader *plan, const int32_t *order, int cls,
+                                               int part, char *slot, int32_t slot_p)
 {
-    constexpr int M = kRing - 1;
+    constexpr int kGroups = kWave / G;
+    // a new configuration is fetched (a path every lane waits for) when this many groups have nothing to do
+    constexpr int kFetchGroups = kGroups >= 8 ? kGroups / 8 : 1;
+    // steps between two looks for room in the ring and for the end of a segment (small groups have short segments)
+    constexpr int kChunk = G >= 8 ? 4 : 2;
     const int lane = lane_id(), gl = lane & (G - 1), gbase = lane & ~(G - 1);
     const int prod = gbase | ((gl + G - 1) & (G - 1));
     const uint64_t gmask = (G == 64 ? ~UINT64_C(0) : ((UINT64_C(1) << G) - 1)) << gbase;
-    T *mybuf = slot + static_cast<size_t>(lane) * 2 * slot_p;       // [2][slot_p]
-    const T *prodbuf = slot + static_cast<size_t>(prod) * 2 * slot_p;
     // part of the class this pass works on: all of it, its giant configurations only, or the rest after those
     int32_t count = plan->class_count[cls], begin = plan->class_begin[cls];
     unsigned long long *tickets = &plan->ticket[cls];
     if (part == kGiantPart) { count = plan->giant_count; tickets = &plan->ticket_giant; }
     else if (part == kRestPart) { begin += plan->giant_count; count -= plan->giant_count; }
-    const T kInf = CostTraits<T>::inf();
+    if (count == 0) return;
 
     // ---- per-group state (the same in all lanes of a group)
-    bool have = false, exhausted = false;
+    bool have = false, exhausted = false, in_slot = false;
     int64_t ci = 0;
     int p = 2, q = 1;
     T c_full = 0, g_full = 0, c_last = 0, g_last = 0;
     T alpha = 0, beta = 0, gamma = 0;   // kComp only
-    uint32_t rest = 0;                  // kComp only: the composition from my segment on (per lane)
-    // ---- per-lane state.  Positions count the entries of a stream from the start of the configuration:
-    // every finished segment adds p of them.
-    int k = 0;                      // segment this lane is running (>= q: none left)
-    int par = 0, apar = 0;          // which of the two buffers my segment writes / my input stream is in
-    int wtot = 0, segBase = 0;      // entries I have written; the same at the start of my segment
-    int apos = 0, astart = 0;       // next entry of my input stream; its first entry
-    int bpos = 0;                   // next entry of my own stream whose B value is unread
-    T lastS = 0, cc = 0, gg = 0;
-    bool farA = false, farB = false, anyFar = false;
-    T la0 = 0, la1 = 0, lb0 = 0, lb1 = 0;   // entries loaded from the workspace in the previous iteration
+    uint32_t comp = 0, rest = 0;        // kComp only: the composition; the part of it from my segment on (per lane)
+    // ---- per-lane state
+    Ring own = lds_ring<G>(lds, lane, shape), in = lds_ring<G>(lds, prod, shape);    // my output stream, my input stream
+    bool active = false;            // this lane has a segment to run
+    int k = 0;                      // which one
+    int left = 0;                   // pairs it still has to form
+    int aleft = 0;                  // processors of my input stream not taken yet
+    int32_t aat = 0, bat = 0;       // places of the heads of A (in my producer's ring) and B (in mine)
+    int32_t wat = 0, wlast = 0;     // place of the next run to write; of the newest one (wat if the segment has none): published before it
+    int odd = 0;                    // processor left over from an earlier value
+    T lastS = 0, cc = 0, gg = 0;    // value of the newest run (-1: none in this segment), costs of my segment
+    int lastN = 0;                  // its count
+
+    auto put = [&](auto to_slot, int32_t at, T v, int n) {
+        if (decltype(to_slot)::value) {
+            Run<T> *e = reinterpret_cast<Run<T> *>(slot + at);
+            e->v = v; e->n = n;
+        } else {
+            auto *e = lds_run<T>(at);
+            e->v = v; e->n = n;
+        }
+    };
+    auto segment_costs = [&]() {
+        cc = k == q - 1 ? c_last : c_full; gg = k == q - 1 ? g_last : g_full;
+        if (kComp) {
+            const T sz = static_cast<T>(rest ? comp_first(rest) : 1);
+            const T bs = beta * sz;                                          // each product and sum rounded on its own
+            cc = alpha + bs; gg = gamma * sz;
+        }
+    };
+    // first segment of every lane; the input stream of segment 0 is p processors at time 0
+    auto start_configuration = [&](auto to_slot) {
+        k = gl; active = k < q;
+        left = active ? p - 1 : 0; aleft = p; odd = 0; lastS = T(-1); lastN = 0;
+        aat = in.base;
+        wat = own.base;
+        if (gl == G - 1) { put(to_slot, wat, T(0), p); wat = ring_next(own, wat); }
+        put(to_slot, wat, T(0), 0);
+        bat = wlast = wat;
+        if (kComp) rest = comp_drop(comp, gl);
+        segment_costs();
+    };
 
     for (;;) {
-        // ---------------------------------------------------------------- fetch a configuration
-        if (!have && !exhausted) {
-            unsigned long long got = atomicAdd(tickets, gl == 0 ? 1ULL : 0ULL);
-            int64_t ticket = static_cast<int64_t>(got);
-            if (G > 1) {
-                const uint32_t lo = __shfl(static_cast<uint32_t>(got), 0, G), hi = __shfl(static_cast<uint32_t>(got >> 32), 0, G);
-                ticket = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-            }
-            if (ticket >= count) {
-                exhausted = true;
-            } else {
-                ci = order[begin + ticket];
-                const Config<T> c = decode_config<T>(cfg, ci, p_max, q_max);
-                if (gl == 0) {
-                    if (!kComp) write_closed_forms<T>(times, ci, c, model);
-                    if (times.cfg_status) times.cfg_status[ci] = c.status;
-                    if (c.status != PRS_CFG_OK && times.greedy) static_cast<T *>(times.greedy)[ci] = CostTraits<T>::bad();
-                }
-                if (c.status == PRS_CFG_OK) {
-                    have = true;
-                    p = c.p; q = c.q;
-                    c_full = c.c_full; g_full = c.g_full; c_last = c.c_last; g_last = c.g_last;
-                    k = gl; par = 0; apar = gl == 0 ? 1 : 0;
-                    wtot = segBase = apos = astart = bpos = 0;
-                    lastS = 0; farA = farB = false;
-                    cc = k == q - 1 ? c_last : c_full; gg = k == q - 1 ? g_last : g_full;
-                    if (kComp) {
-                        alpha = c.alpha; beta = c.beta; gamma = c.gamma;
-                        rest = comp_drop(c.comp, gl);
-                        const T sz = static_cast<T>(rest ? comp_first(rest) : 1);
-                        const T bs = beta * sz;                               // each product and sum rounded on its own
-                        cc = alpha + bs; gg = gamma * sz;
+        // ---------------------------------------------------------------- fetch configurations
+        const uint64_t need = ballot64(gl == 0 && !have && !exhausted);
+        if (need != 0) {
+            const unsigned long long got = atomicAdd(tickets, lane == 0 ? static_cast<unsigned long long>(__builtin_popcountll(need)) : 0ULL);
+            const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(got)),
+                           hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(got >> 32));
+            const int64_t first = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+            if (!have && !exhausted) {
+                const int64_t ticket = first + __builtin_popcountll(need & ((UINT64_C(1) << gbase) - 1));
+                if (ticket >= count) {
+                    exhausted = true;
+                } else {
+                    ci = order[begin + ticket];
+                    const Config<T> c = decode_config<T>(cfg, ci, p_max, q_max);
+                    if (gl == 0) {
+                        if (!kComp) write_closed_forms<T>(times, ci, c, model);
+                        if (times.cfg_status) times.cfg_status[ci] = c.status;
+                        if (c.status != PRS_CFG_OK && times.greedy) static_cast<T *>(times.greedy)[ci] = CostTraits<T>::bad();
+                    }
+                    if (c.status == PRS_CFG_OK) {
+                        have = true; in_slot = false;
+                        p = c.p; q = c.q;
+                        c_full = c.c_full; g_full = c.g_full; c_last = c.c_last; g_last = c.g_last;
+                        if (kComp) { alpha = c.alpha; beta = c.beta; gamma = c.gamma; comp = c.comp; }
+                        own = lds_ring<G>(lds, lane, shape); in = lds_ring<G>(lds, prod, shape);
+                        start_configuration(BoolConst<false>());
                     }
                 }
             }
         }
         if (ballot64(have) == 0 && ballot64(!exhausted) == 0) break;
 
-        const bool active = have && k < q;
-
-        // ---------------------------------------------------------------- what the neighbours have done so far
-        int pw = wtot;
-        T plast = lastS;
-        if (G > 1) {
-            pw = __shfl(wtot, prod, kWave);
-            plast = __shfl(lastS, prod, kWave);
-        }
-        const bool first = k == 0;
-        const int aend = astart + p;
-        const int availEnd = first ? aend : (pw < aend ? pw : aend);
-        // every missing value is >= front (nothing is known before the producer has started this stream)
-        const T front = (first || pw >= aend) ? kInf : (pw > astart ? plast : T(0));
-
-        // ---------------------------------------------------------------- heads of A and B
-        T a0 = ring[(apos & M) * kWave + prod], a1 = ring[((apos + 1) & M) * kWave + prod];
-        T sb0 = ring[(bpos & M) * kWave + lane], sb1 = ring[((bpos + 1) & M) * kWave + lane];
-        if (anyFar) {                       // the same in all lanes: only this path waits for the loads below
-            PRS_KEEP_BRANCH();
-            if (farA) { a0 = la0; a1 = la1; }
-            if (farB) { sb0 = lb0; sb1 = lb1; }
-        }
-        if (first) { a0 = 0; a1 = 0; }
-        T b0 = wrap_add<T>(sb0, gg), b1 = wrap_add<T>(sb1, gg);
-        if (!(apos < availEnd)) a0 = kInf;
-        if (!(apos + 1 < availEnd)) a1 = kInf;
-        if (!(bpos < wtot)) b0 = kInf;
-        if (!(bpos + 1 < wtot)) b1 = kInf;
-
-        // ---------------------------------------------------------------- the two smallest; e2 is the larger one
-        const bool x = a0 <= b0;
-        const T u = x ? a1 : a0, v = x ? b0 : b1;
-        const bool y = u <= v;
-        const T e2 = y ? u : v;
-        const int dA = (x ? 1 : 0) + (y ? 1 : 0);
-        // (My buffer `par` held my stream of two rounds ago.  Its reader is through with it: I can only have
-        // finished the round in between after the first lane of the group finished it, and every lane after the
-        // first had to read its producer's whole stream to finish.)
-        const bool ok = active && e2 < kInf && e2 <= front;
-
-        // ---------------------------------------------------------------- new state of the lane
-        const T tc = wrap_add<T>(e2, cc), tr = wrap_add<T>(tc, gg);           // sender leaves at tc, receiver stays until tr
-        const int w0 = wtot, i = wtot - segBase;
-        const bool seg_end = ok && i == p - 2;                                // the last receiver is the root
-        const bool last_seg = seg_end && k == q - 1;
-        T *const wbuf = mybuf + static_cast<size_t>(par) * slot_p;
-        if (ok) {
-            lastS = tc;
-            ++wtot;
-            apos += dA; bpos += 2 - dA;
-            if (seg_end) {
-                lastS = tr;
-                ++wtot;
-                k += G; par ^= 1;
-                segBase = wtot; bpos = wtot;
-                astart = gl == 0 ? segBase - p : segBase;                     // the stream my producer writes in its current round
-                apar = gl == 0 ? par ^ 1 : par;
-                apos = astart;
-                cc = k == q - 1 ? c_last : c_full; gg = k == q - 1 ? g_last : g_full;
-                if (kComp) {
-                    rest = comp_drop(rest, G);
-                    const T sz = static_cast<T>(rest ? comp_first(rest) : 1);
-                    const T bs = beta * sz;
-                    cc = alpha + bs; gg = gamma * sz;
+        // ---------------------------------------------------------------- steps
+        bool moved = false;
+        auto steps = [&](auto with_slots) {
+            constexpr bool kSlots = decltype(with_slots)::value;      // some lanes have their rings in the workspace slot
+            auto store = [&](int32_t at, T v, int n) {
+                if (kSlots && in_slot) put(BoolConst<true>(), at, v, n); else put(BoolConst<false>(), at, v, n);
+            };
+            for (int it = 0; it < kSpan; it += kChunk) {
+                // ---- is there room in my ring for the runs of a chunk of steps, the root's and the open place?
+                const int32_t reader = from_next<G>(active ? aat : kRetired, gl);
+                int32_t held = wat - reader, heldB = wat - bat;       // bytes of the ring not read yet
+                if (held < 0) held += own.end - own.base;
+                if (heldB < 0) heldB += own.end - own.base;
+                if (reader == kRetired) held = 0;
+                const int32_t most = (own.cap - 3 - kChunk) * own.stride;
+                const bool room = held <= most && heldB <= most;
+#pragma unroll
+                for (int c = 0; c < kChunk; ++c) {
+                    // ---- the heads of A and B
+                    const int32_t upto = from_previous<G>(wlast, gl); // my producer has published its stream up to here
+                    T va, vb;
+                    int na, nb;
+                    if (kSlots && in_slot) {
+                        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");      // stores of earlier steps have landed
+                        const Run<T> *ea = reinterpret_cast<const Run<T> *>(slot + aat), *eb = reinterpret_cast<const Run<T> *>(slot + bat);
+                        va = ea->v; na = ea->n; vb = eb->v; nb = eb->n;
+                    } else {
+                        const auto *ea = lds_run<T>(aat), *eb = lds_run<T>(bat);
+                        va = ea->v; na = ea->n; vb = eb->v; nb = eb->n;
+                    }
+                    asm volatile("" : "+v"(va), "+v"(vb), "+v"(na), "+v"(nb));       // the loads stay together, outside the branches below
+                    const bool avail = aat != upto;                   // else va is the value of the open run: a bound of what follows
+                    const T a = or_absent<T>(aleft > 0, va), b = or_absent<T>(bat != wat, wrap_add<T>(vb, gg));
+                    const bool le = a <= b, ge = b <= a, go = room & (left > 0);
+                    const bool takeA = go & avail & le, takeB = go & ge & (avail | !le);
+                    const int an = takeA ? na : 0, x = odd + an + (takeB ? nb : 0), pairs = x >> 1;
+                    odd = x & 1;
+                    aleft -= an;
+                    aat = takeA ? ring_next(in, aat) : aat;
+                    bat = takeB ? ring_next(own, bat) : bat;
+                    moved = moved | takeA | takeB;
+                    // ---- the pairs that start now: a run of my stream, or more of its newest run (unless B has taken that)
+                    const T tc = wrap_add<T>(takeA ? a : b, cc);
+                    const bool some = pairs > 0, join = some & (tc == lastS) & (bat != wat), fresh = some & !join;
+                    const int n = pairs + (join ? lastN : 0);
+                    wlast = fresh ? wat : wlast;
+                    wat = fresh ? ring_next(own, wat) : wat;
+                    left -= pairs;
+                    if (some) { store(wlast, tc, n); lastS = tc; lastN = n; }
+                }
+                // ---- end of a segment
+                const bool seg_end = active && left == 0;
+                if (ballot64(seg_end) != 0) {
+                    PRS_KEEP_BRANCH();
+                    if (seg_end) {
+                        const T tr = wrap_add<T>(lastS, gg);                // the last receiver is the root
+                        if (tr == lastS) { store(wlast, tr, lastN + 1); }
+                        else { store(wat, tr, 1); wat = ring_next(own, wat); }
+                        store(wat, T(0), 0);
+                        bat = wlast = wat;
+                        if (k == q - 1 && times.greedy) static_cast<T *>(times.greedy)[ci] = tr;
+                        k += G;
+                        active = k < q;
+                        lastS = T(-1); odd = 0; left = active ? p - 1 : 0; aleft = p;
+                        if (kComp) rest = comp_drop(rest, G);
+                        segment_costs();
+                    }
+                    const uint64_t on = ballot64(active);
+                    if ((on & gmask) == 0) have = false;
+                    if (on == 0 || __builtin_popcountll(ballot64(!have && !exhausted)) >= kFetchGroups * G) break;
                 }
             }
-        }
-        const bool on = have && k < q;
-        const uint64_t on_mask = ballot64(on);
-        if ((on_mask & gmask) == 0) have = false;                            // every lane of the group is through: fetch next
-
-        // ---------------------------------------------------------------- entries too far back for LDS: load them now
-        // (before this iteration's stores, so that waiting for the loads does not wait for those; what is
-        // loaded was written in earlier iterations)
-        farA = on && k > 0 && pw - apos > kNear;
-        farB = on && w0 - bpos > kNear;
-        anyFar = ballot64(farA || farB) != 0;
-        if (anyFar) {
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");            // stores of earlier iterations have landed
-            if (farA) {
-                const int i0 = apos - astart < p ? apos - astart : p - 1, i1 = i0 + 1 < p ? i0 + 1 : p - 1;
-                la0 = prodbuf[static_cast<size_t>(apar) * slot_p + i0];
-                la1 = prodbuf[static_cast<size_t>(apar) * slot_p + i1];
-            }
-            if (farB) {
-                const int i0 = bpos - segBase;
-                lb0 = mybuf[static_cast<size_t>(par) * slot_p + i0];
-                lb1 = mybuf[static_cast<size_t>(par) * slot_p + i0 + 1];
-            }
+        };
+        if (ballot64(active) != 0) {
+            if (ballot64(have && in_slot) != 0) steps(BoolConst<true>()); else steps(BoolConst<false>());
         }
 
-        // ---------------------------------------------------------------- this pair's entries
-        if (ok) {
-            wbuf[i] = tc;
-            ring[(w0 & M) * kWave + lane] = tc;
-            if (seg_end) {
-                wbuf[p - 1] = tr;
-                ring[((w0 + 1) & M) * kWave + lane] = tr;
-                if (last_seg && times.greedy) static_cast<T *>(times.greedy)[ci] = tr;
+        // ---------------------------------------------------------------- a group in which no lane moves will never move again
+        const bool stuck = have && (ballot64(moved) & gmask) == 0;
+        if (ballot64(stuck) != 0) {
+            PRS_KEEP_BRANCH();
+            if (stuck) {
+                if (in_slot) {                                              // cannot happen (see above): give it up rather than wait for ever
+                    if (gl == 0) {
+                        if (times.cfg_status) times.cfg_status[ci] = PRS_CFG_STALLED;
+                        if (times.greedy) static_cast<T *>(times.greedy)[ci] = CostTraits<T>::bad();
+                    }
+                    have = active = false; left = 0;
+                } else {
+                    in_slot = true;
+                    own = slot_ring(lane, slot_p); in = slot_ring(prod, slot_p);
+                    start_configuration(BoolConst<true>());
+                }
             }
         }
     }
@@ -225,29 +340,32 @@ __device__ __forceinline__ void uni_times_body(T *ring, const ConfigArrays &cfg,
 // configurations (largest groups) to the lightest, so the long-running ones start first and the light
 // ones fill the machine around them.
 template <typename T, bool kComp>
-__global__ __launch_bounds__(kWave) void uni_times_kernel(ConfigArrays cfg, int32_t p_max, int32_t q_max, int model, TimesOut times,
-                                                          PlanHeader *plan, const int32_t *order, char *slots, size_t slot_bytes,
-                                                          int32_t slot_p)
+__global__ __launch_bounds__(kWave) void uni_times_kernel(RingShape shape, ConfigArrays cfg, int32_t p_max, int32_t q_max, int model,
+                                                          TimesOut times, PlanHeader *plan, const int32_t *order, char *slots,
+                                                          size_t slot_bytes, int32_t slot_p)
 {
     PRS_DYNAMIC_LDS(lds_raw);
-    T *ring = reinterpret_cast<T *>(lds_raw);                    // [kRing][64]
-    T *slot = reinterpret_cast<T *>(slots + static_cast<size_t>(blockIdx.x) * slot_bytes);
-    // configurations of millions of pairs trail their predecessor segment by thousands of entries: a whole wavefront each
-    uni_times_body<T, 64, kComp>(ring, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kGiantPart, slot, slot_p);
+    const int32_t lds = static_cast<int32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char *)lds_raw));
+    char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
+    uni_times_body<T, 64, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kGiantPart, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 32, kComp>(ring, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kRestPart, slot, slot_p);
+    uni_times_body<T, 32, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kRestPart, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 16, kComp>(ring, cfg, p_max, q_max, model, times, plan, order, 2, kWholeClass, slot, slot_p);
+    uni_times_body<T, 16, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, 4, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 4, kComp>(ring, cfg, p_max, q_max, model, times, plan, order, 1, kWholeClass, slot, slot_p);
+    uni_times_body<T, 8, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, 3, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 1, kComp>(ring, cfg, p_max, q_max, model, times, plan, order, 0, kWholeClass, slot, slot_p);
+    uni_times_body<T, 4, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, 2, kWholeClass, slot, slot_p);
+    __syncthreads();
+    uni_times_body<T, 2, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, 1, kWholeClass, slot, slot_p);
+    __syncthreads();
+    uni_times_body<T, 1, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, 0, kWholeClass, slot, slot_p);
 }
 
 template <typename T, bool kComp>
 static void launch_uni_times_as(const UniLaunch &L)
 {
-    hipLaunchKernelGGL((uni_times_kernel<T, kComp>), dim3(L.grid), dim3(kWave), uni_times_lds_bytes(), L.stream, L.cfg, L.p_max,
+    hipLaunchKernelGGL((uni_times_kernel<T, kComp>), dim3(L.grid), dim3(kWave), L.lds_bytes, L.stream, L.rings, L.cfg, L.p_max,
                        L.q_max, L.model, L.times, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p);
 }
 

@@ -159,6 +159,40 @@ def test_uni_every_group_size(prs, grouping):
     _check_schedules(prs, hostf, 0, 160, 80, tuning=tuning)
 
 
+@pytest.mark.parametrize("p_max", [1024, 8192, 40000])
+def test_uni_times_rings_of_runs(prs, p_max):
+    """Completion times of a batch large enough that every group size from 1 to 64 lanes is used, with pair counts on
+    both sides of the limits between them, for each size of the LDS rings.  Three machines keep more receivers
+    combining at different times than a ring holds (tcomp = 1000 tcomm) and start again in the workspace.  Integer
+    costs, fp64 costs and fp64 costs whose sums collide in rounding, bit for bit."""
+    shapes = [(2, 1), (2, 300), (3, 128), (17, 16), (18, 16), (257, 1), (65, 32), (65, 33), (33, 64), (129, 64), (129, 65), (513, 16),
+              (257, 128), (257, 129), (1024, 33), (1024, 128), (1024, 129), (700, 400), (1024, 512), (1000, 520), (31, 9), (64, 5)]
+    rng = np.random.default_rng(31)
+    p = np.array([a for a, _ in shapes] + [300, 1024, 90], np.int32)
+    q = np.array([b for _, b in shapes] + [50, 40, 90], np.int32)
+    n = len(p)
+    m = q.astype(np.int64) * 3
+    m[::3] -= 1                                                        # a smaller last segment
+    m = np.maximum(m, 1)
+    al, ga = rng.integers(0, 12, n).astype(np.int64), rng.integers(0, 4, n).astype(np.int64)
+    be = rng.integers(1, 4, n).astype(np.int64)
+    al[-3:], be[-3:], ga[-3:] = 0, 1, 1000
+    every = np.arange(40000) % n
+    for cost in ("i64", "f64", "ties"):
+        if cost == "i64":
+            host = prs_inputs.SweepConfigs(p, q, m, al, be, ga, "i64")
+        elif cost == "f64":
+            host = prs_inputs.SweepConfigs(p, q, m, 10.0 ** rng.uniform(-6, -4, n), 10.0 ** rng.uniform(-10, -8, n),
+                                           10.0 ** rng.uniform(-11, -9, n), "f64")
+        else:
+            host = prs_inputs.SweepConfigs(p, q, m, np.full(n, 1.0), np.full(n, 0.0), np.full(n, 2.0 ** -52), "f64")
+        got = prs.simulate_completion_batch(prs.DeviceConfigs.from_host(host.take(every)), 0, p_max, 520)
+        _sync()
+        ref = np.array([O.uni_greedy_time(int(p[i]), O.equi_sizes(int(m[i]), int(q[i])), host.alpha[i].item(), host.beta[i].item(),
+                                          host.gamma[i].item(), host.cost) for i in range(n)])
+        assert np.array_equal(_np(got["greedy"]), ref[every]) and np.all(_np(got["cfg_status"]) == 0)
+
+
 def test_uni_times_a_block_per_configuration(prs):
     """The kernel that gives a machine of thousands of processors a block of its own and forms many pairs of a
     segment at once, here fed with machines of every size (the limit lowered to two processors): completion
