@@ -75,11 +75,14 @@ constexpr size_t kLdsPerCU = 160 * 1024, kLdsPerBlockMax = 64 * 1024, kBitmapLds
 constexpr int kCUs = 256, kMaxBlocksPerCU = 24, kGlobalClassGrid = 1024;
 constexpr int32_t kGroupQMax = 1023;   // the several-per-wavefront bi-greedy kernel counts sent segments in 10 bit planes
 constexpr int kUniGroupSizes = 3;        // group sizes below the largest; the classes between them and the last stay empty
-// completion times: most pairs of a configuration run by 1, 2, 4, 8, 16 lanes; larger ones by 32, from 2^kUniTimesGiantLog2 pairs
-// on by 64.  Fewer lanes than this and the deep ring of a group overflows (limits twice as high: 300 configurations of the
-// 100,000 start again in the workspace, 4.65 ms against 4.15), more and lanes wait for their neighbours (limits half as high:
-// 4.45 ms).  64 lanes halve the time of the longest configurations (4 million pairs: 31 ms on 32 lanes, 13 on 64).
+// completion times: a configuration gets 1, 2, 4, 8 or 16 lanes with at most so many pairs and processors, more get 32, and 64
+// from 2^kUniTimesGiantLog2 pairs on.  With fewer lanes the deep ring of a group overflows and the configuration starts again
+// in the workspace (limits twice as high: 300 of the 100,000, 4.65 ms against 4.15; without the limits on processors 80, 3.75
+// against 3.55), with more of them lanes wait for their neighbours (limits half as high: 4.45 ms).  64 lanes halve the time of
+// the longest configurations (4 million pairs: 31 ms on 32 lanes, 13 on 64).  Compositions have few segments and deeper rings: no
+// limit on processors (1.46 ms against 1.6 to 2.8).
 constexpr int64_t kUniTimesWork[kClasses - 1] = {256, 2048, 8192, 32768, 131072};
+constexpr int32_t kUniTimesProcs[kClasses - 1] = {36, 64, 128, 320, INT32_MAX};
 constexpr int kUniTimesGiantLog2 = 19;
 constexpr int64_t kUniWorkSched[kUniGroupSizes] = {1024, 65536, 262144};  // schedules: by 1, 8, 16 lanes (measured best on the sweep)
 // uni-greedy completion times: machines of at least this many processors would get a block per configuration.  Off: on the
@@ -96,7 +99,6 @@ struct ClassSpec {
     bool lds;                 // state (uni batch) / small arrays and maybe the bitmap (bi general) in LDS
     size_t lds_bytes;
     int32_t lds_bitmap_bytes;
-    RingShape rings;          // kUniTimes
     size_t slot_bytes, slot_offset;
     int grid;
 };
@@ -130,16 +132,8 @@ static void general_spec(ClassSpec &c, int32_t p_cap, int32_t q_cap)
     c.slot_bytes = bi_slot_bytes(p_cap, q_cap, c.lds);
 }
 
-// Rings of a uni-greedy completion-time wavefront in LDS (12 bytes a run): B of a segment, the receivers still combining,
-// has up to 21 runs with 1024 processors, 40 with 15,000, 131 with 45,000 and thousands of segments, and has to fit a ring.
-static RingShape uni_ring_shape(int32_t p_max)
-{
-    if (p_max <= 1024) return RingShape{3413, 32};           // 40 KB: four wavefronts per CU, one per SIMD
-    if (p_max <= 8192) return RingShape{6826, 64};
-    return RingShape{13653, 192};
-}
-
-static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t q_max, const prs_tuning *tuning = nullptr)
+static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t q_max, const prs_tuning *tuning = nullptr,
+                          bool compositions = false)
 {
     Layout L;
     const bool sched = call == PRS_CALL_SCHEDULE;
@@ -154,6 +148,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
     L.limits.by_work = 0;
     for (int k = 0; k < kClasses - 1; ++k) L.limits.work[k] = 0;
     L.limits.giant_log2 = kGiantLog2;
+    L.limits.lanes_log2 = 0;
     L.limits.wide_p = 0;
     L.wide.grid = 0; L.wide.slot_bytes = 0; L.wide.slot_offset = 0;
     static const int group_lpc[kClasses - 1] = {1, 2, 4, 8, 16};
@@ -161,17 +156,22 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
         // classes by number of pairs (1, 2, 4, 8, 16 or 32 lanes per configuration; schedules 1, 8, 16 or 32), all run by
         // one launch, described by class 0
         L.limits.by_work = 1;
+        for (int k = 0; k < kClasses - 1; ++k) L.limits.p[k] = sched || compositions ? INT32_MAX : kUniTimesProcs[k];
         for (int k = 0; k < kClasses - 1; ++k)
             L.limits.work[k] = sched ? kUniWorkSched[k < kUniGroupSizes ? k : kUniGroupSizes - 1] : kUniTimesWork[k];
         if (!sched) {
             L.limits.giant_log2 = kUniTimesGiantLog2;
             // A batch that leaves lanes without a configuration gives each of its configurations more of them.
-            const int64_t lanes = static_cast<int64_t>(kLdsPerCU / uni_times_lds_bytes(uni_ring_shape(p_max))) * kCUs * kWave;
+            const int64_t lanes = static_cast<int64_t>(kLdsPerCU / uni_times_lds_bytes(p_max, compositions)) * kCUs * kWave;
             for (int k = 0; k < kClasses - 1; ++k)
                 if (n << (k + 1) <= lanes) L.limits.work[k] = 0;
             if (n << 6 <= lanes) L.limits.giant_log2 = 0;
+            else L.limits.lanes_log2 = 1;
         }
         if (tuning) {                                              // never changes a result, only who runs what
+            L.limits.lanes_log2 = 0;
+            L.limits.giant_log2 = sched ? kGiantLog2 : kUniTimesGiantLog2;
+            for (int k = 0; k < kClasses - 1; ++k) L.limits.p[k] = INT32_MAX;
             const int64_t a = tuning->uni_group_pairs[0], b = tuning->uni_group_pairs[1], c3 = tuning->uni_group_pairs[2];
             if (a >= 0 && b >= a && c3 >= b) {
                 if (sched) {
@@ -191,8 +191,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             c.kind = sched ? kUniSched : kUniTimes; c.lpc = 0; c.rows_per_group = 0; c.lds = true; c.lds_bitmap_bytes = 0;
             // schedules: keeps every per-lane array 64-byte aligned; times: a ring of p + 4 runs per lane
             c.p_cap = sched ? (p_max + 15) / 16 * 16 : (p_max + 4 + 15) / 16 * 16;
-            c.rings = uni_ring_shape(p_max);
-            c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes(c.rings);
+            c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes(p_max, compositions);
             c.slot_bytes = k != 0 ? 0 : (sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap));
             int64_t g = static_cast<int64_t>(kLdsPerCU / c.lds_bytes) * kCUs;
             while (g > 1 && static_cast<size_t>(g) * c.slot_bytes > kMaxWorkspace) g /= 2;
@@ -314,7 +313,7 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
     if (comp_m > 0 && (call != PRS_CALL_SIMULATE || model != PRS_UNI)) return PRS_EINVAL;   // compositions: uni-greedy times only
     if (n == 0) return PRS_OK;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255)) return PRS_EINVAL;
-    const Layout lay = make_layout(call, model, n, p_max, q_max, tuning);
+    const Layout lay = make_layout(call, model, n, p_max, q_max, tuning, comp_m > 0);
     if (workspace_bytes < lay.total) return PRS_ENOSPC;
     char *ws = static_cast<char *>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -338,7 +337,6 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
         L.lds_p = c.lds ? c.p_cap : 0;
         L.lds_bitmap_bytes = c.lds_bitmap_bytes;
         L.lds_bytes = c.lds_bytes;
-        L.rings = c.rings;
         L.slots = ws + c.slot_offset;
         L.slot_bytes = c.slot_bytes;
         L.slot_p = c.p_cap; L.slot_q = c.q_cap;
@@ -580,7 +578,7 @@ static UnequalLayout make_unequal_layout(int64_t n, int32_t p_max, int32_t m_max
     U.times = take(static_cast<size_t>(U.n_exp) * 8);
     U.status = take(static_cast<size_t>(U.n_exp) * 4);
     U.sim = off;
-    U.total = off + make_layout(PRS_CALL_SIMULATE, PRS_UNI, U.n_exp, p_max, m_max).total;
+    U.total = off + make_layout(PRS_CALL_SIMULATE, PRS_UNI, U.n_exp, p_max, m_max, nullptr, true).total;
     return U;
 }
 

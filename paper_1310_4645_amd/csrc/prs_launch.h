@@ -22,6 +22,7 @@ struct SchedOut {
 // Rings of a wavefront of the uni-greedy completion-time kernel in LDS: `runs` runs in all, runs_per_lane for every lane but
 // the last of a group, which shares what is left with the last lanes of the other groups.
 struct RingShape { int32_t runs, runs_per_lane; };
+constexpr int32_t kUniSmallProcs = 1024;
 
 // One launch = one size class of the plan.  lds_p > 0: per-configuration state lives in LDS arrays sized
 // for lds_p processors (uni) / the small arrays and, if it fits lds_bitmap_bytes, the sent bitmap (bi);
@@ -39,7 +40,6 @@ struct UniLaunch {
     int32_t lds_p;
     int32_t lds_bitmap_bytes;
     size_t lds_bytes;
-    RingShape rings;             // uni-greedy completion times
     char *slots;
     size_t slot_bytes;
     int32_t slot_p, slot_q;
@@ -83,7 +83,7 @@ size_t bi_group_lds_bytes(int lpc);
 int bi_group_list_capacity(int lpc);
 hipError_t launch_bi_group(const BiGroupLaunch &L);
 // uni-greedy: all classes of a batch in one launch
-size_t uni_times_lds_bytes(const RingShape &s);
+size_t uni_times_lds_bytes(int32_t p_max, bool compositions);
 size_t uni_times_slot_bytes(int32_t p_cap);
 hipError_t launch_uni_times(const UniLaunch &L);
 size_t uni_sched_lds_bytes();

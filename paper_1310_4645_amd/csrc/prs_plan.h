@@ -30,13 +30,15 @@ enum ClassPart { kWholeClass = 0, kGiantPart = 1, kRestPart = 2 };
 
 // By size (by_work == 0): class k holds p <= limits.p[k]; the last class the rest and every configuration
 // with more than q segments.
-// By work (by_work != 0): class k holds the configurations with at most work[k] pairs, the last class the rest.
+// By work (by_work != 0): class k holds the configurations with at most work[k] pairs and p[k] processors, the last class
+// the rest.
 struct ClassLimits {
     int32_t p[kClasses - 1];
     int32_t q;
     int32_t by_work;
     int64_t work[kClasses - 1];
     int32_t giant_log2;          // configurations of the last class with at least 2^giant_log2 pairs are "giant"
+    int32_t lanes_log2;          // by_work only: 1: class k has 2^k lanes per configuration, and none gets more than it has segments
     int32_t wide_p;              // by_work only: machines of at least this many processors form the class kWideClass (0: none)
 };
 

@@ -12,7 +12,8 @@ __device__ __forceinline__ int plan_bucket(const ConfigArrays &cfg, int64_t i, i
     int cls = kClasses - 1;
     if (lim.by_work) {
         for (int k = kClasses - 2; k >= 0; --k)
-            if (work <= lim.work[k]) cls = k;
+            if (work <= lim.work[k] && c.p <= lim.p[k]) cls = k;
+        if (lim.lanes_log2) { const int enough = ceil_log2(c.q); cls = cls < enough ? cls : enough; }
         if (lim.wide_p > 0 && c.p >= lim.wide_p && cfg.comp_m == 0) cls = kWideClass;
     } else {
         for (int k = kClasses - 2; k >= 0; --k)

@@ -33,10 +33,11 @@
 // always suffices: a segment cannot have sent more processors than the lane that reads its stream has
 // taken from the stream before it, so at most p are waiting to be read.
 //
-// Measured (pair by pair with streams in global memory -> runs in LDS rings): the 100,000-configuration sweep
-// 11.9 -> 4.1 ms, 64 machines of 1024 to 65536 processors 587 -> 7.4 ms, 986 x 512 segmentations of a short message
-// 10.4 -> 1.9 ms.  A step is about 65 instructions and takes 240 ns with one wavefront per SIMD: what bounds it now is
-// the latency of that chain (LDS read, two compares, two additions).
+// Measured (pair by pair with streams in global memory -> runs in LDS rings -> 27 KB of rings, six wavefronts per CU instead
+// of four, and tickets drawn several at a time): the 100,000-configuration sweep 11.9 -> 4.1 -> 3.55 ms, 64 machines of
+// 1024 to 65536 processors 587 -> 7.4 -> 7.0 ms, 986 x 512 segmentations of a short message 10.4 -> 1.94 -> 1.43 ms.  A step is
+// about 65 instructions, a chain of an LDS read, two compares and two additions, and takes 240 ns on a SIMD of its own:
+// that latency is what bounds it, with one or two wavefronts per SIMD.
 #include "prs_device.h"
 #include "prs_launch.h"
 
@@ -48,7 +49,22 @@ constexpr int32_t kRetired = 1 << 30;            // read place of a lane without
 
 template <typename T> struct __attribute__((packed, aligned(4))) Run { T v; int32_t n; };
 
-size_t uni_times_lds_bytes(const RingShape &s) { return static_cast<size_t>(s.runs) * kRunBytes; }
+// Machines of up to 1024 processors: counts fit 16 bits, and a wavefront keeps its runs in 27 KB, values first: six
+// wavefronts per CU.  B has at most 23 runs on all but a dozen of the 100,000-configuration sweep, and 30 - 3 - 4 of a ring of
+// 30 can wait (the root's run, the open place, the runs of four steps).  Compositions, whose segments differ in size,
+// keep more runs waiting: 40 KB, four wavefronts per CU.
+template <bool kComp> struct SmallRings;
+template <> struct SmallRings<false> { static constexpr int kRuns = 2730, kRing = 30; };
+template <> struct SmallRings<true> { static constexpr int kRuns = 4096, kRing = 36; };
+static RingShape large_rings(int32_t p_max)
+{
+    return p_max <= 8192 ? RingShape{6826, 96} : RingShape{13653, 192};       // B: 40 runs with 15,000 processors, 131 with 45,000
+}
+size_t uni_times_lds_bytes(int32_t p_max, bool compositions)
+{
+    if (p_max <= kUniSmallProcs) return static_cast<size_t>(compositions ? SmallRings<true>::kRuns : SmallRings<false>::kRuns) * 10;
+    return static_cast<size_t>(large_rings(p_max).runs) * kRunBytes;
+}
 size_t uni_times_slot_bytes(int32_t p_cap) { return static_cast<size_t>(kWave) * static_cast<size_t>(p_cap) * kRunBytes; }
 
 // Value of the lane before this one in its group of G (the last lane's for the first), and of the lane after it: moves
@@ -97,35 +113,48 @@ template <typename T> __device__ __forceinline__ T or_absent(bool there, T v)
     return v;
 }
 
-// A place in LDS by its byte address.
-template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) Run<T> *lds_run(int32_t at)
+// Runs in LDS by the byte address of their place.  kSmall: the value there, the count among the 16-bit ones behind all
+// values; otherwise both packed into 12 bytes.
+template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) T *lds_at(int32_t at)
 {
-    return reinterpret_cast<__attribute__((address_space(3))) Run<T> *>(static_cast<uint32_t>(at));
+    return reinterpret_cast<__attribute__((address_space(3))) T *>(static_cast<uint32_t>(at));
+}
+// kSmallRuns: how many runs a wavefront keeps, 0 if they are packed
+template <typename T, int kSmallRuns> __device__ __forceinline__ void lds_load(int32_t at, T &v, int32_t &n)
+{
+    if (kSmallRuns > 0) { v = *lds_at<T>(at); n = *lds_at<uint16_t>((at >> 2) + kSmallRuns * 8); }
+    else { const auto *e = lds_at<Run<T>>(at); v = e->v; n = e->n; }
+}
+template <typename T, int kSmallRuns> __device__ __forceinline__ void lds_store(int32_t at, T v, int32_t n)
+{
+    if (kSmallRuns > 0) { *lds_at<T>(at) = v; *lds_at<uint16_t>((at >> 2) + kSmallRuns * 8) = static_cast<uint16_t>(n); }
+    else { auto *e = lds_at<Run<T>>(at); e->v = v; e->n = n; }
 }
 
-// A ring of `cap` runs at byte addresses base, base + stride, ..., end (exclusive) of LDS or of the workspace slot.
-struct Ring { int32_t base, stride, end, cap; };
+// A ring of runs at byte addresses base, base + stride, ..., end (exclusive) of LDS or of the workspace slot.
+struct Ring { int32_t base, stride, end; };
 
-// Rings of a wavefront in LDS: the last lane of every group has a deep ring, the others ring.runs_per_lane runs.
+// Rings of a wavefront in LDS: the last lane of every group has a deep ring, the others s.runs_per_lane runs.
 // Both kinds are laid out run by run, the lanes side by side, so that lanes at different places of their rings mostly
 // stay on different banks.
-template <int G> __device__ __forceinline__ Ring lds_ring(int32_t lds, int l, const RingShape &s)
+template <int G, bool kSmall> __device__ __forceinline__ Ring lds_ring(int l, const RingShape &s)
 {
-    constexpr int kGroups = kWave / G, kCols = G == 1 ? 0 : (G >= 8 ? kWave : kWave - kGroups);
+    constexpr int kBytes = kSmall ? 8 : kRunBytes, kGroups = kWave / G, kCols = G == 1 ? 0 : (G >= 8 ? kWave : kWave - kGroups);
     const int g = l / G, i = l & (G - 1), shallow = kCols * s.runs_per_lane;
+    int runs = s.runs_per_lane;
     Ring r;
     if (i == G - 1) {
-        r.base = lds + (shallow + g) * kRunBytes; r.stride = kGroups * kRunBytes; r.cap = (s.runs - shallow) / kGroups;
+        r.base = (shallow + g) * kBytes; r.stride = kGroups * kBytes; runs = (s.runs - shallow) / kGroups;
     } else {
-        r.base = lds + (G >= 8 ? l : g * (G - 1) + i) * kRunBytes; r.stride = kCols * kRunBytes; r.cap = s.runs_per_lane;
+        r.base = (G >= 8 ? l : g * (G - 1) + i) * kBytes; r.stride = kCols * kBytes;
     }
-    r.end = r.base + r.cap * r.stride;
+    r.end = r.base + runs * r.stride;
     return r;
 }
 __device__ __forceinline__ Ring slot_ring(int l, int32_t slot_p)
 {
     Ring r;
-    r.base = l * slot_p * kRunBytes; r.stride = kRunBytes; r.cap = slot_p; r.end = r.base + slot_p * kRunBytes;
+    r.base = l * slot_p * kRunBytes; r.stride = kRunBytes; r.end = r.base + slot_p * kRunBytes;
     return r;
 }
 __device__ __forceinline__ int32_t ring_next(const Ring &r, int32_t at)
@@ -136,12 +165,12 @@ __device__ __forceinline__ int32_t ring_next(const Ring &r, int32_t at)
 
 // kComp: the segments of a configuration have the sizes its composition gives (Section 8) instead of one size
 // and a smaller last one; every lane keeps the part of the composition that starts at its segment.
-template <typename T, int G, bool kComp>
-__device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &shape, const ConfigArrays &cfg, int32_t p_max, int32_t q_max,
+template <typename T, int G, bool kComp, bool kSmall>
+__device__ __forceinline__ void uni_times_body(const RingShape &shape, const ConfigArrays &cfg, int32_t p_max, int32_t q_max,
                                                int model, const TimesOut &times, PlanHeader *plan, const int32_t *order, int cls,
                                                int part, char *slot, int32_t slot_p)
 {
-    constexpr int kGroups = kWave / G;
+    constexpr int kGroups = kWave / G, kSmallRuns = kSmall ? SmallRings<kComp>::kRuns : 0;
     // a new configuration is fetched (a path every lane waits for) when this many groups have nothing to do
     constexpr int kFetchGroups = kGroups >= 8 ? kGroups / 8 : 1;
     // steps between two looks for room in the ring and for the end of a segment (small groups have short segments)
@@ -155,6 +184,11 @@ __device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &sha
     if (part == kGiantPart) { count = plan->giant_count; tickets = &plan->ticket_giant; }
     else if (part == kRestPart) { begin += plan->giant_count; count -= plan->giant_count; }
     if (count == 0) return;
+    // Tickets are drawn several at a time, a sixteenth of a wavefront's share at most (a counter that every wavefront adds to
+    // serves one of them every few nanoseconds); those in hand are hand .. hand_end - 1, and may lie past the end.
+    int batch = count / (static_cast<int>(gridDim.x) * 16);
+    if (batch > 4 * kGroups) batch = 4 * kGroups;
+    int64_t hand = 0, hand_end = 0;
 
     // ---- per-group state (the same in all lanes of a group)
     bool have = false, exhausted = false, in_slot = false;
@@ -164,7 +198,7 @@ __device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &sha
     T alpha = 0, beta = 0, gamma = 0;   // kComp only
     uint32_t comp = 0, rest = 0;        // kComp only: the composition; the part of it from my segment on (per lane)
     // ---- per-lane state
-    Ring own = lds_ring<G>(lds, lane, shape), in = lds_ring<G>(lds, prod, shape);    // my output stream, my input stream
+    Ring own = lds_ring<G, kSmall>(lane, shape), in = lds_ring<G, kSmall>(prod, shape);    // my output stream, my input stream
     bool active = false;            // this lane has a segment to run
     int k = 0;                      // which one
     int left = 0;                   // pairs it still has to form
@@ -180,8 +214,7 @@ __device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &sha
             Run<T> *e = reinterpret_cast<Run<T> *>(slot + at);
             e->v = v; e->n = n;
         } else {
-            auto *e = lds_run<T>(at);
-            e->v = v; e->n = n;
+            lds_store<T, kSmallRuns>(at, v, n);
         }
     };
     auto segment_costs = [&]() {
@@ -209,12 +242,19 @@ __device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &sha
         // ---------------------------------------------------------------- fetch configurations
         const uint64_t need = ballot64(gl == 0 && !have && !exhausted);
         if (need != 0) {
-            const unsigned long long got = atomicAdd(tickets, lane == 0 ? static_cast<unsigned long long>(__builtin_popcountll(need)) : 0ULL);
-            const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(got)),
-                           hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(got >> 32));
-            const int64_t first = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+            // the groups without a configuration take the tickets in hand first, then those just drawn
+            const int wanted = __builtin_popcountll(need), in_hand = static_cast<int>(hand_end - hand);
+            const int more = wanted - in_hand, grab = more > batch ? more : batch;
+            int64_t drawn = 0;
+            if (more > 0) {
+                const unsigned long long got = atomicAdd(tickets, lane == 0 ? static_cast<unsigned long long>(grab) : 0ULL);
+                const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(got)),
+                               hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(got >> 32));
+                drawn = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+            }
             if (!have && !exhausted) {
-                const int64_t ticket = first + __builtin_popcountll(need & ((UINT64_C(1) << gbase) - 1));
+                const int rank = __builtin_popcountll(need & ((UINT64_C(1) << gbase) - 1));
+                const int64_t ticket = rank < in_hand ? hand + rank : drawn + (rank - in_hand);
                 if (ticket >= count) {
                     exhausted = true;
                 } else {
@@ -230,11 +270,13 @@ __device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &sha
                         p = c.p; q = c.q;
                         c_full = c.c_full; g_full = c.g_full; c_last = c.c_last; g_last = c.g_last;
                         if (kComp) { alpha = c.alpha; beta = c.beta; gamma = c.gamma; comp = c.comp; }
-                        own = lds_ring<G>(lds, lane, shape); in = lds_ring<G>(lds, prod, shape);
+                        own = lds_ring<G, kSmall>(lane, shape); in = lds_ring<G, kSmall>(prod, shape);
                         start_configuration(BoolConst<false>());
                     }
                 }
             }
+            hand = more > 0 ? drawn + more : hand + wanted;
+            if (more > 0) hand_end = drawn + grab;
         }
         if (ballot64(have) == 0 && ballot64(!exhausted) == 0) break;
 
@@ -245,6 +287,7 @@ __device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &sha
             auto store = [&](int32_t at, T v, int n) {
                 if (kSlots && in_slot) put(BoolConst<true>(), at, v, n); else put(BoolConst<false>(), at, v, n);
             };
+            __builtin_amdgcn_s_waitcnt(0);                            // nothing in the loop waits for what was asked for before it
             for (int it = 0; it < kSpan; it += kChunk) {
                 // ---- is there room in my ring for the runs of a chunk of steps, the root's and the open place?
                 const int32_t reader = from_next<G>(active ? aat : kRetired, gl);
@@ -252,7 +295,7 @@ __device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &sha
                 if (held < 0) held += own.end - own.base;
                 if (heldB < 0) heldB += own.end - own.base;
                 if (reader == kRetired) held = 0;
-                const int32_t most = (own.cap - 3 - kChunk) * own.stride;
+                const int32_t most = own.end - own.base - (3 + kChunk) * own.stride;
                 const bool room = held <= most && heldB <= most;
 #pragma unroll
                 for (int c = 0; c < kChunk; ++c) {
@@ -265,8 +308,8 @@ __device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &sha
                         const Run<T> *ea = reinterpret_cast<const Run<T> *>(slot + aat), *eb = reinterpret_cast<const Run<T> *>(slot + bat);
                         va = ea->v; na = ea->n; vb = eb->v; nb = eb->n;
                     } else {
-                        const auto *ea = lds_run<T>(aat), *eb = lds_run<T>(bat);
-                        va = ea->v; na = ea->n; vb = eb->v; nb = eb->n;
+                        lds_load<T, kSmallRuns>(aat, va, na);
+                        lds_load<T, kSmallRuns>(bat, vb, nb);
                     }
                     asm volatile("" : "+v"(va), "+v"(vb), "+v"(na), "+v"(nb));       // the loads stay together, outside the branches below
                     const bool avail = aat != upto;                   // else va is the value of the open run: a bound of what follows
@@ -339,34 +382,39 @@ __device__ __forceinline__ void uni_times_body(int32_t lds, const RingShape &sha
 // One launch for the whole batch: every wavefront works through the classes from the heaviest
 // configurations (largest groups) to the lightest, so the long-running ones start first and the light
 // ones fill the machine around them.
-template <typename T, bool kComp>
+template <typename T, bool kComp, bool kSmall>
 __global__ __launch_bounds__(kWave) void uni_times_kernel(RingShape shape, ConfigArrays cfg, int32_t p_max, int32_t q_max, int model,
                                                           TimesOut times, PlanHeader *plan, const int32_t *order, char *slots,
                                                           size_t slot_bytes, int32_t slot_p)
 {
-    PRS_DYNAMIC_LDS(lds_raw);
-    const int32_t lds = static_cast<int32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char *)lds_raw));
+    // LDS is addressed from 0: the kernel has no other LDS than what the launch asks for
+    if (kSmall) shape = RingShape{SmallRings<kComp>::kRuns, SmallRings<kComp>::kRing};
     char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
-    uni_times_body<T, 64, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kGiantPart, slot, slot_p);
+    uni_times_body<T, 64, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kGiantPart, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 32, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kRestPart, slot, slot_p);
+    uni_times_body<T, 32, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kRestPart, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 16, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, 4, kWholeClass, slot, slot_p);
+    uni_times_body<T, 16, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 4, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 8, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, 3, kWholeClass, slot, slot_p);
+    uni_times_body<T, 8, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 3, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 4, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, 2, kWholeClass, slot, slot_p);
+    uni_times_body<T, 4, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 2, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 2, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, 1, kWholeClass, slot, slot_p);
+    uni_times_body<T, 2, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 1, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 1, kComp>(lds, shape, cfg, p_max, q_max, model, times, plan, order, 0, kWholeClass, slot, slot_p);
+    uni_times_body<T, 1, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 0, kWholeClass, slot, slot_p);
 }
 
 template <typename T, bool kComp>
 static void launch_uni_times_as(const UniLaunch &L)
 {
-    hipLaunchKernelGGL((uni_times_kernel<T, kComp>), dim3(L.grid), dim3(kWave), L.lds_bytes, L.stream, L.rings, L.cfg, L.p_max,
-                       L.q_max, L.model, L.times, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p);
+    const RingShape shape = large_rings(L.p_max);
+    if (L.p_max <= kUniSmallProcs)
+        hipLaunchKernelGGL((uni_times_kernel<T, kComp, true>), dim3(L.grid), dim3(kWave), L.lds_bytes, L.stream, shape, L.cfg, L.p_max,
+                           L.q_max, L.model, L.times, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p);
+    else
+        hipLaunchKernelGGL((uni_times_kernel<T, kComp, false>), dim3(L.grid), dim3(kWave), L.lds_bytes, L.stream, shape, L.cfg, L.p_max,
+                           L.q_max, L.model, L.times, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p);
 }
 
 hipError_t launch_uni_times(const UniLaunch &L)
