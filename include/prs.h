@@ -100,9 +100,8 @@ typedef struct prs_times {
  * uni_wide_procs: uni-greedy completion times of machines with at least this many processors are computed by a
  *   whole block per configuration, many pairs of a segment at once (>= 2; else built-in: never, the kernel is
  *   slower than the segment pipeline on every workload measured).
- * bi_list_entries: most entries of the per-configuration list of running transfers in the bi-greedy kernel
- *   for p <= 1024; a configuration that needs more is rerun by the general kernel (1 .. built-in size; else
- *   built-in). */
+ * bi_list_entries: most entries of the per-configuration list of running transfers in the bi-greedy kernels;
+ *   a configuration that needs more is rerun without such a list (1 .. built-in size; else built-in). */
 typedef struct prs_tuning {
     int64_t uni_group_pairs[3];
     int32_t uni_wave_log2;

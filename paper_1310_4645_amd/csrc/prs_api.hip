@@ -237,7 +237,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             c.rows_per_group = static_cast<size_t>(q_cap) * c.lpc;
             c.slot_bytes = c.rows_per_group * 8 * (64 / c.lpc);
         } else if (p_max > L.limits.p[kClasses - 2] && bi_block_lds_bytes(c.p_cap) <= kLdsPerBlockMax) {
-            // thousands of processors: one block of 16 wavefronts per configuration, bit sets in LDS
+            // thousands of processors: one block of 8 wavefronts per configuration
             c.kind = kBiBlock;
             c.lds_bytes = bi_block_lds_bytes(c.p_cap);
             c.slot_bytes = bi_block_slot_bytes(c.p_cap, q_max);
@@ -334,6 +334,7 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
         L.want_schedule = call == PRS_CALL_SCHEDULE;
         L.times = times; L.sched = sched;
         L.plan = P.header; L.order = order; L.cls = cls;
+        L.list_entries = (tuning && tuning->bi_list_entries > 0 && tuning->bi_list_entries < kWave) ? tuning->bi_list_entries : kWave;
         L.lds_p = c.lds ? c.p_cap : 0;
         L.lds_bitmap_bytes = c.lds_bitmap_bytes;
         L.lds_bytes = c.lds_bytes;

@@ -1,26 +1,28 @@
 // Bi-greedy schedules (Lowery & Langou, Algorithm 2, Section 6.2) for machines of thousands of processors on
-// gfx950: one block of 16 wavefronts per configuration.
+// gfx950: one block of eight wavefronts per configuration.
 //
-// The same sequence of set operations as the one-wavefront kernel (every list of Algorithm 2 a bit set over the
-// processors, list lengths population counts, "first k entries" a rank select inside a word, list positions from
-// prefix sums), with the words of the bit sets and the processors spread over the 1024 threads of a block:
-// thread w owns word w of every set, the per-processor times are read 1024 at a time, sums and prefix sums go
-// through the wavefronts and then through LDS.  The bit sets of a visit sit in LDS (7 sets of up to 1024 words),
-// the per-processor times, the pairing lists, the per-segment counters and the sent bitmap in the block's
-// workspace slot.
+// Every list of Algorithm 2 is a bit set over the processors, list lengths are population counts, "first k entries" a
+// rank select inside a word, list positions prefix sums.  run_bi_wide keeps the sets in registers and the running transfers in a
+// list; run_bi_block, which keeps times per processor in the workspace slot, does what does not fit there: more than 65536
+// processors, or more than 64 transfers running at once.
+//
+// What bounds it: the chain of visits of the longest configuration (about 33,000 on 65536 processors and 1000 segments), each
+// one or two sums over the block.  64 machines of 1024 to 65536 processors, completion times: 263 ms with times per processor
+// (about 14 barriers a visit, scattered updates of S, R and C1, all of them read again at every event), 41 ms with
+// run_bi_wide.
 #include "prs_device.h"
 #include "prs_launch.h"
 
 namespace prs {
 
-constexpr int kBlockThreads = 1024;
+constexpr int kBlockThreads = 512;
 constexpr int kBlockWaves = kBlockThreads / kWave;
 
 __host__ __device__ inline size_t bb_align(size_t v) { return (v + 255) / 256 * 256; }
 
 // workspace slot of a block: S, R, C1 (8 B per processor), flags and count of sent segments (4 B), the two pairing
 // lists, the per-segment counters, the sent bitmap [q][W]
-struct BlockSlot { size_t S, R, C1, nsent, sendList, recvList, rem, sent, total; };
+struct BlockSlot { size_t S, R, C1, nsent, sendList, recvList, rem, sent, sets, total; };
 
 __host__ __device__ inline BlockSlot bi_block_slot(int32_t p_cap, int32_t q_cap)
 {
@@ -35,6 +37,7 @@ __host__ __device__ inline BlockSlot bi_block_slot(int32_t p_cap, int32_t q_cap)
     L.recvList = o; o += bb_align((p / 2 + 1) * 4);
     L.rem = o; o += bb_align(q * 4);
     L.sent = o; o += bb_align(W * q * 8);
+    L.sets = o; o += bb_align(W * 16 * kWave);
     L.total = o;
     return L;
 }
@@ -47,6 +50,10 @@ size_t bi_block_lds_bytes(int32_t p_cap)
     return bb_align(W * 8 * 7) + bb_align(W * 2 * 2) + 1024;
 }
 
+// run_bi_block: the same sequence of set operations as the one-wavefront kernel, the words of the bit sets and the processors
+// spread over the threads of the block: thread w owns the words w, w + 512, ... of every set, sums and prefix sums go
+// through the wavefronts and then through LDS.  The bit sets of a visit sit in LDS (7 sets of up to about 1060 words), the
+// per-processor times, the pairing lists, the per-segment counters and the sent bitmap in the block's workspace slot.
 struct BlockScratch {
     int32_t *part;       // [3][kBlockWaves] partial sums of the wavefronts
     double *tpart;       // [kBlockWaves] partial minima (bit patterns of T)
@@ -338,11 +345,340 @@ __device__ T run_bi_block(const Config<T> &c, char *lds, char *slot, const Block
     return Tmax;
 }
 
+// ---- the usual path: sets in registers, running transfers as a list --------------------------------------------------
+//
+// Thread i of the block owns the words i kw .. i kw + kw - 1 of every bit set, kw = 1 or 2, and keeps them in registers.
+// All pairs of a visit (time t, segment j) have the same end of send and end of combine, so the ports and computations
+// of Algorithm 2 are a list of groups (end of send, end of combine, set of senders, set of receivers): lane e of EVERY
+// wavefront holds the two times of entry e, the sets lie in the workspace slot, word by word written and read by the
+// thread that owns the word.  Nothing is kept per processor, and a visit needs one sum over the block (the lengths of the
+// three lists, the prefix counts of the free processors and a few yes/no questions travel in 16 bytes per
+// wavefront) and a second one only if a list has to be cut; a sum is one barrier, with two buffers in turn: a wavefront
+// that writes a buffer again has passed the barrier of the sum in between, which nobody reaches before it has read the first.
+// Processors that have sent everything stay in the sets: they hold no segment, so they never pair.
+constexpr int kWideWords = 65536 / 64 / kBlockThreads;     // words per thread on the largest machine of this path
+constexpr int kWideProcs = kBlockThreads * kWideWords * 64;
+constexpr int kWideEntries = kWave;                        // running transfers, one per lane
+
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_rows(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, ROWS == 0xF);
+}
+// inclusive prefix sum over the 64 lanes by moves inside the vector unit (row_shr 1, 2, 4, 8, then the last lane of a row
+// of 16 to the next row and of the lower half to the upper half)
+__device__ __forceinline__ int dpp_inclusive_scan(int v)
+{
+    v += dpp_rows<0x111, 0xF>(v);
+    v += dpp_rows<0x112, 0xF>(v);
+    v += dpp_rows<0x114, 0xF>(v);
+    v += dpp_rows<0x118, 0xF>(v);
+    v += dpp_rows<0x142, 0xA>(v);
+    v += dpp_rows<0x143, 0xC>(v);
+    return v;
+}
+template <int CTRL, typename T> __device__ __forceinline__ T dpp_min(T v)
+{
+    int32_t w[2];
+    __builtin_memcpy(w, &v, 8);
+    w[0] = dpp_rows<CTRL, 0xF>(w[0]); w[1] = dpp_rows<CTRL, 0xF>(w[1]);
+    T u;
+    __builtin_memcpy(&u, w, 8);
+    return u < v ? u : v;
+}
+// smallest value of the 64 lanes: rotations inside the rows of 16, then one lane of each row
+template <typename T> __device__ __forceinline__ T wave_min_dpp(T v)
+{
+    v = dpp_min<0x128, T>(v); v = dpp_min<0x124, T>(v); v = dpp_min<0x122, T>(v); v = dpp_min<0x121, T>(v);
+    int32_t w[2];
+    __builtin_memcpy(w, &v, 8);
+    T m = v;
+#pragma unroll
+    for (int r = 0; r < kWave; r += 16) {
+        int32_t x[2] = {__builtin_amdgcn_readlane(w[0], r), __builtin_amdgcn_readlane(w[1], r)};
+        T u;
+        __builtin_memcpy(&u, x, 8);
+        m = r == 0 ? u : (u < m ? u : m);
+    }
+    return m;
+}
+
+// Returns false if the list of running transfers would need more than `entries` entries: nothing of the configuration is
+// final then, and run_bi_block does it from the start.
+template <typename T, bool kSched>
+__device__ bool run_bi_wide(const Config<T> &c, int4 *red, uint64_t *rows, uint64_t *sets, int entries, const SchedOut &sched,
+                            int64_t out_base, T *result, int32_t *status)
+{
+    constexpr int K = kWideWords;
+    const int tid = static_cast<int>(threadIdx.x), lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int p = c.p, q = c.q;
+    const int W = (p + 63) >> 6, kw = (W + kBlockThreads - 1) / kBlockThreads, w0 = tid * kw;
+    const uint64_t root = tid == 0 ? UINT64_C(1) : 0;                      // processor 0: bit 0 of word 0
+    const bool ragged = c.sz_last != c.sz, guardL = ragged && c.g_last > 0;
+    const T kInf = CostTraits<T>::inf();
+
+    uint64_t valid[K], sfree[K], rfree[K], compF[K], compL[K], lateL[K], rowNext[K];
+    bool own[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int w = w0 + k;
+        own[k] = k < kw && w < W;
+        valid[k] = !own[k] ? 0 : ((w == W - 1 && (p & 63)) ? (UINT64_C(1) << (p & 63)) - 1 : ~UINT64_C(0));
+        rowNext[k] = 0;
+    }
+    // ---- the list: lane e of every wavefront holds entry e
+    T se = 0, re = 0;
+    bool mine = false, mineShort = false;
+    uint64_t active = 0;                                 // ballot of `mine`
+    const uint64_t full = entries >= kWave ? ~UINT64_C(0) : (UINT64_C(1) << entries) - 1;
+
+    T t = 0, Tmax = 0;
+    int ndone = 0, segStart = 0, jhi = -1, preJ = -1, turn = 0;
+    int64_t emitted = 0;
+    bool anySender = true;
+    const int64_t max_events = 4 * static_cast<int64_t>(p) * q + 16;
+    auto fetch = [&](int j) {                            // row j: who has sent segment j; rows nobody has visited are not written
+        preJ = j;
+#pragma unroll
+        for (int k = 0; k < K; ++k) rowNext[k] = (j <= jhi && own[k]) ? rows[static_cast<size_t>(j) * W + w0 + k] : 0;
+    };
+    auto partial = [&](int a, int b, int d) -> const int4 * {
+        int4 *const part = red + (turn & 1) * kBlockWaves;
+        ++turn;
+        if (lane == kWave - 1) part[wave] = make_int4(a, b, 0, d);
+        __syncthreads();
+        return part;
+    };
+
+    for (int64_t ev = 0;; ++ev) {
+        // ---------------------------------------------------------------- advance time (Algorithm 2: t <- next port release)
+        if (ev > max_events) { *status = PRS_CFG_STALLED; return true; }
+        bool lateOnly = false;
+        if (ev > 0) {
+            // ends of sends and combines after t; and the instants at which the sender of a full segment may take in the
+            // smaller last one, at which only the last segment is visited and which count only while a processor has a
+            // free send port (nothing pairs otherwise before a port frees)
+            T port = kInf, late = kInf;
+            if (mine) {
+                if (se > t) port = se;
+                if (re > t && re < port) port = re;
+                if (guardL && !mineShort && se > t + c.c_last) { const T v = se - c.c_last; if (v > t) late = v; }
+            }
+            T tn = wave_min_dpp<T>(port);
+            if (guardL) {
+                const T tl = wave_min_dpp<T>(late);
+                lateOnly = anySender && tl < tn;
+                if (lateOnly) tn = tl;
+            }
+            if (!(tn < kInf)) { *status = PRS_CFG_STALLED; return true; }
+            t = tn;
+        }
+        int j = lateOnly ? q - 1 : segStart;
+        fetch(j);
+        // ---- port and computation sets from the transfers that still run
+        {
+            mine = mine && (se > t || re > t);
+            active = ballot64(mine);
+            const bool busy = se <= t && t < re, pend = t < se;            // receivers compute / will from se on
+            // A transfer begun now must not run into that computation.  The entry began before t: against a segment of
+            // its own size that settles it; against the other size the rounded sums are compared.
+            const uint64_t sb = ballot64(mine && se > t), rb = ballot64(mine && re > t);
+            const uint64_t cF = ballot64(mine && (busy || (pend && (!mineShort || t + c.c_full > se))));
+            const uint64_t cL = ballot64(mine && (busy || (pend && (mineShort || !ragged || t + c.c_last > se))));
+            // the combine of the smaller last segment, received now, would begin while this processor is still sending
+            const uint64_t lt = ballot64(mine && guardL && !mineShort && se > t + c.c_last);
+#pragma unroll
+            for (int k = 0; k < K; ++k) { sfree[k] = rfree[k] = valid[k]; compF[k] = compL[k] = lateL[k] = 0; }
+            sfree[0] &= ~root;                                             // the root never sends
+            uint64_t left = active;
+            while (left != 0) {                                            // four entries at a time: their loads are independent
+                int e[4];
+                uint64_t sm[4][K], rm[4][K];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    e[u] = left != 0 ? __builtin_ctzll(left) : e[u > 0 ? u - 1 : 0];
+                    left &= left - 1;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const size_t at = static_cast<size_t>(e[u]) * 2 * W + w0 + k;
+                        sm[u][k] = own[k] ? sets[at] : 0;
+                        rm[u][k] = own[k] ? sets[at + W] : 0;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint64_t ms = 0 - ((sb >> e[u]) & 1), mr = 0 - ((rb >> e[u]) & 1), mF = 0 - ((cF >> e[u]) & 1),
+                                   mL = 0 - ((cL >> e[u]) & 1), mt = 0 - ((lt >> e[u]) & 1);
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        sfree[k] &= ~(sm[u][k] & ms); rfree[k] &= ~(rm[u][k] & mr);
+                        compF[k] |= rm[u][k] & mF; compL[k] |= rm[u][k] & mL; lateL[k] |= sm[u][k] & mt;
+                    }
+                }
+            }
+        }
+        // ---------------------------------------------------------------- visits (t, j)
+        for (;;) {
+            const bool past = j >= q;
+            if (past && !guardL) break;                                    // only the late instants ask for free senders
+            const bool last = j >= q - 1;
+            if (preJ != j && !past) fetch(j);
+            uint64_t row[K], fr[K], so[K], ro[K];
+            int pf = 0, pm = 0, pso = 0, pro = 0, pu = 0;
+            bool as = false, ar = false, any = false, cand = false;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                row[k] = rowNext[k];
+                const uint64_t comp = last ? compL[k] : compF[k];
+                const uint64_t s = sfree[k] & ~comp, r = rfree[k] & ~comp & ~(last ? lateL[k] : UINT64_C(0));
+                const uint64_t memb = ~row[k] & valid[k];                  // still hold segment j (root: until done)
+                const uint64_t sOK = memb & s, rOK = memb & r;
+                fr[k] = sOK & rOK; so[k] = sOK ^ fr[k]; ro[k] = rOK ^ fr[k];
+                pf += __popcll(fr[k]); pm += __popcll(memb); pso += __popcll(so[k]); pro += __popcll(ro[k]);
+                pu += __popcll(s | r);
+                as = as | (s != 0); ar = ar | (r != 0); any = any | (sfree[k] != 0);
+                cand = cand | (((sfree[k] | rfree[k]) & ~comp & row[k]) != 0);
+            }
+            const int scanF = dpp_inclusive_scan(pf | (pm << 16)), sumO = dpp_inclusive_scan(pso | (pro << 16));
+            const uint64_t some = ballot64(pu != 0);
+            const int two = ballot64(pu > 1) != 0 ? 2 : (some == 0 ? 0 : ((some & (some - 1)) != 0 ? 2 : 1));
+            const int4 *const part = partial(scanF, sumO, (ballot64(as) != 0 ? 1 : 0) | (ballot64(ar) != 0 ? 2 : 0) |
+                                                              (ballot64(any) != 0 ? 4 : 0) | (ballot64(cand) != 0 ? 8 : 0) | (two << 8));
+            if (!past && j + 1 < q) fetch(j + 1);                          // on its way while this visit goes on
+            int nf_ = 0, remj = -1, ns_ = 0, nr_ = 0, either = 0, flags = 0, exF = (scanF & 0xFFFF) - pf;
+#pragma unroll
+            for (int w = 0; w < kBlockWaves; ++w) {
+                const int4 x = part[w];
+                if (w < wave) exF += x.x & 0xFFFF;
+                nf_ += x.x & 0xFFFF; remj += x.x >> 16; ns_ += x.y & 0xFFFF; nr_ += x.y >> 16;
+                flags |= x.w & 15; either += x.w >> 8;
+            }
+            flags = __builtin_amdgcn_readfirstlane(flags); either = __builtin_amdgcn_readfirstlane(either);
+            nf_ = __builtin_amdgcn_readfirstlane(nf_); remj = __builtin_amdgcn_readfirstlane(remj);
+            ns_ = __builtin_amdgcn_readfirstlane(ns_); nr_ = __builtin_amdgcn_readfirstlane(nr_);
+            anySender = (flags & 4) != 0;
+            if (past) break;
+            // a pair needs a free send port and a free receive port on two different processors: without them only the last
+            // segment, whose shorter transfer is kept out by fewer pending computations, is left to try
+            if ((flags & 3) != 3 || either < 2) {
+                if (last) break;
+                j = q - 1;
+                continue;
+            }
+            if (remj == 0) {                                               // everybody has sent segment j
+                if (j == segStart) ++segStart;
+                ++j;
+                continue;
+            }
+            int toSendLast, toRecvFirst;                                   // free processors go to the shorter list
+            if (ns_ == nr_) {
+                toSendLast = toRecvFirst = nf_ / 2;
+            } else if (ns_ < nr_) {
+                const int y = nr_ - ns_, mm = nf_ < y ? nf_ : y, xx = (nf_ - mm) / 2;
+                toSendLast = mm + xx; toRecvFirst = xx;
+            } else {
+                const int y = ns_ - nr_, mm = nf_ < y ? nf_ : y, xx = (nf_ - mm) / 2;
+                toRecvFirst = mm + xx; toSendLast = xx;
+            }
+            const int sN = ns_ + toSendLast, rN = nr_ + toRecvFirst;
+            const int l = sN < rN ? sN : rN;
+            const int at = j;
+            if (j > jhi) {
+                // a jump to the last segment can pass segments nobody has visited: their rows are empty
+                for (int jj = jhi + 1; jj <= j; ++jj)
+#pragma unroll
+                    for (int k = 0; k < K; ++k)
+                        if (own[k]) rows[static_cast<size_t>(jj) * W + w0 + k] = 0;
+                jhi = j;
+            }
+            ++j;
+            if (l == 0) {
+                // nobody paired although no candidate had already sent the segment: the candidates of later segments are a
+                // subset of these, so only the last one can still pair at this t
+                if ((flags & 8) == 0) {
+                    if (last) break;
+                    j = q - 1;
+                }
+                continue;
+            }
+            uint64_t sset[K], rset[K];
+            int ps = 0, pr = 0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int n = __popcll(fr[k]);
+                sset[k] = so[k] | highest_bits(fr[k], exF + n - (nf_ - toSendLast));
+                rset[k] = ro[k] | lowest_bits(fr[k], toRecvFirst - exF);
+                exF += n;
+                ps += __popcll(sset[k]); pr += __popcll(rset[k]);
+            }
+            int exS = 0, exR = 0;
+            if (kSched || sN != l || rN != l) {                            // first l entries of each list
+                const int scan = dpp_inclusive_scan(ps | (pr << 16));
+                const int4 *const cut = partial(scan, 0, 0);
+                exS = (scan & 0xFFFF) - ps; exR = (scan >> 16) - pr;
+#pragma unroll
+                for (int w = 0; w < kBlockWaves; ++w)
+                    if (w < wave) { const int x = cut[w].x; exS += x & 0xFFFF; exR += x >> 16; }
+                int es = exS, er = exR;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int ns1 = __popcll(sset[k]), nr1 = __popcll(rset[k]);
+                    sset[k] = lowest_bits(sset[k], l - es); rset[k] = lowest_bits(rset[k], l - er);
+                    es += ns1; er += nr1;
+                }
+            }
+            const T cj = last ? c.c_last : c.c_full, gj = last ? c.g_last : c.g_full;
+            const T tc = t + cj, tr = tc + gj;
+            if (!(tc > t)) { *status = PRS_CFG_STALLED; return true; }
+            if ((active & full) == full) return false;
+            if (kSched) {                                                  // e-th sender pairs with e-th receiver
+                const int64_t o = out_base + emitted;
+                for (int e = tid; e < l; e += kBlockThreads) {
+                    if (sched.seg) sched.seg[o + e] = at;
+                    if (sched.tstart) static_cast<T *>(sched.tstart)[o + e] = t;
+                }
+                int32_t *src = sched.src ? sched.src + (o + exS) : nullptr, *dst = sched.dst ? sched.dst + (o + exR) : nullptr;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int base = (w0 + k) * 64;
+                    if (src) {
+                        src += emit_set_bits(src, static_cast<uint32_t>(sset[k]), base);
+                        src += emit_set_bits(src, static_cast<uint32_t>(sset[k] >> 32), base + 32);
+                    }
+                    if (dst) {
+                        dst += emit_set_bits(dst, static_cast<uint32_t>(rset[k]), base);
+                        dst += emit_set_bits(dst, static_cast<uint32_t>(rset[k] >> 32), base + 32);
+                    }
+                }
+            }
+            emitted += l;
+            const int e = __builtin_ctzll(~active);
+            if (lane == e) { se = tc; re = tr; mine = true; mineShort = last && ragged; }
+            active |= UINT64_C(1) << e;
+            const bool late = guardL && !last && tc > t + c.c_last;         // these senders cannot take the last segment in yet
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                sfree[k] &= ~sset[k]; rfree[k] &= ~rset[k];
+                if (late) lateL[k] |= sset[k];
+                if (own[k]) {
+                    sets[static_cast<size_t>(e) * 2 * W + w0 + k] = sset[k];
+                    sets[static_cast<size_t>(e) * 2 * W + W + w0 + k] = rset[k];
+                    rows[static_cast<size_t>(at) * W + w0 + k] = row[k] | sset[k];
+                }
+            }
+            if (remj == l) {                                               // only the root is left: done after the last arrival
+                if (tr > Tmax) Tmax = tr;
+                if (++ndone == q) { *result = Tmax; return true; }
+            }
+        }
+    }
+}
+
 template <typename T, bool kSched>
 __global__ __launch_bounds__(kBlockThreads) void bi_block_kernel(ConfigArrays cfg, int32_t p_max, int32_t q_max, int model,
                                                                  TimesOut times, SchedOut sched, PlanHeader *plan,
-                                                                 const int32_t *order, int cls, int32_t state_p, int32_t state_q,
-                                                                 char *slots, size_t slot_bytes)
+                                                                 const int32_t *order, int cls, int entries, int32_t state_p,
+                                                                 int32_t state_q, char *slots, size_t slot_bytes)
 {
     PRS_DYNAMIC_LDS(lds_raw);
     __shared__ long long s_ticket;
@@ -350,6 +686,7 @@ __global__ __launch_bounds__(kBlockThreads) void bi_block_kernel(ConfigArrays cf
     char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
     const BlockSlot sl = bi_block_slot(state_p, state_q);
     const int Wc = (state_p + 63) >> 6;
+    int4 *red = reinterpret_cast<int4 *>(lds_raw + bb_align(static_cast<size_t>(Wc) * 8 * 7) + bb_align(static_cast<size_t>(Wc) * 2 * 2) + 512);
     const int32_t count = plan->class_count[cls], begin = plan->class_begin[cls];
     for (;;) {
         __syncthreads();
@@ -367,7 +704,16 @@ __global__ __launch_bounds__(kBlockThreads) void bi_block_kernel(ConfigArrays cf
             if (base < 0 || base + cnt > sched.pair_capacity) status = PRS_CFG_TOO_LARGE;
         }
         T result = CostTraits<T>::bad();
-        if (status == PRS_CFG_OK) result = run_bi_block<T, kSched>(c, lds_raw, slot, sl, Wc, sched, base, &status);
+        if (status == PRS_CFG_OK) {
+            bool done = false;
+            if (c.p <= kWideProcs)
+                done = run_bi_wide<T, kSched>(c, red, reinterpret_cast<uint64_t *>(slot + sl.sent), reinterpret_cast<uint64_t *>(slot + sl.sets),
+                                              entries, sched, base, &result, &status);
+            if (!done) {
+                __syncthreads();
+                result = run_bi_block<T, kSched>(c, lds_raw, slot, sl, Wc, sched, base, &status);
+            }
+        }
         __syncthreads();
         if (tid == 0) {
             if (!kSched) write_closed_forms<T>(times, i, c, model);
@@ -383,7 +729,7 @@ template <typename T, bool kSched>
 static hipError_t launch_bi_block_t(const BiLaunch &L)
 {
     hipLaunchKernelGGL((bi_block_kernel<T, kSched>), dim3(L.grid), dim3(kBlockThreads), L.lds_bytes, L.stream, L.cfg, L.p_max,
-                       L.q_max, L.model, L.times, L.sched, L.plan, L.order, L.cls, L.slot_p, L.slot_q, L.slots, L.slot_bytes);
+                       L.q_max, L.model, L.times, L.sched, L.plan, L.order, L.cls, L.list_entries, L.slot_p, L.slot_q, L.slots, L.slot_bytes);
     return hipGetLastError();
 }
 

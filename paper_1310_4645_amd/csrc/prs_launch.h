@@ -37,6 +37,7 @@ struct UniLaunch {
     PlanHeader *plan;
     const int32_t *order;
     int cls;
+    int list_entries;             // block kernel of bi-greedy: most running transfers it may list (1 .. 64)
     int32_t lds_p;
     int32_t lds_bitmap_bytes;
     size_t lds_bytes;
@@ -94,7 +95,7 @@ size_t uni_wide_slot_bytes(int32_t p_cap);
 size_t uni_wide_lds_bytes();
 hipError_t launch_uni_wide(const UniLaunch &L);
 hipError_t launch_bi(const BiLaunch &L);
-// one block of 16 wavefronts per configuration: thousands of processors
+// one block of 8 wavefronts per configuration: thousands of processors
 size_t bi_block_slot_bytes(int32_t p_cap, int32_t q_cap);
 size_t bi_block_lds_bytes(int32_t p_cap);
 hipError_t launch_bi_block(const BiLaunch &L);

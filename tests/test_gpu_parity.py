@@ -521,6 +521,30 @@ def test_schedules_beyond_1024_processors(prs, model):
     _check_schedules(prs, hostf, model, 4096, 8)
 
 
+@pytest.mark.parametrize("entries", [0, 2])
+@pytest.mark.parametrize("cost", ["i64", "f64"])
+def test_bi_schedules_around_the_words_per_thread(prs, cost, entries):
+    """Bi-greedy on a block of 512 threads: first and last machine with one and with two words per thread, the first one
+    beyond two, equal and smaller last segments, more segments than are in flight; with the list of running
+    transfers cut to two entries every configuration starts again on the path that keeps times per processor."""
+    p = np.array([1025, 1088, 4097, 32767, 32768, 32769, 65536, 65537, 1500, 2047], np.int32)
+    q = np.array([40, 7, 9, 3, 4, 2, 3, 2, 33, 64], np.int32)
+    per = np.array([5, 3, 8, 6, 1, 9, 7, 4, 2, 11], np.int64)
+    m = q * per - np.array([0, 1, 7, 0, 0, 4, 2, 1, 1, 10])
+    if cost == "i64":
+        al, be, ga = np.array([3, 0, 7, 2, 1, 0, 5, 1, 2, 4]), np.full(10, 2), np.array([1, 3, 0, 2, 1, 4, 1, 2, 1, 3])
+        al, be, ga = al.astype(np.int64), be.astype(np.int64), ga.astype(np.int64)
+    else:
+        rng = np.random.default_rng(77)
+        al, be, ga = 10.0 ** rng.uniform(-6, -4, 10), 10.0 ** rng.uniform(-7, -5, 10), 10.0 ** rng.uniform(-7, -5, 10)
+    host = prs_inputs.SweepConfigs(p, q, m, al, be, ga, cost)
+    tuning = {"bi_list_entries": entries} if entries else None
+    got = prs.simulate_completion_batch(prs.DeviceConfigs.from_host(host), 1, 65537, 64, tuning=tuning)
+    _sync()
+    _check_times(got, O.simulate_batch(host, 1), exact=cost == "i64")
+    _check_schedules(prs, host, 1, 65537, 64, tuning=tuning)
+
+
 # --------------------------------------------------------------------------- best segmentation per algorithm
 @pytest.mark.parametrize("model", [0, 1])
 @pytest.mark.parametrize("cost", ["i64", "f64"])
