@@ -268,6 +268,17 @@ def test_uni_schedules_with_long_runs_of_equal_values(prs):
     _check_schedules(prs, full.take(idx), 0, 1024, 512)
 
 
+@pytest.mark.parametrize("n", [1, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193])
+def test_uni_schedules_of_small_batches(prs, n):
+    """Schedules pair for pair at the batch sizes where a configuration gets 64, 32, 16 or 8 lanes or as many as its pairs ask for."""
+    rng = np.random.default_rng(n)
+    p, q = rng.integers(2, 14, n).astype(np.int32), rng.integers(1, 7, n).astype(np.int32)
+    m = (q * rng.integers(1, 5, n) - rng.integers(0, 2, n)).clip(1).astype(np.int64)
+    p[0], q[0], m[0] = 300, 70, 70 * 9 - 4
+    host = prs_inputs.SweepConfigs(p, q, m, rng.integers(0, 9, n).astype(np.int64), np.ones(n, np.int64), rng.integers(0, 3, n).astype(np.int64), "i64")
+    _check_schedules(prs, host, 0, 300, 70)
+
+
 @pytest.mark.parametrize("model", [0, 1])
 def test_fp64_rounding_ties(prs, model):
     # costs chosen so that sums produced at different times round to the same double
