@@ -276,6 +276,49 @@ __device__ __forceinline__ uint64_t highest_bits(uint64_t mask, int k)
     return mask & ~lowest_bits(mask, pc - k);
 }
 
+// Value of the lane before this one in its group of G (the last lane's for the first), and of the lane after it: moves
+// inside the vector unit (quad_perm, rotations of a row of 16 or of the wavefront by one lane), no LDS access.
+template <int CTRL> __device__ __forceinline__ int dpp_from(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
+constexpr int kDppRowRor = 0x120, kDppWaveRol1 = 0x134, kDppWaveRor1 = 0x13C;
+
+template <int G> __device__ __forceinline__ int from_previous(int v, int gl)
+{
+    if (G == 2) return dpp_from<0xB1>(v);                            // quad_perm [1,0,3,2]
+    if (G == 4) return dpp_from<0x93>(v);                            // quad_perm [3,0,1,2]
+    if (G == 8) { const int a = dpp_from<kDppRowRor + 1>(v), b = dpp_from<kDppRowRor + 9>(v); return gl == 0 ? b : a; }
+    if (G == 16) return dpp_from<kDppRowRor + 1>(v);
+    if (G == 32) {
+        const int a = dpp_from<kDppWaveRor1>(v);                     // right except for lanes 0 and 32
+        const int lo = __builtin_amdgcn_readlane(v, 31), hi = __builtin_amdgcn_readlane(v, 63);
+        return gl == 0 ? (lane_id() == 0 ? lo : hi) : a;
+    }
+    if (G == 64) return dpp_from<kDppWaveRor1>(v);
+    return v;
+}
+template <int G> __device__ __forceinline__ int from_next(int v, int gl)
+{
+    if (G == 2) return dpp_from<0xB1>(v);
+    if (G == 4) return dpp_from<0x39>(v);                            // quad_perm [1,2,3,0]
+    if (G == 8) { const int a = dpp_from<kDppRowRor + 15>(v), b = dpp_from<kDppRowRor + 7>(v); return gl == 7 ? b : a; }
+    if (G == 16) return dpp_from<kDppRowRor + 15>(v);
+    if (G == 32) {
+        const int a = dpp_from<kDppWaveRol1>(v);
+        const int lo = __builtin_amdgcn_readlane(v, 0), hi = __builtin_amdgcn_readlane(v, 32);
+        return gl == 31 ? (lane_id() == 31 ? lo : hi) : a;
+    }
+    if (G == 64) return dpp_from<kDppWaveRol1>(v);
+    return v;
+}
+
+template <int G, typename T> __device__ __forceinline__ T from_previous_value(T v, int gl)
+{
+    int32_t w[2];
+    __builtin_memcpy(w, &v, 8);
+    w[0] = from_previous<G>(w[0], gl); w[1] = from_previous<G>(w[1], gl);
+    __builtin_memcpy(&v, w, 8);
+    return v;
+}
+
 // ---------------------------------------------------------------- closed forms
 // Tables I and III (standard algorithms), Table II / Figure 6 (bounds).
 struct TimesOut {

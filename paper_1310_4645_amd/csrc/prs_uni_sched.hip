@@ -14,6 +14,14 @@
 //    so it goes through the same insertion.
 //  - B needs the receiver's index per pair, kept in a per-lane array; its values are still S + tcomp.
 //    Equal B values are kept in index order by the same insertion.
+//
+// What bounds it: 25.7 million wavefront iterations on the 100,000-configuration sweep (60 % of their lanes form a pair), each
+// about 300 vector and 150 scalar instructions and 2 us, half of it waiting, above all for the entries that the first lane of
+// a group reads from the workspace.  Rows that have been read by the time they would leave LDS stay out of the workspace,
+// and what is left at the end of a segment leaves with the rows of the next one instead of entry by entry (those loops
+// ran in every fifth iteration, in all of them on small machines): 279 -> 155 million store instructions with the first
+// and the second half of the change, 54.1 -> 51.7 ms; one machine of 256 processors and 64 segments 2.61 -> 2.35 ms.
+// Measured and not taken: 16-bit indices with a ring of 16 and eight wavefronts per CU, 110 ms.
 #include "prs_device.h"
 #include "prs_launch.h"
 
@@ -21,6 +29,11 @@ namespace prs {
 
 constexpr int kRingS = 32;           // stream entries per lane kept in LDS
 constexpr int kNearS = kRingS - 5;   // entries this close behind the writer are read from LDS in the next iteration
+// Rows of eight leave LDS when this many entries wait, one row every four iterations.  Six more entries can come before (four
+// pairs, the held entry and the root's), four more while the last, shorter row of a segment leaves.
+constexpr int kKeepS = 16;
+constexpr int kTailP = 32;           // with fewer processors the rest of a segment leaves at its end
+static_assert(kKeepS + 10 <= kNearS && kKeepS >= 8, "entries that are read from the workspace have to be there");
 
 constexpr int kStage = 8;            // pairs per lane waiting in LDS for their 16-byte stores
 
@@ -124,6 +137,7 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
     unsigned long long *tickets = &plan->ticket[cls];
     if (part == kGiantPart) { count = plan->giant_count; tickets = &plan->ticket_giant; }
     else if (part == kRestPart) { begin += plan->giant_count; count -= plan->giant_count; }
+    if (count == 0) return;
     const T kInf = CostTraits<T>::inf();
 
     // ---- per-group state (the same in all lanes of a group)
@@ -148,11 +162,24 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
     // every fourth iteration of the wavefront, by all lanes at once: done per lane whenever its row fills, the
     // row code would run in almost every iteration for a few lanes each.
     int fW = 0, fB = 0, fO = 0;     // entries / receivers / pairs of my segment that have reached the workspace (multiples of 8, 8 and 4)
+    int tailFrom = 0, tailTo = 0;   // entries of the segment before that still wait in LDS
     int iter = 0;
     T cc = 0, gg = 0;
     bool farA = false, farB = false, anyFar = false;
     T la0 = 0, la1 = 0, lb0 = 0, lb1 = 0;
     int32_t lai0 = 0, lai1 = 0, lbi0 = 0, lbi1 = 0;
+
+    // entries j .. j + 7 of the segment that begins at position `base`; the last row of a segment may reach past its entries
+    auto store_row = [&](T *toX, int32_t *toI, int base, int j) {
+        T rx8[8]; int32_t ri8[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int rr = ((base + j + i) & M) * kWave + lane;
+            rx8[i] = ringX[rr]; ri8[i] = ringI[rr];
+        }
+        __builtin_memcpy(toX + j, rx8, 64);
+        __builtin_memcpy(toI + j, ri8, 32);
+    };
 
     for (;;) {
         // ---------------------------------------------------------------- fetch a configuration
@@ -185,7 +212,7 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
                     c_full = c.c_full; g_full = c.g_full; c_last = c.c_last; g_last = c.g_last;
                     k = gl; par = 0; apar = gl == 0 ? 1 : 0;
                     wtot = segBase = ns = runStart = apos = astart = bpos = brun = 0;
-                    fW = fB = fO = 0;
+                    fW = fB = fO = tailFrom = tailTo = 0;
                     hold = false; lastS = 0;
                     farA = farB = false;
                     cc = k == q - 1 ? c_last : c_full; gg = k == q - 1 ? g_last : g_full;
@@ -198,13 +225,10 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
         const int n1 = p - 1;                                               // entries (pairs) per segment
 
         // ---------------------------------------------------------------- what my producer has done so far
-        int pw = wtot, pfinal = segBase + runStart;
-        T plast = lastS;
-        if (G > 1) {
-            pw = __shfl(wtot, prod, kWave);
-            pfinal = __shfl(segBase + runStart, prod, kWave);
-            plast = __shfl(lastS, prod, kWave);
-        }
+        const int pw = from_previous<G>(wtot, gl), pfinal = from_previous<G>(segBase + runStart, gl);
+        const T plast = from_previous_value<G, T>(lastS, gl);
+        // how far the reader of my stream has come (the stream of the last segment has none)
+        const int reader = from_next<G>(k == 0 ? INT32_MIN : apos, gl), readTo = k == q - 1 ? INT32_MAX : reader;
         const bool first = k == 0;
         const int aend = astart + p;
         const int availEnd = first ? aend : (pfinal < aend ? pfinal : aend);   // entries below the producer's running value are final
@@ -305,19 +329,40 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
                 // the root's final state: the largest value, in front of entries of the same value
                 if (!(tr == lastS)) runStart = w;
                 put(tr, 0, runStart);
-                // everything of the segment that still waits in LDS
-                for (int j = fW; j < w; ++j) {
-                    const int rr = ((segBase + j) & M) * kWave + lane;
-                    myX[j] = ringX[rr]; myI[j] = ringI[rr];
+                // Entries that still wait in LDS leave with the rows of the next segment, if nobody has read them by then;
+                // nobody reads the last segment.
+                if (p < kTailP) {
+                    for (int j = fW; j < w; j += 8)
+                        if (readTo < segBase + j + 8) store_row(myX, myI, segBase, j);
+                } else if (k < q - 1) {
+                    tailFrom = segBase + fW; tailTo = wtot;
                 }
-                for (int j = fB; j < n1; ++j) bufB[j] = ringB[((segBase + j) & M) * kWave + lane];
-                for (int j = fO; j < n1; ++j) {
-                    const int slot = lane * kStage + (j & (kStage - 1));
-                    const int64_t oj = out_base + static_cast<int64_t>(k) * n1 + j;
-                    if (sched.src) sched.src[oj] = stS[slot];
-                    if (sched.dst) sched.dst[oj] = stD[slot];
-                    if (sched.seg) sched.seg[oj] = k;
-                    if (sched.tstart) static_cast<T *>(sched.tstart)[oj] = stT[slot];
+                // the last pairs: rows of four, the last one reaching back if need be
+                while (fO < n1) {
+                    const int j0 = n1 < 4 ? fO : (fO < n1 - 4 ? fO : n1 - 4);
+                    const int64_t o4 = out_base + static_cast<int64_t>(k) * n1 + j0;
+                    if (n1 < 4) {
+                        const int slot = lane * kStage + (j0 & (kStage - 1));
+                        if (sched.src) sched.src[o4] = stS[slot];
+                        if (sched.dst) sched.dst[o4] = stD[slot];
+                        if (sched.seg) sched.seg[o4] = k;
+                        if (sched.tstart) static_cast<T *>(sched.tstart)[o4] = stT[slot];
+                        ++fO;
+                    } else {
+                        int32_t s4[4], d4[4];
+                        T t4[4];
+                        const int32_t k4[4] = {k, k, k, k};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int slot = lane * kStage + ((j0 + i) & (kStage - 1));
+                            s4[i] = stS[slot]; d4[i] = stD[slot]; t4[i] = stT[slot];
+                        }
+                        if (sched.src) __builtin_memcpy(sched.src + o4, s4, 16);
+                        if (sched.dst) __builtin_memcpy(sched.dst + o4, d4, 16);
+                        if (sched.seg) __builtin_memcpy(sched.seg + o4, k4, 16);
+                        if (sched.tstart) __builtin_memcpy(static_cast<T *>(sched.tstart) + o4, t4, 32);
+                        fO += 4;
+                    }
                 }
                 fW = fB = fO = 0;
                 if (k == q - 1 && sched.T_greedy) static_cast<T *>(sched.T_greedy)[ci] = tr;
@@ -332,29 +377,23 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
         }
         // ---------------------------------------------------------------- full rows leave LDS (every fourth iteration)
         if ((++iter & 3) == 0) {
-            T *const myX = bufX(lane, par);
-            int32_t *const myI = bufI(lane, par);
-            const int w = wtot - segBase;
             // stream entries and receivers in rows of eight (64 bytes of values: whole sectors of a cache line, which
-            // the L2 can no longer merge once millions of half-written lines are open)
-            if (have && k < q && fW + 8 <= w) {
-                T rx8[8]; int32_t ri8[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int rr = ((segBase + fW + j) & M) * kWave + lane;
-                    rx8[j] = ringX[rr]; ri8[j] = ringI[rr];
-                }
-                __builtin_memcpy(myX + fW, rx8, 64);
-                __builtin_memcpy(myI + fW, ri8, 32);
-                fW += 8;
-            }
-            if (have && k < q && fB + 8 <= ns) {
+            // the L2 can no longer merge once millions of half-written lines are open).  Rows that the reader of the stream
+            // and the lane's own B are past stay out of the workspace.
+            const bool tail = tailFrom < tailTo;
+            const int rowAt = tail ? tailFrom : segBase + fW, rowBase = tail ? segBase - p : segBase;
+            const bool rowS = have && (tail || k < q) && wtot - rowAt >= kKeepS, rowB = have && k < q && fB + kKeepS <= ns;
+            if (rowS && ((tail ? reader : readTo) < rowAt + 8 || (!tail && bpos < rowAt + 8)))
+                store_row(bufX(lane, tail ? par ^ 1 : par), bufI(lane, tail ? par ^ 1 : par), rowBase, rowAt - rowBase);
+            tailFrom += rowS && tail ? 8 : 0;
+            fW += rowS && !tail ? 8 : 0;
+            if (rowB && bpos < segBase + fB + 8) {
                 int32_t rb8[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) rb8[j] = ringB[((segBase + fB + j) & M) * kWave + lane];
                 __builtin_memcpy(bufB + fB, rb8, 32);
-                fB += 8;
             }
+            fB += rowB ? 8 : 0;
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
                 if (have && k < q && fO + 4 <= ns) {
