@@ -125,7 +125,7 @@ __device__ __forceinline__ void sliced_increment(uint64_t (&plane)[kPlanes], uin
 template <typename T, bool kSched, int LPC>
 __device__ __forceinline__ void bi_group_body(char *lds_raw, int block, const ConfigArrays &cfg, int32_t p_max, int32_t q_max,
                                               int model, const TimesOut &times, const SchedOut &sched, PlanHeader *plan,
-                                              const int32_t *order, int cls, int32_t *retry, uint64_t *rows,
+                                              const int32_t *order, int cls, int32_t *retry, uint64_t *rows, int per_wave,
                                               size_t rows_per_group, int list_entries)
 {
     constexpr int kCap = bi_group_capacity(LPC);
@@ -150,7 +150,7 @@ __device__ __forceinline__ void bi_group_body(char *lds_raw, int block, const Co
 
     // ---- per-group state (identical in all lanes of a group unless noted)
     bool have = false;          // a configuration is loaded
-    bool exhausted = false;     // no more tickets
+    bool exhausted = gw >= per_wave;   // no (more) tickets
     int64_t ci = 0;             // configuration index
     Config<T> c;
     int W = 0;
@@ -465,23 +465,23 @@ __global__ __launch_bounds__(kWave) void bi_group_kernel(ConfigArrays cfg, int32
         if (!parts.on[cls]) continue;
         switch (cls) {
         case 4:
-            bi_group_body<T, kSched, 16>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 4, retry, rows,
+            bi_group_body<T, kSched, 16>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 4, retry, rows, parts.per_wave,
                                          parts.rows_per_group[4], parts.list_entries[4]);
             break;
         case 3:
-            bi_group_body<T, kSched, 8>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 3, retry, rows,
+            bi_group_body<T, kSched, 8>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 3, retry, rows, parts.per_wave,
                                         parts.rows_per_group[3], parts.list_entries[3]);
             break;
         case 2:
-            bi_group_body<T, kSched, 4>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 2, retry, rows,
+            bi_group_body<T, kSched, 4>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 2, retry, rows, parts.per_wave,
                                         parts.rows_per_group[2], parts.list_entries[2]);
             break;
         case 1:
-            bi_group_body<T, kSched, 2>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 1, retry, rows,
+            bi_group_body<T, kSched, 2>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 1, retry, rows, parts.per_wave,
                                         parts.rows_per_group[1], parts.list_entries[1]);
             break;
         default:
-            bi_group_body<T, kSched, 1>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 0, retry, rows,
+            bi_group_body<T, kSched, 1>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 0, retry, rows, parts.per_wave,
                                         parts.rows_per_group[0], parts.list_entries[0]);
             break;
         }

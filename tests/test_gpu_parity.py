@@ -353,6 +353,27 @@ def test_bi_configurations_handed_over_to_the_general_kernel(prs, entries):
     _check_schedules(prs, hostf, 1, 1024, 64, tuning=tuning)
 
 
+@pytest.mark.parametrize("entries", [0, 2])
+@pytest.mark.parametrize("copies", [1, 15, 40, 700])
+def test_bi_configurations_side_by_side_in_a_wavefront(prs, copies, entries):
+    """The number of configurations that share a wavefront follows the size of the batch: 1, 2, 4 and all its lanes.  Copies of
+    100 machines of every group size, each copy the oracle's times; with the list cut to two entries most are rerun."""
+    rng = np.random.default_rng(5)
+    p = np.concatenate([rng.integers(2, 65, 50), rng.integers(65, 129, 15), rng.integers(129, 257, 15), rng.integers(257, 513, 10),
+                        rng.integers(513, 701, 10)]).astype(np.int32)
+    q = rng.integers(1, 12, 100).astype(np.int32)
+    m = (q.astype(np.int64) * rng.integers(1, 5, 100) - rng.integers(0, 2, 100)).clip(1)
+    host = prs_inputs.SweepConfigs(p, q, m, rng.integers(0, 12, 100).astype(np.int64), rng.integers(1, 4, 100).astype(np.int64),
+                                   rng.integers(0, 4, 100).astype(np.int64), "i64")
+    ref = O.simulate_batch(host, 1)
+    many = host.take(np.tile(np.arange(100), copies))
+    got = prs.simulate_completion_batch(prs.DeviceConfigs.from_host(many), 1, 700, 12,
+                                        tuning={"bi_list_entries": entries} if entries else None)
+    _sync()
+    assert np.array_equal(_np(got["greedy"]).reshape(copies, 100), np.broadcast_to(ref.T_greedy, (copies, 100)))
+    assert np.all(_np(got["cfg_status"]) == 0)
+
+
 def test_costs_too_large_for_the_cost_type_are_refused(prs):
     """A configuration whose schedule would pass the range of the cost type (Table I's pipeline time, which
     bounds every greedy time) is reported as a bad parameter instead of being run: with doubles the sums would
