@@ -197,8 +197,8 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             ClassSpec &c = L.cls[k];
             c.q_cap = q_max;
             c.kind = sched ? kUniSched : kUniTimes; c.lpc = 0; c.rows_per_group = 0; c.lds = true; c.lds_bitmap_bytes = 0;
-            // schedules: keeps every per-lane array 64-byte aligned; times: a ring of p + 4 runs per lane
-            c.p_cap = sched ? (p_max + 15) / 16 * 16 : (p_max + 4 + 15) / 16 * 16;
+            // schedules: keeps every per-lane array 64-byte aligned; times: a ring per lane
+            c.p_cap = sched ? (p_max + 15) / 16 * 16 : (uni_times_slot_runs(p_max) + 15) / 16 * 16;
             c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes(p_max, compositions);
             c.slot_bytes = k != 0 ? 0 : (sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap));
             int64_t g = static_cast<int64_t>(kLdsPerCU / c.lds_bytes) * kCUs;

@@ -29,9 +29,11 @@
 // the scattered 8-byte stores, about 9 cycles of a CU's store path each.)  The rings of a group can all be
 // full at once only through the last lane, whose reader, the first lane, is a whole round behind: its ring
 // is the deep one.  If it does fill up -- or B outgrows a ring -- no lane of the group moves any more; the
-// configuration then starts again with its rings in the wavefront's workspace slot, p + 4 runs each, which
-// always suffices: a segment cannot have sent more processors than the lane that reads its stream has
-// taken from the stream before it, so at most p are waiting to be read.
+// configuration then starts again with its rings in the wavefront's workspace slot, p + 7 runs each, in which a
+// lane never waits: of its stream at most p runs are unread -- a segment cannot have sent more processors than
+// the lane that reads its stream has taken from the stream before it, and all p of them with one lane, which
+// reads its own stream, at the end of a segment without equal ready times -- and a lane goes on as long as 7 places
+// are left, for the runs of a chunk of steps, the root's and the open one.  (p + 4 places were too few for one lane.)
 //
 // Measured (pair by pair with streams in global memory -> runs in LDS rings -> 27 KB of rings, six wavefronts per CU instead
 // of four, and tickets drawn several at a time): the 100,000-configuration sweep 11.9 -> 4.1 -> 3.55 ms, 64 machines of
@@ -43,6 +45,7 @@
 
 namespace prs {
 
+constexpr int kMaxChunk = 4;                     // steps between two looks for room in a ring, at most
 constexpr int kSpan = 64;                        // steps between two looks for groups that do not move
 constexpr int kRunBytes = 12;                    // a run in a ring: value and count
 constexpr int32_t kRetired = 1 << 30;            // read place of a lane without a segment: its producer need not wait for it
@@ -65,6 +68,8 @@ size_t uni_times_lds_bytes(int32_t p_max, bool compositions)
     if (p_max <= kUniSmallProcs) return static_cast<size_t>(compositions ? SmallRings<true>::kRuns : SmallRings<false>::kRuns) * 10;
     return static_cast<size_t>(large_rings(p_max).runs) * kRunBytes;
 }
+// runs of a ring in the workspace
+int32_t uni_times_slot_runs(int32_t p_max) { return p_max + 3 + kMaxChunk; }
 size_t uni_times_slot_bytes(int32_t p_cap) { return static_cast<size_t>(kWave) * static_cast<size_t>(p_cap) * kRunBytes; }
 
 // v, or a value above every time of a schedule (those stay below 4e18 and 1e300: schedule_fits) if v is not there.  Only
@@ -140,7 +145,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
     // a new configuration is fetched (a path every lane waits for) when this many groups have nothing to do
     constexpr int kFetchGroups = kGroups >= 8 ? kGroups / 8 : 1;
     // steps between two looks for room in the ring and for the end of a segment (small groups have short segments)
-    constexpr int kChunk = G >= 8 ? 4 : 2;
+    constexpr int kChunk = G >= 8 ? kMaxChunk : 2;
     const int lane = lane_id(), gl = lane & (G - 1), gbase = lane & ~(G - 1);
     const int prod = gbase | ((gl + G - 1) & (G - 1));
     const uint64_t gmask = (G == 64 ? ~UINT64_C(0) : ((UINT64_C(1) << G) - 1)) << gbase;

@@ -193,6 +193,27 @@ def test_uni_times_rings_of_runs(prs, p_max):
         assert np.array_equal(_np(got["greedy"]), ref[every]) and np.all(_np(got["cfg_status"]) == 0)
 
 
+@pytest.mark.parametrize("p", [44, 59, 60, 76])
+def test_uni_times_one_lane_with_as_many_runs_as_processors(prs, p):
+    """One lane per configuration reads the stream it writes, and at the end of a segment all of that stream can be waiting: as
+    many runs as the machine has processors where no two ready times are equal.  Machines as large as the bound on
+    them, on both sides of the sizes at which the rings in the workspace are rounded up: times and the best of all
+    segmentations, bit for bit."""
+    rng = np.random.default_rng(p)
+    n = 12
+    host = prs_inputs.SweepConfigs(np.full(n, p, np.int32), rng.integers(80, 101, n).astype(np.int32), rng.integers(1 << 20, 1 << 24, n),
+                                   10.0 ** rng.uniform(-6, -4, n), 10.0 ** rng.uniform(-10, -8, n), 10.0 ** rng.uniform(-11, -9, n), "f64")
+    dev = prs.DeviceConfigs.from_host(host)
+    tuning = _GROUPINGS["1 lane"]
+    got = prs.simulate_completion_batch(dev, 0, p, 100, tuning=tuning)
+    best = prs.optimal_segmentation_batch(dev, 0, p, 128, tuning=tuning)
+    _sync()
+    assert np.all(_np(got["cfg_status"]) == 0)
+    assert np.array_equal(_np(got["greedy"]), O.simulate_batch(host, 0).T_greedy)
+    ref = O.optimal_segmentation(host, 0, 128)
+    assert np.array_equal(_np(best["T_greedy"]), ref["T_greedy"]) and np.array_equal(_np(best["q_greedy"]), ref["q_greedy"])
+
+
 def test_uni_times_a_block_per_configuration(prs):
     """The kernel that gives a machine of thousands of processors a block of its own and forms many pairs of a
     segment at once, here fed with machines of every size (the limit lowered to two processors): completion
