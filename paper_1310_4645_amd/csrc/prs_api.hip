@@ -73,6 +73,12 @@ hipError_t launch_offsets(const OffsetsLaunch &L)
 enum ClassKind { kUniTimes, kUniSched, kBiGroup, kBiGeneral, kBiBlock, kUniWide };
 constexpr size_t kLdsPerCU = 160 * 1024, kLdsPerBlockMax = 64 * 1024, kBitmapLdsMax = 24 * 1024;
 constexpr int kCUs = 256, kMaxBlocksPerCU = 24, kGlobalClassGrid = 1024;
+// LDS is given out in units of 1280 bytes: six one-wavefront blocks of 26,880 bytes run on a CU side by side, five of 27,300.
+constexpr size_t kLdsUnit = 1280;
+static int64_t blocks_per_cu(size_t lds_bytes)
+{
+    return static_cast<int64_t>(kLdsPerCU / ((lds_bytes + kLdsUnit - 1) / kLdsUnit * kLdsUnit));
+}
 constexpr int32_t kGroupQMax = 1023;   // the several-per-wavefront bi-greedy kernel counts sent segments in 10 bit planes
 constexpr int kUniGroupSizes = 3;        // group sizes below the largest; the classes between them and the last stay empty
 // completion times: a configuration gets 1, 2, 4, 8 or 16 lanes with at most so many pairs and processors, more get 32, and 64
@@ -162,7 +168,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
         if (!sched) {
             L.limits.giant_log2 = kUniTimesGiantLog2;
             // A batch that leaves lanes without a configuration gives each of its configurations more of them.
-            const int64_t lanes = static_cast<int64_t>(kLdsPerCU / uni_times_lds_bytes(p_max, compositions)) * kCUs * kWave;
+            const int64_t lanes = blocks_per_cu(uni_times_lds_bytes(p_max, compositions)) * kCUs * kWave;
             for (int k = 0; k < kClasses - 1; ++k)
                 if (n << (k + 1) <= lanes) L.limits.work[k] = 0;
             if (n << 6 <= lanes) L.limits.giant_log2 = 0;
@@ -170,7 +176,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
         } else {
             // The same for schedules: 64, 32, 16 or 8 lanes where the batch leaves that many idle (one machine of 256
             // processors and 64 segments 3.2 -> 2.6 ms, a few hundred machines 3.3 -> 2.1 ms).
-            const int64_t lanes = static_cast<int64_t>(kLdsPerCU / uni_sched_lds_bytes()) * kCUs * kWave;
+            const int64_t lanes = blocks_per_cu(uni_sched_lds_bytes()) * kCUs * kWave;
             static const int more[kUniGroupSizes] = {3, 4, 5};            // the next group size: 8, 16, 32 lanes
             for (int k = 0; k < kClasses - 1; ++k)
                 if (n << more[k < kUniGroupSizes ? k : kUniGroupSizes - 1] <= lanes) L.limits.work[k] = 0;
@@ -201,7 +207,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             c.p_cap = sched ? (p_max + 15) / 16 * 16 : (uni_times_slot_runs(p_max) + 15) / 16 * 16;
             c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes(p_max, compositions);
             c.slot_bytes = k != 0 ? 0 : (sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap));
-            int64_t g = static_cast<int64_t>(kLdsPerCU / c.lds_bytes) * kCUs;
+            int64_t g = blocks_per_cu(c.lds_bytes) * kCUs;
             while (g > 1 && static_cast<size_t>(g) * c.slot_bytes > kMaxWorkspace) g /= 2;
             c.grid = k == 0 ? static_cast<int>(g) : 0;
             c.slot_offset = off;

@@ -35,7 +35,7 @@
 // reads its own stream, at the end of a segment without equal ready times -- and a lane goes on as long as 7 places
 // are left, for the runs of a chunk of steps, the root's and the open one.  (p + 4 places were too few for one lane.)
 //
-// Measured (pair by pair with streams in global memory -> runs in LDS rings -> 27 KB of rings, six wavefronts per CU instead
+// Measured (pair by pair with streams in global memory -> runs in LDS rings -> 27 KB of rings, five wavefronts per CU instead
 // of four, and tickets drawn several at a time): the 100,000-configuration sweep 11.9 -> 4.1 -> 3.55 ms, 64 machines of
 // 1024 to 65536 processors 587 -> 7.4 -> 7.0 ms, 986 x 512 segmentations of a short message 10.4 -> 1.94 -> 1.43 ms.  A step is
 // about 65 instructions, a chain of an LDS read, two compares and two additions, and takes 240 ns on a SIMD of its own:
@@ -52,8 +52,8 @@ constexpr int32_t kRetired = 1 << 30;            // read place of a lane without
 
 template <typename T> struct __attribute__((packed, aligned(4))) Run { T v; int32_t n; };
 
-// Machines of up to 1024 processors: counts fit 16 bits, and a wavefront keeps its runs in 27 KB, values first: six
-// wavefronts per CU.  B has at most 23 runs on all but a dozen of the 100,000-configuration sweep, and 30 - 3 - 4 of a ring of
+// Machines of up to 1024 processors: counts fit 16 bits, and a wavefront keeps its runs in 27 KB, values first: five
+// wavefronts per CU (LDS is given out in units of 1280 bytes).  B has at most 23 runs on all but a dozen of the 100,000-configuration sweep, and 30 - 3 - 4 of a ring of
 // 30 can wait (the root's run, the open place, the runs of four steps).  Compositions, whose segments differ in size,
 // keep more runs waiting: 40 KB, four wavefronts per CU.
 template <bool kComp> struct SmallRings;
