@@ -65,9 +65,10 @@ hipError_t launch_offsets(const OffsetsLaunch &L)
 
 // ---- size classes and workspace layout (shared by prs_workspace_bytes and the launches) --------------
 //
-// A batch is split into four classes, each run by the kernel and the LDS allocation that fit it:
-//   uni-greedy (times and schedules): by number of pairs; 1, 4 (schedules: 8), 16 or 32 lanes per configuration, all four
-//                                     classes in one launch;
+// A batch is split into classes, each run by the kernel and the LDS allocation that fit it:
+//   uni-greedy times:                 by number of pairs; 1, 2, 4, 8, 16, 32 or 64 lanes per configuration in one launch, machines
+//                                     of more than kUniSmallProcs processors in another;
+//   uni-greedy schedules:             by number of pairs; 1, 8, 16, 32 or 64 lanes per configuration, all in one launch;
 //   bi-greedy:                        1, 2, 4, 8 or 16 lanes per configuration for p <= 64 / 128 / 256 / 512 / 1024 and
 //                                     q <= 1023; the general kernel for the rest and for reruns.
 enum ClassKind { kUniTimes, kUniSched, kBiGroup, kBiGeneral, kBiBlock, kUniWide };
@@ -115,6 +116,8 @@ struct Layout {
     ClassSpec cls[kClasses];
     ClassSpec rerun;              // bi-greedy: the one-wavefront kernel for configurations the group kernel hands back
     ClassSpec wide;               // uni-greedy completion times: the block-per-configuration kernel (grid 0: not used)
+    bool help;                    // its wavefronts begin with the small machines when they have no large ones left
+    ClassSpec large;              // uni-greedy completion times: machines of more than kUniSmallProcs processors (grid 0: none)
     bool bi_on[kClasses - 1];     // bi-greedy group classes a configuration can fall into
 };
 
@@ -152,67 +155,91 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
     for (int k = 0; k < kClasses - 1; ++k) L.limits.p[k] = plim[k];
     L.limits.q = kGroupQMax;
     L.limits.by_work = 0;
-    for (int k = 0; k < kClasses - 1; ++k) L.limits.work[k] = 0;
-    L.limits.giant_log2 = kGiantLog2;
-    L.limits.lanes_log2 = 0;
+    L.limits.large_p = 0;
+    for (int set = 0; set < 2; ++set) {
+        for (int k = 0; k < kClasses - 1; ++k) L.limits.work[set][k] = 0;
+        L.limits.giant_log2[set] = kGiantLog2;
+        L.limits.lanes_log2[set] = 0;
+    }
     L.limits.wide_p = 0;
+    L.large.grid = 0;
+    L.help = false;
     L.wide.grid = 0; L.wide.slot_bytes = 0; L.wide.slot_offset = 0;
     static const int group_lpc[kClasses - 1] = {1, 2, 4, 8, 16};
     if (model == PRS_UNI) {
-        // classes by number of pairs (1, 2, 4, 8, 16 or 32 lanes per configuration; schedules 1, 8, 16 or 32), all run by
-        // one launch, described by class 0
+        // Classes by number of pairs (1, 2, 4, 8, 16 or 32 lanes per configuration; schedules 1, 8, 16 or 32), all run by
+        // one launch, described by class 0.  Completion times of machines with more than kUniSmallProcs processors take a
+        // launch of their own, whose wavefronts have larger rings: a bound p_max above the machines of a batch, or one large
+        // machine among them, does not cost the others their wavefronts (100,000 machines of up to 1024 processors with
+        // p_max = 16384: 15.5 ms with the large rings for all, one wavefront per CU).
         L.limits.by_work = 1;
+        const bool has_large = !sched && p_max > kUniSmallProcs;
+        if (has_large) L.limits.large_p = kUniSmallProcs;
+        const int32_t p_small = has_large ? kUniSmallProcs : p_max;
         for (int k = 0; k < kClasses - 1; ++k) L.limits.p[k] = sched || compositions ? INT32_MAX : kUniTimesProcs[k];
-        for (int k = 0; k < kClasses - 1; ++k)
-            L.limits.work[k] = sched ? kUniWorkSched[k < kUniGroupSizes ? k : kUniGroupSizes - 1] : kUniTimesWork[k];
-        if (!sched) {
-            L.limits.giant_log2 = kUniTimesGiantLog2;
-            // A batch that leaves lanes without a configuration gives each of its configurations more of them.
-            const int64_t lanes = blocks_per_cu(uni_times_lds_bytes(p_max, compositions)) * kCUs * kWave;
+        for (int set = 0; set < 2; ++set) {
+            int64_t *const work = L.limits.work[set];
             for (int k = 0; k < kClasses - 1; ++k)
-                if (n << (k + 1) <= lanes) L.limits.work[k] = 0;
-            if (n << 6 <= lanes) L.limits.giant_log2 = 0;
-            else L.limits.lanes_log2 = 1;
-        } else {
-            // The same for schedules: 64, 32, 16 or 8 lanes where the batch leaves that many idle (one machine of 256
-            // processors and 64 segments 3.2 -> 2.6 ms, a few hundred machines 3.3 -> 2.1 ms).
-            const int64_t lanes = blocks_per_cu(uni_sched_lds_bytes()) * kCUs * kWave;
-            static const int more[kUniGroupSizes] = {3, 4, 5};            // the next group size: 8, 16, 32 lanes
-            for (int k = 0; k < kClasses - 1; ++k)
-                if (n << more[k < kUniGroupSizes ? k : kUniGroupSizes - 1] <= lanes) L.limits.work[k] = 0;
-            if (n << 6 <= lanes) L.limits.giant_log2 = 0;
-        }
-        if (tuning) {                                              // never changes a result, only who runs what
-            L.limits.lanes_log2 = 0;
-            L.limits.giant_log2 = sched ? kGiantLog2 : kUniTimesGiantLog2;
-            for (int k = 0; k < kClasses - 1; ++k) L.limits.p[k] = INT32_MAX;
-            const int64_t a = tuning->uni_group_pairs[0], b = tuning->uni_group_pairs[1], c3 = tuning->uni_group_pairs[2];
-            if (a >= 0 && b >= a && c3 >= b) {
-                if (sched) {
-                    L.limits.work[0] = a; L.limits.work[1] = b;
-                    for (int k = 2; k < kClasses - 1; ++k) L.limits.work[k] = c3;
-                } else {                                           // 1, 4 and 16 lanes; nothing for 2 and 8
-                    L.limits.work[0] = L.limits.work[1] = a;
-                    L.limits.work[2] = L.limits.work[3] = b;
-                    L.limits.work[4] = c3;
-                }
+                work[k] = sched ? kUniWorkSched[k < kUniGroupSizes ? k : kUniGroupSizes - 1] : kUniTimesWork[k];
+            if (!sched) {
+                L.limits.giant_log2[set] = kUniTimesGiantLog2;
+                // A batch that leaves lanes without a configuration gives each of its configurations more of them.
+                const int64_t lanes = blocks_per_cu(uni_times_lds_bytes(set ? p_max : p_small, compositions)) * kCUs * kWave;
+                for (int k = 0; k < kClasses - 1; ++k)
+                    if (n << (k + 1) <= lanes) work[k] = 0;
+                if (n << 6 <= lanes) L.limits.giant_log2[set] = 0;
+                else L.limits.lanes_log2[set] = 1;
+            } else {
+                // The same for schedules: 64, 32, 16 or 8 lanes where the batch leaves that many idle (one machine of 256
+                // processors and 64 segments 3.2 -> 2.6 ms, a few hundred machines 3.3 -> 2.1 ms).
+                const int64_t lanes = blocks_per_cu(uni_sched_lds_bytes()) * kCUs * kWave;
+                static const int more[kUniGroupSizes] = {3, 4, 5};            // the next group size: 8, 16, 32 lanes
+                for (int k = 0; k < kClasses - 1; ++k)
+                    if (n << more[k < kUniGroupSizes ? k : kUniGroupSizes - 1] <= lanes) work[k] = 0;
+                if (n << 6 <= lanes) L.limits.giant_log2[set] = 0;
             }
-            if (tuning->uni_wave_log2 > 0 && tuning->uni_wave_log2 < kWorkBuckets) L.limits.giant_log2 = tuning->uni_wave_log2;
+            if (tuning) {                                              // never changes a result, only who runs what
+                L.limits.lanes_log2[set] = 0;
+                L.limits.giant_log2[set] = sched ? kGiantLog2 : kUniTimesGiantLog2;
+                for (int k = 0; k < kClasses - 1; ++k) L.limits.p[k] = INT32_MAX;
+                const int64_t a = tuning->uni_group_pairs[0], b = tuning->uni_group_pairs[1], c3 = tuning->uni_group_pairs[2];
+                if (a >= 0 && b >= a && c3 >= b) {
+                    if (sched) {
+                        work[0] = a; work[1] = b;
+                        for (int k = 2; k < kClasses - 1; ++k) work[k] = c3;
+                    } else {                                           // 1, 4 and 16 lanes; nothing for 2 and 8
+                        work[0] = work[1] = a;
+                        work[2] = work[3] = b;
+                        work[4] = c3;
+                    }
+                }
+                if (tuning->uni_wave_log2 > 0 && tuning->uni_wave_log2 < kWorkBuckets) L.limits.giant_log2[set] = tuning->uni_wave_log2;
+            }
         }
-        for (int k = 0; k < kClasses; ++k) {
-            ClassSpec &c = L.cls[k];
+        auto uni_spec = [&](ClassSpec &c, int32_t p) {                 // one launch for machines of up to p processors
             c.q_cap = q_max;
             c.kind = sched ? kUniSched : kUniTimes; c.lpc = 0; c.rows_per_group = 0; c.lds = true; c.lds_bitmap_bytes = 0;
             // schedules: keeps every per-lane array 64-byte aligned; times: a ring per lane
-            c.p_cap = sched ? (p_max + 15) / 16 * 16 : (uni_times_slot_runs(p_max) + 15) / 16 * 16;
-            c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes(p_max, compositions);
-            c.slot_bytes = k != 0 ? 0 : (sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap));
+            c.p_cap = sched ? (p + 15) / 16 * 16 : (uni_times_slot_runs(p) + 15) / 16 * 16;
+            c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes(p, compositions);
+            c.slot_bytes = sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap);
             int64_t g = blocks_per_cu(c.lds_bytes) * kCUs;
             while (g > 1 && static_cast<size_t>(g) * c.slot_bytes > kMaxWorkspace) g /= 2;
-            c.grid = k == 0 ? static_cast<int>(g) : 0;
+            c.grid = static_cast<int>(g);
             c.slot_offset = off;
-            off += align256(static_cast<size_t>(c.grid) * c.slot_bytes);
+            return align256(static_cast<size_t>(c.grid) * c.slot_bytes);
+        };
+        size_t slots = uni_spec(L.cls[0], p_small);
+        for (int k = 1; k < kClasses; ++k) { L.cls[k] = L.cls[0]; L.cls[k].grid = 0; L.cls[k].slot_bytes = 0; }
+        if (has_large) {                                               // the launches follow each other and share the slots
+            // A batch whose small machines leave lanes idle is bound by its longest chains: these begin beside the large
+            // machines (3000 machines, 81 of them of 1024 to 20000 processors: 5.9 -> 4.0 ms).  A larger one is bound by how many
+            // run at once, which is one wavefront per CU there and five in the launch that follows (30000 machines: 5.9 -> 6.4).
+            L.help = n << 4 <= blocks_per_cu(uni_times_lds_bytes(p_small, compositions)) * kCUs * kWave;
+            const size_t large = uni_spec(L.large, p_max);
+            if (large > slots) slots = large;
         }
+        off += slots;
         // completion times of machines with thousands of processors: a block per configuration
         if (!sched) {
             int32_t wide_p = kUniWideProcs;
@@ -347,7 +374,7 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
         L.p_max = p_max; L.q_max = q_max; L.model = model; L.cost = cost;
         L.want_schedule = call == PRS_CALL_SCHEDULE;
         L.times = times; L.sched = sched;
-        L.plan = P.header; L.order = order; L.cls = cls;
+        L.plan = P.header; L.order = order; L.cls = cls; L.help = lay.help;
         L.list_entries = (tuning && tuning->bi_list_entries > 0 && tuning->bi_list_entries < kWave) ? tuning->bi_list_entries : kWave;
         L.lds_p = c.lds ? c.p_cap : 0;
         L.lds_bitmap_bytes = c.lds_bitmap_bytes;
@@ -365,6 +392,7 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
     };
     // the class with the longest-running configurations first; a class without configurations ends at once
     if (lay.limits.wide_p > 0 && general(lay.wide, P.order, kWideClass) != hipSuccess) return PRS_EDEVICE;
+    if (lay.large.grid > 0 && general(lay.large, P.order, kLargeClass) != hipSuccess) return PRS_EDEVICE;
     bool groups_done = false;
     for (int k = kClasses - 1; k >= 0; --k) {
         const ClassSpec &c = lay.cls[k];

@@ -37,6 +37,7 @@ struct UniLaunch {
     PlanHeader *plan;
     const int32_t *order;
     int cls;
+    bool help;                    // uni-greedy times of large machines: idle wavefronts begin with the small ones
     int list_entries;             // block kernel of bi-greedy: most running transfers it may list (1 .. 64)
     int32_t lds_p;
     int32_t lds_bitmap_bytes;

@@ -11,9 +11,11 @@ __device__ __forceinline__ int plan_bucket(const ConfigArrays &cfg, int64_t i, i
     const int64_t work = static_cast<int64_t>(c.p - 1) * c.q;
     int cls = kClasses - 1;
     if (lim.by_work) {
+        const bool large = lim.large_p > 0 && c.p > lim.large_p;
         for (int k = kClasses - 2; k >= 0; --k)
-            if (work <= lim.work[k] && c.p <= lim.p[k]) cls = k;
-        if (lim.lanes_log2) { const int enough = ceil_log2(c.q); cls = cls < enough ? cls : enough; }
+            if (work <= lim.work[large ? 1 : 0][k] && c.p <= lim.p[k]) cls = k;
+        if (lim.lanes_log2[large ? 1 : 0]) { const int enough = ceil_log2(c.q); cls = cls < enough ? cls : enough; }
+        if (large) cls += kLargeClass;
         if (lim.wide_p > 0 && c.p >= lim.wide_p && cfg.comp_m == 0) cls = kWideClass;
     } else {
         for (int k = kClasses - 2; k >= 0; --k)
@@ -27,9 +29,9 @@ __device__ __forceinline__ int plan_bucket(const ConfigArrays &cfg, int64_t i, i
 __global__ void plan_clear(PlanHeader *h)
 {
     const int i = threadIdx.x;
-    if (i < kClasses + 1) { h->ticket[i] = 0ULL; h->class_begin[i] = 0; h->class_count[i] = 0; }
-    if (i == 0) { h->giant_count = 0; h->ticket_giant = 0ULL; }
-    for (int k = i; k < kPlanClasses * kWorkBuckets; k += blockDim.x) { h->hist[k] = 0; h->start[k] = 0; h->cursor[k] = 0; }
+    if (i < kPlanClasses) { h->ticket[i] = 0ULL; h->class_begin[i] = 0; h->class_count[i] = 0; }
+    if (i < 2) { h->giant_count[i] = 0; h->ticket_giant[i] = 0ULL; }
+    for (int k = i; k < kPlanClasses * kWorkBuckets; k += blockDim.x) h->place[k] = 0;
 }
 
 constexpr int kPlanThreads = 256;
@@ -39,45 +41,52 @@ constexpr int kPlanBins = kPlanClasses * kWorkBuckets;
 // global atomic per configuration, a batch of millions spends its time queueing on a few dozen addresses.
 template <typename T>
 __global__ __launch_bounds__(kPlanThreads) void plan_hist(ConfigArrays cfg, int64_t n, int32_t p_max, int32_t q_max, ClassLimits lim,
-                                                          PlanHeader *h)
+                                                          int bins, PlanHeader *h)
 {
     __shared__ int32_t local[kPlanBins];
     const int tid = static_cast<int>(threadIdx.x);
-    for (int k = tid; k < kPlanBins; k += kPlanThreads) local[k] = 0;
+    for (int k = tid; k < bins; k += kPlanThreads) local[k] = 0;
     __syncthreads();
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kPlanThreads + tid;
     if (i < n) atomicAdd(&local[plan_bucket<T>(cfg, i, p_max, q_max, lim)], 1);
     __syncthreads();
-    for (int k = tid; k < kPlanBins; k += kPlanThreads)
-        if (local[k] != 0) atomicAdd(&h->hist[k], local[k]);
+    for (int k = tid; k < bins; k += kPlanThreads)
+        if (local[k] != 0) atomicAdd(&h->place[k], local[k]);
 }
 
-// n_classes: kClasses, or kPlanClasses when the batch has a class of wide machines (otherwise that slot is the
-// retry list of bi-greedy, which starts empty at position 0 of an array of its own)
-__global__ void plan_scan(PlanHeader *h, int32_t giant_log2, int n_classes)
+// One wavefront turns the counts of the first n_classes classes into places (the class after kClasses is the retry list of
+// bi-greedy otherwise, which starts empty at position 0 of an array of its own).
+__global__ __launch_bounds__(kWave) void plan_scan(PlanHeader *h, int giant_log2, int giant_log2_large, int n_classes)
 {
-    if (threadIdx.x != 0) return;
+    __shared__ int32_t before[kPlanBins + 1];
+    const int lane = lane_id(), bins = n_classes * kWorkBuckets;
     int32_t run = 0;
-    for (int c = 0; c < n_classes; ++c) {
-        h->class_begin[c] = run;
-        for (int b = 0; b < kWorkBuckets; ++b) {
-            h->start[c * kWorkBuckets + b] = run;
-            run += h->hist[c * kWorkBuckets + b];
-        }
-        h->class_count[c] = run - h->class_begin[c];
+    for (int at = 0; at < bins; at += kWave) {
+        const int k = at + lane;
+        const int32_t n = k < bins ? h->place[k] : 0, upto = run + wave_inclusive_scan(n);
+        if (k < bins) { h->place[k] = upto - n; before[k] = upto - n; }
+        run = __shfl(upto, kWave - 1, kWave);
     }
-    int32_t giants = 0;                                   // buckets are ordered heaviest first: bucket b holds floor(log2) = kWorkBuckets-1-b
-    for (int b = 0; b <= kWorkBuckets - 1 - giant_log2; ++b) giants += h->hist[(kClasses - 1) * kWorkBuckets + b];
-    h->giant_count = giants;
+    if (lane == 0) before[bins] = run;
+    __syncthreads();
+    if (lane < n_classes) {
+        h->class_begin[lane] = before[lane * kWorkBuckets];
+        h->class_count[lane] = before[(lane + 1) * kWorkBuckets] - before[lane * kWorkBuckets];
+    }
+    if (lane == 0) h->large_left = kLargeClass < n_classes ? before[bins] - before[kLargeClass * kWorkBuckets] : 0;
+    // buckets are ordered heaviest first: bucket b holds floor(log2) = kWorkBuckets - 1 - b
+    const int last = (lane == 0 ? kClasses - 1 : kLargeClass + kClasses - 1), giants = kWorkBuckets - (lane == 0 ? giant_log2 : giant_log2_large);
+    if (lane < 2 && last < n_classes && giants > 0)
+        h->giant_count[lane] = before[last * kWorkBuckets + giants] - before[last * kWorkBuckets];
 }
 
 template <typename T>
 __global__ __launch_bounds__(kPlanThreads) void plan_scatter(ConfigArrays cfg, int64_t n, int32_t p_max, int32_t q_max, ClassLimits lim,
-                                                             PlanHeader *h, int32_t *order)
+                                                             int bins, PlanHeader *h, int32_t *order)
 {
     __shared__ int32_t local[kPlanBins];                             // configurations of this block per bin, then the bin's first slot
     const int tid = static_cast<int>(threadIdx.x);
-    for (int k = tid; k < kPlanBins; k += kPlanThreads) local[k] = 0;
+    for (int k = tid; k < bins; k += kPlanThreads) local[k] = 0;
     __syncthreads();
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kPlanThreads + tid;
     int b = 0, rank = 0;
@@ -86,25 +95,26 @@ __global__ __launch_bounds__(kPlanThreads) void plan_scatter(ConfigArrays cfg, i
         rank = atomicAdd(&local[b], 1);
     }
     __syncthreads();
-    for (int k = tid; k < kPlanBins; k += kPlanThreads)
-        if (local[k] != 0) local[k] = h->start[k] + atomicAdd(&h->cursor[k], local[k]);
+    for (int k = tid; k < bins; k += kPlanThreads)
+        if (local[k] != 0) local[k] = atomicAdd(&h->place[k], local[k]);
     __syncthreads();
     if (i < n) order[local[b] + rank] = static_cast<int32_t>(i);
 }
 
-hipError_t launch_plan(const PlanLaunch &L)
+template <typename T> static void launch_plan_as(const PlanLaunch &L)
 {
     const unsigned blocks = static_cast<unsigned>((L.n + kPlanThreads - 1) / kPlanThreads);
+    const ClassLimits &lim = L.limits;
+    const int classes = !lim.by_work ? kClasses : lim.large_p > 0 ? kPlanClasses : lim.wide_p > 0 ? kWideClass + 1 : kClasses;
     hipLaunchKernelGGL(plan_clear, dim3(1), dim3(256), 0, L.stream, L.header);
-    if (L.cost == PRS_COST_I64) {
-        hipLaunchKernelGGL((plan_hist<int64_t>), dim3(blocks), dim3(kPlanThreads), 0, L.stream, L.cfg, L.n, L.p_max, L.q_max, L.limits, L.header);
-        hipLaunchKernelGGL(plan_scan, dim3(1), dim3(64), 0, L.stream, L.header, L.limits.giant_log2, (L.limits.by_work && L.limits.wide_p > 0) ? kPlanClasses : kClasses);
-        hipLaunchKernelGGL((plan_scatter<int64_t>), dim3(blocks), dim3(kPlanThreads), 0, L.stream, L.cfg, L.n, L.p_max, L.q_max, L.limits, L.header, L.order);
-    } else {
-        hipLaunchKernelGGL((plan_hist<double>), dim3(blocks), dim3(kPlanThreads), 0, L.stream, L.cfg, L.n, L.p_max, L.q_max, L.limits, L.header);
-        hipLaunchKernelGGL(plan_scan, dim3(1), dim3(64), 0, L.stream, L.header, L.limits.giant_log2, (L.limits.by_work && L.limits.wide_p > 0) ? kPlanClasses : kClasses);
-        hipLaunchKernelGGL((plan_scatter<double>), dim3(blocks), dim3(kPlanThreads), 0, L.stream, L.cfg, L.n, L.p_max, L.q_max, L.limits, L.header, L.order);
-    }
+    hipLaunchKernelGGL((plan_hist<T>), dim3(blocks), dim3(kPlanThreads), 0, L.stream, L.cfg, L.n, L.p_max, L.q_max, lim, classes * kWorkBuckets, L.header);
+    hipLaunchKernelGGL(plan_scan, dim3(1), dim3(kWave), 0, L.stream, L.header, lim.giant_log2[0], lim.giant_log2[1], classes);
+    hipLaunchKernelGGL((plan_scatter<T>), dim3(blocks), dim3(kPlanThreads), 0, L.stream, L.cfg, L.n, L.p_max, L.q_max, lim, classes * kWorkBuckets, L.header, L.order);
+}
+
+hipError_t launch_plan(const PlanLaunch &L)
+{
+    if (L.cost == PRS_COST_I64) launch_plan_as<int64_t>(L); else launch_plan_as<double>(L);
     return hipGetLastError();
 }
 

@@ -135,8 +135,8 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
     // part of the class this pass works on: all of it, its giant configurations only, or the rest after those
     int32_t count = plan->class_count[cls], begin = plan->class_begin[cls];
     unsigned long long *tickets = &plan->ticket[cls];
-    if (part == kGiantPart) { count = plan->giant_count; tickets = &plan->ticket_giant; }
-    else if (part == kRestPart) { begin += plan->giant_count; count -= plan->giant_count; }
+    if (part == kGiantPart) { count = plan->giant_count[0]; tickets = &plan->ticket_giant[0]; }
+    else if (part == kRestPart) { begin += plan->giant_count[0]; count -= plan->giant_count[0]; }
     if (count == 0) return;
     const T kInf = CostTraits<T>::inf();
 

@@ -139,7 +139,7 @@ __device__ __forceinline__ int32_t ring_next(const Ring &r, int32_t at)
 template <typename T, int G, bool kComp, bool kSmall>
 __device__ __forceinline__ void uni_times_body(const RingShape &shape, const ConfigArrays &cfg, int32_t p_max, int32_t q_max,
                                                int model, const TimesOut &times, PlanHeader *plan, const int32_t *order, int cls,
-                                               int part, char *slot, int32_t slot_p)
+                                               int part, char *slot, int32_t slot_p, bool help = false)
 {
     constexpr int kGroups = kWave / G, kSmallRuns = kSmall ? SmallRings<kComp>::kRuns : 0;
     // a new configuration is fetched (a path every lane waits for) when this many groups have nothing to do
@@ -150,15 +150,17 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
     const int prod = gbase | ((gl + G - 1) & (G - 1));
     const uint64_t gmask = (G == 64 ? ~UINT64_C(0) : ((UINT64_C(1) << G) - 1)) << gbase;
     // part of the class this pass works on: all of it, its giant configurations only, or the rest after those
+    const int set = cls >= kLargeClass ? 1 : 0;
     int32_t count = plan->class_count[cls], begin = plan->class_begin[cls];
     unsigned long long *tickets = &plan->ticket[cls];
-    if (part == kGiantPart) { count = plan->giant_count; tickets = &plan->ticket_giant; }
-    else if (part == kRestPart) { begin += plan->giant_count; count -= plan->giant_count; }
+    if (part == kGiantPart) { count = plan->giant_count[set]; tickets = &plan->ticket_giant[set]; }
+    else if (part == kRestPart) { begin += plan->giant_count[set]; count -= plan->giant_count[set]; }
     if (count == 0) return;
     // Tickets are drawn several at a time, a sixteenth of a wavefront's share at most (a counter that every wavefront adds to
     // serves one of them every few nanoseconds); those in hand are hand .. hand_end - 1, and may lie past the end.
     int batch = count / (static_cast<int>(gridDim.x) * 16);
     if (batch > 4 * kGroups) batch = 4 * kGroups;
+    if (help) batch = 0;                                              // every ticket drawn is run
     int64_t hand = 0, hand_end = 0;
 
     // ---- per-group state (the same in all lanes of a group)
@@ -211,6 +213,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
 
     for (;;) {
         // ---------------------------------------------------------------- fetch configurations
+        if (help && __hip_atomic_load(&plan->large_left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) exhausted = exhausted || !have;
         const uint64_t need = ballot64(gl == 0 && !have && !exhausted);
         if (need != 0) {
             // the groups without a configuration take the tickets in hand first, then those just drawn
@@ -313,6 +316,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
                         store(wat, T(0), 0);
                         bat = wlast = wat;
                         if (k == q - 1 && times.greedy) static_cast<T *>(times.greedy)[ci] = tr;
+                        if (!kSmall && k == q - 1 && set == 1) atomicAdd(&plan->large_left, -1);
                         k += G;
                         active = k < q;
                         lastS = T(-1); odd = 0; left = active ? p - 1 : 0; aleft = p;
@@ -350,42 +354,52 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
     }
 }
 
-// One launch for the whole batch: every wavefront works through the classes from the heaviest
+// One launch for all machines of a ring size: every wavefront works through the classes from the heaviest
 // configurations (largest groups) to the lightest, so the long-running ones start first and the light
 // ones fill the machine around them.
 template <typename T, bool kComp, bool kSmall>
 __global__ __launch_bounds__(kWave) void uni_times_kernel(RingShape shape, ConfigArrays cfg, int32_t p_max, int32_t q_max, int model,
                                                           TimesOut times, PlanHeader *plan, const int32_t *order, char *slots,
-                                                          size_t slot_bytes, int32_t slot_p)
+                                                          size_t slot_bytes, int32_t slot_p, bool help)
 {
     // LDS is addressed from 0: the kernel has no other LDS than what the launch asks for
     if (kSmall) shape = RingShape{SmallRings<kComp>::kRuns, SmallRings<kComp>::kRing};
+    constexpr int kFirst = kSmall ? 0 : kLargeClass;
     char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
-    uni_times_body<T, 64, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kGiantPart, slot, slot_p);
+    uni_times_body<T, 64, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + kClasses - 1, kGiantPart, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 32, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kRestPart, slot, slot_p);
+    uni_times_body<T, 32, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + kClasses - 1, kRestPart, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 16, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 4, kWholeClass, slot, slot_p);
+    uni_times_body<T, 16, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 4, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 8, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 3, kWholeClass, slot, slot_p);
+    uni_times_body<T, 8, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 3, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 4, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 2, kWholeClass, slot, slot_p);
+    uni_times_body<T, 4, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 2, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 2, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 1, kWholeClass, slot, slot_p);
+    uni_times_body<T, 2, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 1, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_times_body<T, 1, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 0, kWholeClass, slot, slot_p);
+    uni_times_body<T, 1, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 0, kWholeClass, slot, slot_p);
+    if (!kSmall && help) {
+        // while the last of the large machines run, wavefronts that have none begin with the heavy small ones
+        __syncthreads();
+        uni_times_body<T, 64, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kGiantPart, slot, slot_p, true);
+        __syncthreads();
+        uni_times_body<T, 32, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kRestPart, slot, slot_p, true);
+        __syncthreads();
+        uni_times_body<T, 16, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 4, kWholeClass, slot, slot_p, true);
+    }
 }
 
 template <typename T, bool kComp>
 static void launch_uni_times_as(const UniLaunch &L)
 {
     const RingShape shape = large_rings(L.p_max);
-    if (L.p_max <= kUniSmallProcs)
+    if (L.cls < kLargeClass)
         hipLaunchKernelGGL((uni_times_kernel<T, kComp, true>), dim3(L.grid), dim3(kWave), L.lds_bytes, L.stream, shape, L.cfg, L.p_max,
-                           L.q_max, L.model, L.times, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p);
+                           L.q_max, L.model, L.times, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p, L.help);
     else
         hipLaunchKernelGGL((uni_times_kernel<T, kComp, false>), dim3(L.grid), dim3(kWave), L.lds_bytes, L.stream, shape, L.cfg, L.p_max,
-                           L.q_max, L.model, L.times, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p);
+                           L.q_max, L.model, L.times, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p, L.help);
 }
 
 hipError_t launch_uni_times(const UniLaunch &L)

@@ -214,6 +214,38 @@ def test_uni_times_one_lane_with_as_many_runs_as_processors(prs, p):
     assert np.array_equal(_np(best["T_greedy"]), ref["T_greedy"]) and np.array_equal(_np(best["q_greedy"]), ref["q_greedy"])
 
 
+@pytest.mark.parametrize("cost", ["i64", "f64"])
+@pytest.mark.parametrize("p_max,n", [(1025, 33000), (8192, 33000), (8193, 17000), (40000, 17000), (8193, 40), (1025, 700)])
+def test_uni_times_small_and_large_machines_in_one_batch(prs, p_max, n, cost):
+    """Machines of up to 1024 processors and larger ones have rings of different size and a launch each: the last small and
+    the first large machine, every group size of the large ones (few segments, few lanes), bounds on both sides of the
+    two sizes of their rings, batches with and without idle lanes, invalid configurations among them; bit for bit."""
+    shapes = [(2, 1), (1024, 5), (60, 30), (1024, 128), (300, 300), (1025, 1), (1025, 2), (1025, 4), (1025, 8), (1025, 9), (1025, 200),
+              (1100, 600), (8192, 3), (8192, 70), (8193, 20), (39999, 2), (40000, 18)]
+    shapes = [s for s in shapes if s[0] <= p_max]
+    rng = np.random.default_rng(p_max + n)
+    k = len(shapes)
+    p, q = (np.array([s[i] for s in shapes], np.int32) for i in (0, 1))
+    m = (q.astype(np.int64) * 5 - rng.integers(0, 5, k)).clip(1)
+    if cost == "i64":
+        host = prs_inputs.SweepConfigs(p, q, m, rng.integers(0, 12, k).astype(np.int64), rng.integers(1, 4, k).astype(np.int64),
+                                       rng.integers(0, 4, k).astype(np.int64), cost)
+    else:
+        host = prs_inputs.SweepConfigs(p, q, m, 10.0 ** rng.uniform(-6, -4, k), 10.0 ** rng.uniform(-10, -8, k),
+                                       10.0 ** rng.uniform(-11, -9, k), cost)
+    ref = np.array([O.uni_greedy_time(int(p[i]), O.equi_sizes(int(m[i]), int(q[i])), host.alpha[i].item(), host.beta[i].item(),
+                                      host.gamma[i].item(), cost) for i in range(k)])
+    every = np.arange(n) % k
+    many = host.take(every)
+    many.p[7], many.p[11], many.p[13] = p_max + 1, 1, 2000000000
+    got = prs.simulate_completion_batch(prs.DeviceConfigs.from_host(many), 0, p_max, 600)
+    _sync()
+    want = np.zeros(n, np.int32)
+    want[[7, 11, 13]] = 2, 1, 2
+    assert np.array_equal(_np(got["cfg_status"]), want)
+    assert np.array_equal(_np(got["greedy"])[want == 0], ref[every][want == 0])
+
+
 def test_uni_times_a_block_per_configuration(prs):
     """The kernel that gives a machine of thousands of processors a block of its own and forms many pairs of a
     segment at once, here fed with machines of every size (the limit lowered to two processors): completion
