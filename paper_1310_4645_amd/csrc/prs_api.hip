@@ -3,6 +3,8 @@
 #include "prs_device.h"
 #include "prs_launch.h"
 
+#include <algorithm>
+
 namespace prs {
 
 constexpr size_t kHeaderBytes = 256;
@@ -219,15 +221,23 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
         auto uni_spec = [&](ClassSpec &c, int32_t p) {                 // one launch for machines of up to p processors
             c.q_cap = q_max;
             c.kind = sched ? kUniSched : kUniTimes; c.lpc = 0; c.rows_per_group = 0; c.lds = true; c.lds_bitmap_bytes = 0;
-            // schedules: keeps every per-lane array 64-byte aligned; times: a ring per lane
-            c.p_cap = sched ? (p + 15) / 16 * 16 : (uni_times_slot_runs(p) + 15) / 16 * 16;
+            // schedules: keeps every per-lane array 64-byte aligned; times: runs of a lane's ring
+            c.p_cap = sched ? (p + 15) / 16 * 16 : uni_times_slot_runs(p);
             c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes(p, compositions);
-            c.slot_bytes = sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap);
+            c.slot_bytes = sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap, p <= kUniSmallProcs);
             int64_t g = blocks_per_cu(c.lds_bytes) * kCUs;
-            while (g > 1 && static_cast<size_t>(g) * c.slot_bytes > kMaxWorkspace) g /= 2;
+            if (!sched && g > n) g = n < 1 ? 1 : n;
+            size_t bytes = static_cast<size_t>(g) * c.slot_bytes;
+            if (sched) {
+                while (g > 1 && static_cast<size_t>(g) * c.slot_bytes > kMaxWorkspace) g /= 2;
+                bytes = static_cast<size_t>(g) * c.slot_bytes;
+            } else if (bytes > kMaxWorkspace) {
+                bytes = kMaxWorkspace;
+                g = static_cast<int64_t>(bytes / c.slot_bytes);
+            }
             c.grid = static_cast<int>(g);
             c.slot_offset = off;
-            return align256(static_cast<size_t>(c.grid) * c.slot_bytes);
+            return align256(bytes);
         };
         size_t slots = uni_spec(L.cls[0], p_small);
         for (int k = 1; k < kClasses; ++k) { L.cls[k] = L.cls[0]; L.cls[k].grid = 0; L.cls[k].slot_bytes = 0; }
@@ -236,16 +246,15 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             // machines (3000 machines, 81 of them of 1024 to 20000 processors: 5.9 -> 4.0 ms).  A larger one is bound by how many
             // run at once, which is one wavefront per CU there and five in the launch that follows (30000 machines: 5.9 -> 6.4).
             L.help = n << 4 <= blocks_per_cu(uni_times_lds_bytes(p_small, compositions)) * kCUs * kWave;
-            const size_t large = uni_spec(L.large, p_max);
-            if (large > slots) slots = large;
+            if (p_max > kUniMidProcs) slots = std::max(slots, uni_spec(L.large, kUniMidProcs));   // more wavefronts: no less than for that bound
+            slots = std::max(slots, uni_spec(L.large, p_max));
         }
-        off += slots;
         // completion times of machines with thousands of processors: a block per configuration
         if (!sched) {
             int32_t wide_p = kUniWideProcs;
             if (tuning && tuning->uni_wide_procs > 0) wide_p = tuning->uni_wide_procs;
             if (p_max >= wide_p) L.limits.wide_p = wide_p;
-            {                                                          // its slots are always there: the size of the workspace does not depend on the tuning
+            {                                                          // runs before the others, in the same slots (smaller than theirs)
                 ClassSpec &c = L.wide;
                 c.kind = kUniWide; c.p_cap = p_max; c.q_cap = q_max; c.lds = true; c.lds_bytes = uni_wide_lds_bytes();
                 c.lds_bitmap_bytes = 0; c.lpc = 0; c.rows_per_group = 0;
@@ -255,9 +264,10 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
                 if (g > n) g = n < 1 ? 1 : n;
                 c.grid = static_cast<int>(g);
                 c.slot_offset = off;
-                off += align256(static_cast<size_t>(c.grid) * c.slot_bytes);
+                slots = std::max(slots, align256(static_cast<size_t>(c.grid) * c.slot_bytes));
             }
         }
+        off += slots;
         L.total = off;
         return L;
     }

@@ -22,7 +22,7 @@ struct SchedOut {
 // Rings of a wavefront of the uni-greedy completion-time kernel in LDS: `runs` runs in all, runs_per_lane for every lane but
 // the last of a group, which shares what is left with the last lanes of the other groups.
 struct RingShape { int32_t runs, runs_per_lane; };
-constexpr int32_t kUniSmallProcs = 1024;
+constexpr int32_t kUniSmallProcs = 1024, kUniMidProcs = 8192;    // largest machines of the first two ring sizes
 
 // One launch = one size class of the plan.  lds_p > 0: per-configuration state lives in LDS arrays sized
 // for lds_p processors (uni) / the small arrays and, if it fits lds_bitmap_bytes, the sent bitmap (bi);
@@ -88,7 +88,7 @@ hipError_t launch_bi_group(const BiGroupLaunch &L);
 // uni-greedy: all classes of a batch in one launch
 size_t uni_times_lds_bytes(int32_t p_max, bool compositions);
 int32_t uni_times_slot_runs(int32_t p_max);
-size_t uni_times_slot_bytes(int32_t p_cap);
+size_t uni_times_slot_bytes(int32_t runs, bool small);
 hipError_t launch_uni_times(const UniLaunch &L);
 size_t uni_sched_lds_bytes();
 size_t uni_sched_slot_bytes(int32_t p_cap);

@@ -29,8 +29,8 @@
 // the scattered 8-byte stores, about 9 cycles of a CU's store path each.)  The rings of a group can all be
 // full at once only through the last lane, whose reader, the first lane, is a whole round behind: its ring
 // is the deep one.  If it does fill up -- or B outgrows a ring -- no lane of the group moves any more; the
-// configuration then starts again with its rings in the wavefront's workspace slot, p + 7 runs each, in which a
-// lane never waits: of its stream at most p runs are unread -- a segment cannot have sent more processors than
+// configuration then starts again with its rings in the wavefront's workspace slot, p + 7 runs each (none where p + 7 runs fit
+// every ring in LDS), in which a lane never waits: of its stream at most p runs are unread -- a segment cannot have sent more processors than
 // the lane that reads its stream has taken from the stream before it, and all p of them with one lane, which
 // reads its own stream, at the end of a segment without equal ready times -- and a lane goes on as long as 7 places
 // are left, for the runs of a chunk of steps, the root's and the open one.  (p + 4 places were too few for one lane.)
@@ -61,16 +61,21 @@ template <> struct SmallRings<false> { static constexpr int kRuns = 2730, kRing 
 template <> struct SmallRings<true> { static constexpr int kRuns = 4096, kRing = 36; };
 static RingShape large_rings(int32_t p_max)
 {
-    return p_max <= 8192 ? RingShape{6826, 96} : RingShape{13653, 192};       // B: 40 runs with 15,000 processors, 131 with 45,000
+    return p_max <= kUniMidProcs ? RingShape{6826, 96} : RingShape{13653, 192};       // B: 40 runs with 15,000 processors, 131 with 45,000
 }
 size_t uni_times_lds_bytes(int32_t p_max, bool compositions)
 {
     if (p_max <= kUniSmallProcs) return static_cast<size_t>(compositions ? SmallRings<true>::kRuns : SmallRings<false>::kRuns) * 10;
     return static_cast<size_t>(large_rings(p_max).runs) * kRunBytes;
 }
-// runs of a ring in the workspace
-int32_t uni_times_slot_runs(int32_t p_max) { return p_max + 3 + kMaxChunk; }
-size_t uni_times_slot_bytes(int32_t p_cap) { return static_cast<size_t>(kWave) * static_cast<size_t>(p_cap) * kRunBytes; }
+// runs of a ring in the workspace: none for machines that never fill one in LDS
+int32_t uni_times_slot_runs(int32_t p_max)
+{
+    static_assert(SmallRings<false>::kRing <= SmallRings<true>::kRing, "the smallest ring in LDS");
+    const int32_t runs = p_max + 3 + kMaxChunk;
+    return runs <= SmallRings<false>::kRing ? 0 : (runs + 1) / 2 * 2;
+}
+size_t uni_times_slot_bytes(int32_t runs, bool small) { return static_cast<size_t>(kWave) * static_cast<size_t>(runs) * (small ? 10 : kRunBytes); }
 
 // v, or a value above every time of a schedule (those stay below 4e18 and 1e300: schedule_fits) if v is not there.  Only
 // the upper half is exchanged.
@@ -85,7 +90,7 @@ template <typename T> __device__ __forceinline__ T or_absent(bool there, T v)
 }
 
 // Runs in LDS by the byte address of their place.  kSmall: the value there, the count among the 16-bit ones behind all
-// values; otherwise both packed into 12 bytes.
+// values (in the workspace slot as well); otherwise both packed into 12 bytes.
 template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) T *lds_at(int32_t at)
 {
     return reinterpret_cast<__attribute__((address_space(3))) T *>(static_cast<uint32_t>(at));
@@ -122,11 +127,23 @@ template <int G, bool kSmall> __device__ __forceinline__ Ring lds_ring(int l, co
     r.end = r.base + runs * r.stride;
     return r;
 }
-__device__ __forceinline__ Ring slot_ring(int l, int32_t slot_p)
+template <bool kSmall> __device__ __forceinline__ Ring slot_ring(int l, int32_t slot_runs)
 {
+    constexpr int kBytes = kSmall ? 8 : kRunBytes;
     Ring r;
-    r.base = l * slot_p * kRunBytes; r.stride = kRunBytes; r.end = r.base + slot_p * kRunBytes;
+    r.base = l * slot_runs * kBytes; r.stride = kBytes; r.end = r.base + slot_runs * kBytes;
     return r;
+}
+// runs in the workspace slot; `counts`: where the 16-bit counts begin
+template <typename T, bool kSmall> __device__ __forceinline__ void slot_load(const char *slot, int32_t counts, int32_t at, T &v, int32_t &n)
+{
+    if (kSmall) { v = *reinterpret_cast<const T *>(slot + at); n = *reinterpret_cast<const uint16_t *>(slot + counts + (at >> 2)); }
+    else { const auto *e = reinterpret_cast<const Run<T> *>(slot + at); v = e->v; n = e->n; }
+}
+template <typename T, bool kSmall> __device__ __forceinline__ void slot_store(char *slot, int32_t counts, int32_t at, T v, int32_t n)
+{
+    if (kSmall) { *reinterpret_cast<T *>(slot + at) = v; *reinterpret_cast<uint16_t *>(slot + counts + (at >> 2)) = static_cast<uint16_t>(n); }
+    else { auto *e = reinterpret_cast<Run<T> *>(slot + at); e->v = v; e->n = n; }
 }
 __device__ __forceinline__ int32_t ring_next(const Ring &r, int32_t at)
 {
@@ -139,7 +156,7 @@ __device__ __forceinline__ int32_t ring_next(const Ring &r, int32_t at)
 template <typename T, int G, bool kComp, bool kSmall>
 __device__ __forceinline__ void uni_times_body(const RingShape &shape, const ConfigArrays &cfg, int32_t p_max, int32_t q_max,
                                                int model, const TimesOut &times, PlanHeader *plan, const int32_t *order, int cls,
-                                               int part, char *slot, int32_t slot_p, bool help = false)
+                                               int part, char *slot, int32_t slot_runs, bool help = false)
 {
     constexpr int kGroups = kWave / G, kSmallRuns = kSmall ? SmallRings<kComp>::kRuns : 0;
     // a new configuration is fetched (a path every lane waits for) when this many groups have nothing to do
@@ -151,6 +168,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
     const uint64_t gmask = (G == 64 ? ~UINT64_C(0) : ((UINT64_C(1) << G) - 1)) << gbase;
     // part of the class this pass works on: all of it, its giant configurations only, or the rest after those
     const int set = cls >= kLargeClass ? 1 : 0;
+    const int32_t counts = kWave * 8 * slot_runs;                     // kSmall: where they begin in the slot
     int32_t count = plan->class_count[cls], begin = plan->class_begin[cls];
     unsigned long long *tickets = &plan->ticket[cls];
     if (part == kGiantPart) { count = plan->giant_count[set]; tickets = &plan->ticket_giant[set]; }
@@ -184,8 +202,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
 
     auto put = [&](auto to_slot, int32_t at, T v, int n) {
         if (decltype(to_slot)::value) {
-            Run<T> *e = reinterpret_cast<Run<T> *>(slot + at);
-            e->v = v; e->n = n;
+            slot_store<T, kSmall>(slot, counts, at, v, n);
         } else {
             lds_store<T, kSmallRuns>(at, v, n);
         }
@@ -279,8 +296,8 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
                     int na, nb;
                     if (kSlots && in_slot) {
                         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");      // stores of earlier steps have landed
-                        const Run<T> *ea = reinterpret_cast<const Run<T> *>(slot + aat), *eb = reinterpret_cast<const Run<T> *>(slot + bat);
-                        va = ea->v; na = ea->n; vb = eb->v; nb = eb->n;
+                        slot_load<T, kSmall>(slot, counts, aat, va, na);
+                        slot_load<T, kSmall>(slot, counts, bat, vb, nb);
                     } else {
                         lds_load<T, kSmallRuns>(aat, va, na);
                         lds_load<T, kSmallRuns>(bat, vb, nb);
@@ -338,7 +355,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
         if (ballot64(stuck) != 0) {
             PRS_KEEP_BRANCH();
             if (stuck) {
-                if (in_slot) {                                              // cannot happen (see above): give it up rather than wait for ever
+                if (in_slot || slot_runs == 0) {                            // cannot happen (see above): give it up rather than wait for ever
                     if (gl == 0) {
                         if (times.cfg_status) times.cfg_status[ci] = PRS_CFG_STALLED;
                         if (times.greedy) static_cast<T *>(times.greedy)[ci] = CostTraits<T>::bad();
@@ -346,7 +363,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
                     have = active = false; left = 0;
                 } else {
                     in_slot = true;
-                    own = slot_ring(lane, slot_p); in = slot_ring(prod, slot_p);
+                    own = slot_ring<kSmall>(lane, slot_runs); in = slot_ring<kSmall>(prod, slot_runs);
                     start_configuration(BoolConst<true>());
                 }
             }
@@ -360,33 +377,33 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
 template <typename T, bool kComp, bool kSmall>
 __global__ __launch_bounds__(kWave) void uni_times_kernel(RingShape shape, ConfigArrays cfg, int32_t p_max, int32_t q_max, int model,
                                                           TimesOut times, PlanHeader *plan, const int32_t *order, char *slots,
-                                                          size_t slot_bytes, int32_t slot_p, bool help)
+                                                          size_t slot_bytes, int32_t slot_runs, bool help)
 {
     // LDS is addressed from 0: the kernel has no other LDS than what the launch asks for
     if (kSmall) shape = RingShape{SmallRings<kComp>::kRuns, SmallRings<kComp>::kRing};
     constexpr int kFirst = kSmall ? 0 : kLargeClass;
     char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
-    uni_times_body<T, 64, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + kClasses - 1, kGiantPart, slot, slot_p);
+    uni_times_body<T, 64, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + kClasses - 1, kGiantPart, slot, slot_runs);
     __syncthreads();
-    uni_times_body<T, 32, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + kClasses - 1, kRestPart, slot, slot_p);
+    uni_times_body<T, 32, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + kClasses - 1, kRestPart, slot, slot_runs);
     __syncthreads();
-    uni_times_body<T, 16, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 4, kWholeClass, slot, slot_p);
+    uni_times_body<T, 16, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 4, kWholeClass, slot, slot_runs);
     __syncthreads();
-    uni_times_body<T, 8, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 3, kWholeClass, slot, slot_p);
+    uni_times_body<T, 8, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 3, kWholeClass, slot, slot_runs);
     __syncthreads();
-    uni_times_body<T, 4, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 2, kWholeClass, slot, slot_p);
+    uni_times_body<T, 4, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 2, kWholeClass, slot, slot_runs);
     __syncthreads();
-    uni_times_body<T, 2, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 1, kWholeClass, slot, slot_p);
+    uni_times_body<T, 2, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 1, kWholeClass, slot, slot_runs);
     __syncthreads();
-    uni_times_body<T, 1, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 0, kWholeClass, slot, slot_p);
+    uni_times_body<T, 1, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kFirst + 0, kWholeClass, slot, slot_runs);
     if (!kSmall && help) {
         // while the last of the large machines run, wavefronts that have none begin with the heavy small ones
         __syncthreads();
-        uni_times_body<T, 64, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kGiantPart, slot, slot_p, true);
+        uni_times_body<T, 64, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kGiantPart, slot, slot_runs, true);
         __syncthreads();
-        uni_times_body<T, 32, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kRestPart, slot, slot_p, true);
+        uni_times_body<T, 32, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, kClasses - 1, kRestPart, slot, slot_runs, true);
         __syncthreads();
-        uni_times_body<T, 16, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 4, kWholeClass, slot, slot_p, true);
+        uni_times_body<T, 16, kComp, kSmall>(shape, cfg, p_max, q_max, model, times, plan, order, 4, kWholeClass, slot, slot_runs, true);
     }
 }
 

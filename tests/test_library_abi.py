@@ -43,6 +43,21 @@ def test_workspace_sizes_are_monotone_and_bounded():
     assert w(u, prs.PRS_UNI, 0, 986, 1024, 25) == 0 and w(u, prs.PRS_UNI, 0, 1 << 20, 1024, 24) == 0
 
 
+def test_workspace_of_uni_greedy_times_grows_with_its_bounds():
+    """A caller that allocates for its largest batch and its largest machine can make every smaller call: around the sizes at which
+    rings and wavefronts per CU change, and where the number of resident wavefronts is capped."""
+    bounds = [2, 23, 24, 64, 511, 1024, 1025, 2048, 8192, 8193, 20000, 65536, 65537, 87381, 87382, 200000, 1 << 20]
+    for call in (prs.PRS_CALL_SIMULATE, prs.PRS_CALL_SEARCH, prs.PRS_CALL_UNEQUAL):
+        sizes = {}
+        for n in (1, 255, 256, 1280, 1281, 100000):
+            q = 10 if call == prs.PRS_CALL_UNEQUAL else 512
+            sizes[n] = [prs.prs_workspace_bytes(call, prs.PRS_UNI, prs.PRS_COST_F64, n, p, q) for p in bounds]
+            assert sizes[n] == sorted(sizes[n]), (call, n)
+        assert [list(c) for c in zip(*sizes.values())] == [sorted(c) for c in zip(*sizes.values())], call
+    # one machine needs the rings of one wavefront
+    assert prs.prs_workspace_bytes(prs.PRS_CALL_SIMULATE, prs.PRS_UNI, prs.PRS_COST_F64, 1, 256, 64) < 1 << 20
+
+
 def test_calls_reject_bad_arguments_before_touching_the_gpu():
     import ctypes as C
     lib = prs.load_library()
