@@ -162,10 +162,10 @@ def test_uni_every_group_size(prs, grouping):
 @pytest.mark.parametrize("p_max", [1024, 8192, 40000])
 def test_uni_times_rings_of_runs(prs, p_max):
     """Completion times of a batch large enough that every group size from 1 to 64 lanes is used, with pair counts on
-    both sides of the limits between them, for each size of the LDS rings.  Three machines keep more receivers
-    combining at different times than a ring holds (tcomp = 1000 tcomm) and start again in the workspace.  Integer
+    both sides of the limits between them, for each bound on the machines that has a ring size of its own (the machines
+    themselves have the rings of up to 1024 processors).  Three of them combine for long (tcomp = 1000 tcomm).  Integer
     costs, fp64 costs and fp64 costs whose sums collide in rounding, bit for bit."""
-    shapes = [(2, 1), (2, 300), (3, 128), (17, 16), (18, 16), (257, 1), (65, 32), (65, 33), (33, 64), (129, 64), (129, 65), (513, 16),
+    shapes = [(1024, 512), (1024, 513), (1000, 525), (2, 1), (2, 300), (3, 128), (17, 16), (18, 16), (257, 1), (65, 32), (65, 33), (33, 64), (129, 64), (129, 65), (513, 16),
               (257, 128), (257, 129), (1024, 33), (1024, 128), (1024, 129), (700, 400), (1024, 512), (1000, 520), (31, 9), (64, 5)]
     rng = np.random.default_rng(31)
     p = np.array([a for a, _ in shapes] + [300, 1024, 90], np.int32)
@@ -186,7 +186,7 @@ def test_uni_times_rings_of_runs(prs, p_max):
                                            10.0 ** rng.uniform(-11, -9, n), "f64")
         else:
             host = prs_inputs.SweepConfigs(p, q, m, np.full(n, 1.0), np.full(n, 0.0), np.full(n, 2.0 ** -52), "f64")
-        got = prs.simulate_completion_batch(prs.DeviceConfigs.from_host(host.take(every)), 0, p_max, 520)
+        got = prs.simulate_completion_batch(prs.DeviceConfigs.from_host(host.take(every)), 0, p_max, 525)
         _sync()
         ref = np.array([O.uni_greedy_time(int(p[i]), O.equi_sizes(int(m[i]), int(q[i])), host.alpha[i].item(), host.beta[i].item(),
                                           host.gamma[i].item(), host.cost) for i in range(n)])
@@ -244,6 +244,61 @@ def test_uni_times_small_and_large_machines_in_one_batch(prs, p_max, n, cost):
     want[[7, 11, 13]] = 2, 1, 2
     assert np.array_equal(_np(got["cfg_status"]), want)
     assert np.array_equal(_np(got["greedy"])[want == 0], ref[every][want == 0])
+
+
+def _with_marked_workspace(call, size, front):
+    """Runs call(workspace) on a workspace full of 0xA5 and says whether it wrote past its first `front` bytes: the header and
+    the lists of the plan lie there, behind them only the rings of configurations that start again."""
+    import torch
+    ws = torch.full((size + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    got = call(ws)
+    _sync()
+    return got, bool((ws[front:] != 0xA5).any())
+
+
+# p, q, p_max of machines that fill a ring in LDS (with one lane nearly every machine of that size does)
+_RESTARTS = {"1 lane": [(64, 80, 1024), (300, 300, 1024), (1100, 200, 3000), (3000, 60, 9000)],
+             "4 or 8 lanes": [(300, 300, 1024), (700, 300, 1024), (2000, 200, 3000), (1100, 200, 3000)],
+             "16 lanes": [], "32 lanes": [], "64 lanes": []}
+# on 16 lanes and more only sums that differ in their last bit leave runs enough
+_RESTARTS_WIDE = [(1015, 43, 11409079, 9.347070181080557e-06, 6.796609818137614e-10, 2.9341085068449743e-11),
+                  (1016, 66, 13660192, 1.1859514639217455e-06, 4.4664142177029213e-10, 4.022372924305566e-09),
+                  (1011, 85, 6890702, 6.74489421848018e-05, 2.179908004162555e-09, 1.1607586681795065e-11),
+                  (1021, 56, 6568825, 2.9742648979094657e-06, 9.4635633699965e-09, 6.427772534613714e-08)]
+
+
+@pytest.mark.parametrize("grouping", list(_RESTARTS))
+def test_uni_times_start_again_in_the_workspace(prs, grouping):
+    """Configurations whose runs fill a ring in LDS, for every group size and both layouts of the rings: they are seen to write to
+    the rings in the workspace, and their times are the oracle's bit for bit.  Large machines on 16 lanes and more, which
+    never did with equal segments, do so with the segmentations of a short message."""
+    tuning = _GROUPINGS[grouping]
+    cases = [(p, q, q, 0.0, 1.37e-5, 3.1e-6, p_max) for p, q, p_max in _RESTARTS[grouping]]
+    if not cases:
+        cases = [c + (1024,) for c in _RESTARTS_WIDE]
+    filled = {}
+    for p, q, m, al, be, ga, p_max in cases:
+        host = prs_inputs.SweepConfigs(np.array([p], np.int32), np.array([q], np.int32), np.array([m]), np.array([al]), np.array([be]),
+                                       np.array([ga]), "f64")
+        dev = prs.DeviceConfigs.from_host(host)
+        size = prs.prs_workspace_bytes(prs.PRS_CALL_SIMULATE, 0, prs.PRS_COST_F64, 1, p_max, 300)
+        got, wrote = _with_marked_workspace(lambda ws: prs.simulate_completion_batch(dev, 0, p_max, 300, workspace=ws, tuning=tuning), size, 8192)
+        assert _np(got["cfg_status"])[0] == 0 and _np(got["greedy"])[0] == O.simulate_batch(host, 0).T_greedy[0], (p, q)
+        filled[p_max > 1024] = filled.get(p_max > 1024, False) or wrote
+    assert all(filled.values()), filled
+    for p in (700, 1500):
+        m, n = 10, 2
+        al, ga = np.array([2.4150087712361406, 1.6144930544158296]), np.array([4.129348903019313, 0.4858942275222792])
+        host = prs_inputs.SweepConfigs(np.full(n, p, np.int32), np.ones(n, np.int32), np.full(n, m, np.int64), al, np.ones(n), ga, "f64")
+        dev = prs.DeviceConfigs.from_host(host)
+        size = prs.prs_workspace_bytes(prs.PRS_CALL_UNEQUAL, 0, prs.PRS_COST_F64, n, p, m)
+        got, wrote = _with_marked_workspace(lambda ws: prs.unequal_segmentation_batch(dev, p, m, workspace=ws, tuning=tuning), size,
+                                            20 * (n << (m - 1)) + 8192)
+        T = _np(got["T_all"]).reshape(n, -1)
+        for i in range(n):
+            ref = [O.uni_greedy_time(p, sizes, al[i].item(), 1.0, ga[i].item(), "f64") for sizes in O.compositions(m)]
+            assert np.array_equal(T[i], np.array(ref)), i
+        assert wrote, p
 
 
 def test_uni_times_a_block_per_configuration(prs):
