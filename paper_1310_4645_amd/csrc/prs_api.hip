@@ -75,7 +75,7 @@ hipError_t launch_offsets(const OffsetsLaunch &L)
 //                                     q <= 1023; the general kernel for the rest and for reruns.
 enum ClassKind { kUniTimes, kUniSched, kBiGroup, kBiGeneral, kBiBlock, kUniWide };
 constexpr size_t kLdsPerCU = 160 * 1024, kLdsPerBlockMax = 64 * 1024, kBitmapLdsMax = 24 * 1024;
-constexpr int kCUs = 256, kMaxBlocksPerCU = 24, kGlobalClassGrid = 1024;
+constexpr int kCUs = 256, kSIMDs = 4 * kCUs, kMaxBlocksPerCU = 24, kGlobalClassGrid = 1024;
 // LDS is given out in units of 1280 bytes: six one-wavefront blocks of 26,880 bytes run on a CU side by side, five of 27,300.
 constexpr size_t kLdsUnit = 1280;
 static int64_t blocks_per_cu(size_t lds_bytes)
@@ -437,9 +437,17 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
             G.parts.rows = reinterpret_cast<uint64_t *>(ws + c0.slot_offset);
             G.parts.rows_per_block = c0.slot_bytes / 8;
             // Configurations that share a wavefront wait for each other's paths: a batch that leaves wavefronts without one
-            // spreads out (960 machines of 2 to 16 processors, both port models: 488 -> 267 us; a few hundred machines of up to a
-            // thousand processors 1.5 to 2 times faster, handfuls of large ones up to 30 times).
-            G.parts.per_wave = static_cast<int>(n > static_cast<int64_t>(total) * kWave ? kWave : (n + total - 1) / total);
+            // spreads out, unless all of it are single segments (960 machines of 2 to 16 processors, both port models: 488 ->
+            // 255 us; 500 machines of 2 to 1024 processors and up to 512 segments 18.5 -> 10.7 ms, of 2 to 64 processors
+            // 16.8 -> 7.1; 500 equal ones of 1024 and 512 10.4 -> 11.5, of 40 and 8 with schedules 1.25 -> 0.52).
+            // With 64 or 32 groups to a wavefront that ends at one wavefront per SIMD, more only share its cycles (20,000
+            // machines of 60 to 64 processors and 500 to 512 segments: 13.4 ms on 313 wavefronts, 8.8 on 512 or 1024, 22 on 2048),
+            // and at one for two SIMDs with more than four configurations each (10,000 equal ones of 12 and 512: 6.1 ms on
+            // 157, 6.0 on 512, 6.9 on 1024; 3000 of them 6.0 on 47, 6.6 on 512, 5.9 on 1024).  With at most 16 groups it goes
+            // on to all resident ones (3000 machines of 250 to 256 processors: 20.4 -> 13.7 ms, 15.4 on 1024).
+            const int waves = n <= 4 * kSIMDs ? kSIMDs : kSIMDs / 2, spread[2] = {total < waves ? total : waves, total};
+            for (int k = 0; k < 2; ++k)
+                G.parts.per_wave[k] = static_cast<int>(n > static_cast<int64_t>(spread[k]) * kWave ? kWave : (n + spread[k] - 1) / spread[k]);
             G.stream = st;
             if (launch_bi_group(G) != hipSuccess) return PRS_EDEVICE;
         } else if (general(c, P.order, k) != hipSuccess) {

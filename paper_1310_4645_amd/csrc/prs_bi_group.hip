@@ -149,9 +149,9 @@ __device__ __forceinline__ void bi_group_body(char *lds_raw, int block, const Co
     const T kInf = CostTraits<T>::inf();
 
     // ---- per-group state (identical in all lanes of a group unless noted)
-    int iter = 0;               // of the wavefront
+    int idle = 0;               // of the wavefront: what waiting for the clock path has cost since it ran last
     bool have = false;          // a configuration is loaded
-    bool exhausted = gw >= per_wave;   // no (more) tickets
+    bool exhausted = plan->several != 0 && gw >= per_wave;   // no (more) tickets
     int64_t ci = 0;             // configuration index
     Config<T> c;
     int W = 0;
@@ -221,14 +221,25 @@ __device__ __forceinline__ void bi_group_body(char *lds_raw, int block, const Co
         const bool run = have && !finished;
 
         // ---------------------------------------------------------------- advance time (Algorithm 2: t <- next port release)
-        // The clock path costs more than twice a visit and every lane of the wavefront pays for it, so the configurations that
-        // need it wait until all do, at most 16 iterations (one of 64 with many visits left would hold up the others).
-        // 100,000-configuration sweep, completion times / schedules: at once 24.4 / 43.5 ms; every 2nd iteration 21.2 / 40.7,
-        // 4th 18.7 / 32.4, 8th 19.2 / 31.2, 12th 22.7 / 41.3, 16th 16.3 / 27.5, 20th 17.2 / 28.9, 32nd 16.3 / 28.0, only when all do
-        // 18.1 / 33.0.
-        const uint64_t on = ballot64(run), wait = ballot64(run && need_event);
-        const bool due = (++iter & 15) == 0;
-        if (run && need_event && (wait == on || due)) {
+        // The clock path costs several visits and every lane of the wavefront pays for it, so the configurations that need it
+        // wait until all do, but not for one of 64 with many visits left.
+        // With 64 or 32 groups until the lanes that waited, summed over the iterations, pass 60 times those that do not need it
+        // (20 or 200 times: within a tenth): 60,000 machines of 60 to 64 processors and 500 to 512 segments 14.9 ms at once,
+        // 8.9 so, 17 with every 16th iteration; 100,000 of 2 to 64 and 1 to 16 1.87 at once, 1.22 so, 1.31 with 20 times.
+        // With fewer groups until every 16th iteration: 10,000 machines of 1000 to 1024 processors and 60 to 64 segments 9.8 ms
+        // at once, 7.8 so, 9.0 with the sum; 20,000 of 256 and 512 25.6, 20.0, 28.7.  Why 16 serves these best is not
+        // known (100,000 machines of 2 to 1024 processors: every 8th 19.2 ms, 12th 22.7, 16th 16.3, 20th 17.2, at once 24.4).
+        const uint64_t going = ballot64(run && !need_event);
+        bool due;
+        if (LPC <= 2) {
+            idle += __builtin_popcountll(ballot64(run && need_event));
+            due = idle >= 60 * __builtin_popcountll(going);
+            idle = due ? 0 : idle;
+        } else {
+            ++idle;                                                   // counts iterations here
+            due = going == 0 || (idle & 15) == 0;
+        }
+        if (run && need_event && due) {
             T tn = t;
             bool lateOnly = false;
             if (events > 0) {
@@ -473,23 +484,23 @@ __global__ __launch_bounds__(kWave) void bi_group_kernel(ConfigArrays cfg, int32
         if (!parts.on[cls]) continue;
         switch (cls) {
         case 4:
-            bi_group_body<T, kSched, 16>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 4, retry, rows, parts.per_wave,
+            bi_group_body<T, kSched, 16>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 4, retry, rows, parts.per_wave[1],
                                          parts.rows_per_group[4], parts.list_entries[4]);
             break;
         case 3:
-            bi_group_body<T, kSched, 8>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 3, retry, rows, parts.per_wave,
+            bi_group_body<T, kSched, 8>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 3, retry, rows, parts.per_wave[1],
                                         parts.rows_per_group[3], parts.list_entries[3]);
             break;
         case 2:
-            bi_group_body<T, kSched, 4>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 2, retry, rows, parts.per_wave,
+            bi_group_body<T, kSched, 4>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 2, retry, rows, parts.per_wave[1],
                                         parts.rows_per_group[2], parts.list_entries[2]);
             break;
         case 1:
-            bi_group_body<T, kSched, 2>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 1, retry, rows, parts.per_wave,
+            bi_group_body<T, kSched, 2>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 1, retry, rows, parts.per_wave[0],
                                         parts.rows_per_group[1], parts.list_entries[1]);
             break;
         default:
-            bi_group_body<T, kSched, 1>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 0, retry, rows, parts.per_wave,
+            bi_group_body<T, kSched, 1>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 0, retry, rows, parts.per_wave[0],
                                         parts.rows_per_group[0], parts.list_entries[0]);
             break;
         }

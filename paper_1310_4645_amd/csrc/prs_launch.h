@@ -66,7 +66,7 @@ struct BiGroupParts {
     uint64_t *rows;               // sent-bit rows: one slot of rows_per_block words per block
     size_t rows_per_block;
     size_t rows_per_group[kBiGroupSizes];
-    int per_wave;                 // configurations a wavefront runs at once, at most
+    int per_wave[2];              // configurations a wavefront runs at once, at most: on 1 or 2 lanes each, and on more
     int list_entries[kBiGroupSizes];          // entries of the list of running transfers a configuration may use (<= the LDS layout's)
 };
 struct BiGroupLaunch {

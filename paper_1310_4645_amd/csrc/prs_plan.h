@@ -21,6 +21,7 @@ struct PlanHeader {
     unsigned long long ticket_giant[2];
     int32_t giant_count[2];
     int32_t large_left;                           // large machines that are not done
+    int32_t several;                              // bi-greedy: 1 if some configuration requests more than one segment
     int32_t class_begin[kPlanClasses];
     int32_t class_count[kPlanClasses];
     int32_t place[kPlanClasses * kWorkBuckets];   // configurations per bucket, then where the next one of the bucket goes

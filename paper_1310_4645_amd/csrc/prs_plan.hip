@@ -31,6 +31,7 @@ __global__ void plan_clear(PlanHeader *h)
     const int i = threadIdx.x;
     if (i < kPlanClasses) { h->ticket[i] = 0ULL; h->class_begin[i] = 0; h->class_count[i] = 0; }
     if (i < 2) { h->giant_count[i] = 0; h->ticket_giant[i] = 0ULL; }
+    if (i == 0) { h->large_left = 0; h->several = 0; }
     for (int k = i; k < kPlanClasses * kWorkBuckets; k += blockDim.x) h->place[k] = 0;
 }
 
@@ -44,12 +45,18 @@ __global__ __launch_bounds__(kPlanThreads) void plan_hist(ConfigArrays cfg, int6
                                                           int bins, PlanHeader *h)
 {
     __shared__ int32_t local[kPlanBins];
+    __shared__ int32_t several;
     const int tid = static_cast<int>(threadIdx.x);
     for (int k = tid; k < bins; k += kPlanThreads) local[k] = 0;
+    if (tid == 0) several = 0;
     __syncthreads();
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kPlanThreads + tid;
-    if (i < n) atomicAdd(&local[plan_bucket<T>(cfg, i, p_max, q_max, lim)], 1);
+    if (i < n) {
+        atomicAdd(&local[plan_bucket<T>(cfg, i, p_max, q_max, lim)], 1);
+        if (!lim.by_work && cfg.q_req[i] > 1) several = 1;            // the same value whoever writes
+    }
     __syncthreads();
+    if (tid == 0 && several != 0) h->several = 1;
     for (int k = tid; k < bins; k += kPlanThreads)
         if (local[k] != 0) atomicAdd(&h->place[k], local[k]);
 }

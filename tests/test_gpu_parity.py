@@ -482,6 +482,25 @@ def test_bi_configurations_side_by_side_in_a_wavefront(prs, copies, entries):
     assert np.all(_np(got["cfg_status"]) == 0)
 
 
+@pytest.mark.parametrize("copies", [1, 40, 700])
+def test_bi_single_segments_share_a_wavefront(prs, copies):
+    """A batch without a second segment does not spread over the wavefronts and its configurations wait for no clock; one
+    configuration with two segments at its end makes it an ordinary batch.  Both give the oracle's times."""
+    rng = np.random.default_rng(11)
+    p = np.concatenate([rng.integers(2, 65, 50), rng.integers(65, 257, 30), rng.integers(257, 1025, 20)]).astype(np.int32)
+    host = prs_inputs.SweepConfigs(p, np.ones(100, np.int32), rng.integers(1, 50, 100), rng.integers(0, 12, 100).astype(np.int64),
+                                   rng.integers(1, 4, 100).astype(np.int64), rng.integers(0, 4, 100).astype(np.int64), "i64")
+    ref = O.simulate_batch(host, 1).T_greedy
+    many = host.take(np.tile(np.arange(100), copies))
+    for q_last in (1, 2):
+        many.q_req[-1], many.m[-1] = q_last, 64
+        got = prs.simulate_completion_batch(prs.DeviceConfigs.from_host(many), 1, 1024, 2)
+        _sync()
+        last = O.simulate_batch(many, 1, index=[len(many) - 1]).T_greedy
+        assert np.array_equal(_np(got["greedy"])[:-1], np.tile(ref, copies)[:-1]) and _np(got["greedy"])[-1] == last[0]
+        assert np.all(_np(got["cfg_status"]) == 0)
+
+
 def test_costs_too_large_for_the_cost_type_are_refused(prs):
     """A configuration whose schedule would pass the range of the cost type (Table I's pipeline time, which
     bounds every greedy time) is reported as a bad parameter instead of being run: with doubles the sums would
