@@ -3,8 +3,8 @@
 //
 // Every list of Algorithm 2 is a bit set over the processors, list lengths are population counts, "first k entries" a
 // rank select inside a word, list positions prefix sums.  run_bi_wide keeps the sets in registers and the running transfers in a
-// list; run_bi_block, which keeps times per processor in the workspace slot, does what does not fit there: more than 65536
-// processors, or more than 64 transfers running at once.
+// list; run_bi_block, which keeps times per processor in the workspace slot, does what does not fit there: more than 64
+// transfers running at once.
 //
 // What bounds it: the chain of visits of the longest configuration (about 33,000 on 65536 processors and 1000 segments), each
 // one or two sums over the block.  64 machines of 1024 to 65536 processors, completion times: 263 ms with times per processor
@@ -147,7 +147,7 @@ __device__ T run_bi_block(const Config<T> &c, char *lds, char *slot, const Block
     const int64_t max_events = 4 * static_cast<int64_t>(p) * q + 16;
     for (int64_t ev = 0;; ++ev) {
         if (ev > max_events) { *status = PRS_CFG_STALLED; return CostTraits<T>::bad(); }
-        // ---- port and computation state of every processor at time t, as bit sets (wavefront v takes words v, v+16, ...)
+        // ---- port and computation state of every processor at time t, as bit sets (wavefront v takes words v, v+8, ...)
         T minOld = kInf, minLate = kInf;             // next time a port frees / a processor may take in the last segment
         int cs = 0, cr = 0, cu = 0;                  // free send ports, free receive ports, processors with either
         int csAll = 0;                               // free send ports of processors with something left to send
@@ -347,7 +347,9 @@ __device__ T run_bi_block(const Config<T> &c, char *lds, char *slot, const Block
 
 // ---- the usual path: sets in registers, running transfers as a list --------------------------------------------------
 //
-// Thread i of the block owns the words i kw .. i kw + kw - 1 of every bit set, kw = 1 or 2, and keeps them in registers.
+// Thread i of the block owns the words i kw .. i kw + kw - 1 of every bit set, kw = 1, 2 or 3, and keeps them in registers.  The
+// kernel for three words serves batches whose bound passes 65536 processors (16 machines of 66,000, 8 segments: 14.6 ms on
+// run_bi_block, 2.1 so; its registers cost machines of two words a sixth, 20 segments on 16 of 40,000 3.7 -> 4.3 ms).
 // All pairs of a visit (time t, segment j) have the same end of send and end of combine, so the ports and computations
 // of Algorithm 2 are a list of groups (end of send, end of combine, set of senders, set of receivers): lane e of EVERY
 // wavefront holds the two times of entry e, the sets lie in the workspace slot, word by word written and read by the
@@ -356,7 +358,7 @@ __device__ T run_bi_block(const Config<T> &c, char *lds, char *slot, const Block
 // wavefront) and a second one only if a list has to be cut; a sum is one barrier, with two buffers in turn: a wavefront
 // that writes a buffer again has passed the barrier of the sum in between, which nobody reaches before it has read the first.
 // Processors that have sent everything stay in the sets: they hold no segment, so they never pair.
-constexpr int kWideWords = 65536 / 64 / kBlockThreads;     // words per thread on the largest machine of this path
+constexpr int kWideWords = 65536 / 64 / kBlockThreads;     // words per thread on machines of up to 65536 processors
 constexpr int kWideProcs = kBlockThreads * kWideWords * 64;
 constexpr int kWideEntries = kWave;                        // running transfers, one per lane
 
@@ -404,11 +406,10 @@ template <typename T> __device__ __forceinline__ T wave_min_dpp(T v)
 
 // Returns false if the list of running transfers would need more than `entries` entries: nothing of the configuration is
 // final then, and run_bi_block does it from the start.
-template <typename T, bool kSched>
+template <typename T, bool kSched, int K>
 __device__ bool run_bi_wide(const Config<T> &c, int4 *red, uint64_t *rows, uint64_t *sets, int entries, const SchedOut &sched,
                             int64_t out_base, T *result, int32_t *status)
 {
-    constexpr int K = kWideWords;
     const int tid = static_cast<int>(threadIdx.x), lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int p = c.p, q = c.q;
@@ -674,7 +675,7 @@ __device__ bool run_bi_wide(const Config<T> &c, int4 *red, uint64_t *rows, uint6
     }
 }
 
-template <typename T, bool kSched>
+template <typename T, bool kSched, int K>
 __global__ __launch_bounds__(kBlockThreads) void bi_block_kernel(ConfigArrays cfg, int32_t p_max, int32_t q_max, int model,
                                                                  TimesOut times, SchedOut sched, PlanHeader *plan,
                                                                  const int32_t *order, int cls, int entries, int32_t state_p,
@@ -706,9 +707,9 @@ __global__ __launch_bounds__(kBlockThreads) void bi_block_kernel(ConfigArrays cf
         T result = CostTraits<T>::bad();
         if (status == PRS_CFG_OK) {
             bool done = false;
-            if (c.p <= kWideProcs)
-                done = run_bi_wide<T, kSched>(c, red, reinterpret_cast<uint64_t *>(slot + sl.sent), reinterpret_cast<uint64_t *>(slot + sl.sets),
-                                              entries, sched, base, &result, &status);
+            if (c.p <= kBlockThreads * K * 64)                             // always, where this kernel is launched
+                done = run_bi_wide<T, kSched, K>(c, red, reinterpret_cast<uint64_t *>(slot + sl.sent), reinterpret_cast<uint64_t *>(slot + sl.sets),
+                                                 entries, sched, base, &result, &status);
             if (!done) {
                 __syncthreads();
                 result = run_bi_block<T, kSched>(c, lds_raw, slot, sl, Wc, sched, base, &status);
@@ -725,12 +726,18 @@ __global__ __launch_bounds__(kBlockThreads) void bi_block_kernel(ConfigArrays cf
     }
 }
 
+template <typename T, bool kSched, int K>
+static hipError_t launch_bi_block_as(const BiLaunch &L)
+{
+    hipLaunchKernelGGL((bi_block_kernel<T, kSched, K>), dim3(L.grid), dim3(kBlockThreads), L.lds_bytes, L.stream, L.cfg, L.p_max,
+                       L.q_max, L.model, L.times, L.sched, L.plan, L.order, L.cls, L.list_entries, L.slot_p, L.slot_q, L.slots, L.slot_bytes);
+    return hipGetLastError();
+}
 template <typename T, bool kSched>
 static hipError_t launch_bi_block_t(const BiLaunch &L)
 {
-    hipLaunchKernelGGL((bi_block_kernel<T, kSched>), dim3(L.grid), dim3(kBlockThreads), L.lds_bytes, L.stream, L.cfg, L.p_max,
-                       L.q_max, L.model, L.times, L.sched, L.plan, L.order, L.cls, L.list_entries, L.slot_p, L.slot_q, L.slots, L.slot_bytes);
-    return hipGetLastError();
+    if (L.p_max > kBlockThreads * 3 * 64) return hipErrorInvalidValue;     // no batch of this kernel
+    return L.p_max > kWideProcs ? launch_bi_block_as<T, kSched, 3>(L) : launch_bi_block_as<T, kSched, kWideWords>(L);
 }
 
 hipError_t launch_bi_block(const BiLaunch &L)

@@ -684,7 +684,7 @@ def test_schedules_beyond_1024_processors(prs, model):
 @pytest.mark.parametrize("cost", ["i64", "f64"])
 def test_bi_schedules_around_the_words_per_thread(prs, cost, entries):
     """Bi-greedy on a block of 512 threads: first and last machine with one and with two words per thread, the first one
-    beyond two, equal and smaller last segments, more segments than are in flight; with the list of running
+    with three, equal and smaller last segments, more segments than are in flight; with the list of running
     transfers cut to two entries every configuration starts again on the path that keeps times per processor."""
     p = np.array([1025, 1088, 4097, 32767, 32768, 32769, 65536, 65537, 1500, 2047], np.int32)
     q = np.array([40, 7, 9, 3, 4, 2, 3, 2, 33, 64], np.int32)
@@ -702,6 +702,22 @@ def test_bi_schedules_around_the_words_per_thread(prs, cost, entries):
     _sync()
     _check_times(got, O.simulate_batch(host, 1), exact=cost == "i64")
     _check_schedules(prs, host, 1, 65537, 64, tuning=tuning)
+
+
+@pytest.mark.parametrize("entries", [0, 2])
+def test_bi_three_words_per_thread(prs, entries):
+    """The block kernel for batches whose bound passes 65536 processors: the first and the last machine with three words per
+    thread, and machines with one and two in the same batch; with the list of running transfers cut to two entries they
+    start again on the path that keeps times per processor."""
+    p = np.array([65537, 68800, 67001, 65536, 32769, 32768, 1025], np.int32)
+    q = np.array([3, 2, 4, 2, 3, 2, 30], np.int32)
+    m = q * np.array([5, 4, 9, 7, 3, 6, 11], np.int64) - np.array([1, 0, 8, 2, 0, 1, 10])
+    host = prs_inputs.SweepConfigs(p, q, m, np.array([3, 0, 7, 2, 1, 0, 5]), np.full(7, 2), np.array([1, 3, 0, 2, 4, 1, 2]), "i64")
+    tuning = {"bi_list_entries": entries} if entries else None
+    got = prs.simulate_completion_batch(prs.DeviceConfigs.from_host(host), 1, 68800, 30, tuning=tuning)
+    _sync()
+    _check_times(got, O.simulate_batch(host, 1), exact=True)
+    _check_schedules(prs, host, 1, 68800, 30, tuning=tuning)
 
 
 # --------------------------------------------------------------------------- best segmentation per algorithm
