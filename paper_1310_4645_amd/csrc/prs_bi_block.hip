@@ -21,7 +21,8 @@ constexpr int kBlockWaves = kBlockThreads / kWave;
 __host__ __device__ inline size_t bb_align(size_t v) { return (v + 255) / 256 * 256; }
 
 // workspace slot of a block: S, R, C1 (8 B per processor), flags and count of sent segments (4 B), the two pairing
-// lists, the per-segment counters, the sent bitmap [q][W]
+// lists, the per-segment counters, the sent bitmap [q][W].  The 64 pairs of sets of run_bi_wide (16 B per processor) lie where
+// run_bi_block, which begins from the start, keeps S, R and C1 (they fit from 126 processors on).
 struct BlockSlot { size_t S, R, C1, nsent, sendList, recvList, rem, sent, sets, total; };
 
 __host__ __device__ inline BlockSlot bi_block_slot(int32_t p_cap, int32_t q_cap)
@@ -29,6 +30,7 @@ __host__ __device__ inline BlockSlot bi_block_slot(int32_t p_cap, int32_t q_cap)
     BlockSlot L;
     const size_t p = static_cast<size_t>(p_cap), q = static_cast<size_t>(q_cap), W = (p + 63) / 64;
     size_t o = 0;
+    L.sets = o;
     L.S = o; o += bb_align(p * 8);
     L.R = o; o += bb_align(p * 8);
     L.C1 = o; o += bb_align(p * 8);
@@ -37,7 +39,6 @@ __host__ __device__ inline BlockSlot bi_block_slot(int32_t p_cap, int32_t q_cap)
     L.recvList = o; o += bb_align((p / 2 + 1) * 4);
     L.rem = o; o += bb_align(q * 4);
     L.sent = o; o += bb_align(W * q * 8);
-    L.sets = o; o += bb_align(W * 16 * kWave);
     L.total = o;
     return L;
 }

@@ -58,6 +58,13 @@ def test_workspace_of_uni_greedy_times_grows_with_its_bounds():
     assert prs.prs_workspace_bytes(prs.PRS_CALL_SIMULATE, prs.PRS_UNI, prs.PRS_COST_F64, 1, 256, 64) < 1 << 20
 
 
+def test_workspace_of_large_bi_greedy_machines():
+    """Blocks of thousands of processors: the sets of running transfers lie where the other path of the kernel keeps its times
+    (28 bytes per processor, the pairing lists, a bit per processor and segment; 500 blocks)."""
+    for call in (prs.PRS_CALL_SIMULATE, prs.PRS_CALL_SCHEDULE):
+        assert prs.prs_workspace_bytes(call, prs.PRS_BI, prs.PRS_COST_F64, 500, 65536, 1) <= 500 * (65536 * 33 + 4096) + (1 << 20)
+
+
 def test_calls_reject_bad_arguments_before_touching_the_gpu():
     import ctypes as C
     lib = prs.load_library()
