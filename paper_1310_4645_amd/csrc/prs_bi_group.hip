@@ -151,7 +151,7 @@ __device__ __forceinline__ void bi_group_body(char *lds_raw, int block, const Co
     // ---- per-group state (identical in all lanes of a group unless noted)
     int idle = 0;               // of the wavefront: what waiting for the clock path has cost since it ran last
     bool have = false;          // a configuration is loaded
-    bool exhausted = plan->several != 0 && gw >= per_wave;   // no (more) tickets
+    bool exhausted = gw >= per_wave;   // no (more) tickets
     int64_t ci = 0;             // configuration index
     Config<T> c;
     int W = 0;
@@ -468,6 +468,8 @@ __global__ __launch_bounds__(kWave) void bi_group_kernel(ConfigArrays cfg, int32
 {
     PRS_DYNAMIC_LDS(lds_raw);
     const int b = static_cast<int>(blockIdx.x);
+    // a batch of single segments does not spread over the wavefronts
+    const int pw0 = plan->several ? parts.per_wave[0] : kWave, pw1 = plan->several ? parts.per_wave[1] : kWave;
     uint64_t *rows = parts.rows + static_cast<size_t>(b) * parts.rows_per_block;
     int first = 0, upto = 0;
     for (int g = kBiGroupSizes - 1; g >= 0; --g) {
@@ -484,23 +486,23 @@ __global__ __launch_bounds__(kWave) void bi_group_kernel(ConfigArrays cfg, int32
         if (!parts.on[cls]) continue;
         switch (cls) {
         case 4:
-            bi_group_body<T, kSched, 16>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 4, retry, rows, parts.per_wave[1],
+            bi_group_body<T, kSched, 16>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 4, retry, rows, pw1,
                                          parts.rows_per_group[4], parts.list_entries[4]);
             break;
         case 3:
-            bi_group_body<T, kSched, 8>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 3, retry, rows, parts.per_wave[1],
+            bi_group_body<T, kSched, 8>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 3, retry, rows, pw1,
                                         parts.rows_per_group[3], parts.list_entries[3]);
             break;
         case 2:
-            bi_group_body<T, kSched, 4>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 2, retry, rows, parts.per_wave[1],
+            bi_group_body<T, kSched, 4>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 2, retry, rows, pw1,
                                         parts.rows_per_group[2], parts.list_entries[2]);
             break;
         case 1:
-            bi_group_body<T, kSched, 2>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 1, retry, rows, parts.per_wave[0],
+            bi_group_body<T, kSched, 2>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 1, retry, rows, pw0,
                                         parts.rows_per_group[1], parts.list_entries[1]);
             break;
         default:
-            bi_group_body<T, kSched, 1>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 0, retry, rows, parts.per_wave[0],
+            bi_group_body<T, kSched, 1>(lds_raw, 0, cfg, p_max, q_max, model, times, sched, plan, order, 0, retry, rows, pw0,
                                         parts.rows_per_group[0], parts.list_entries[0]);
             break;
         }
