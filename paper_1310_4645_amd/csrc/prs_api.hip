@@ -224,7 +224,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             // schedules: keeps every per-lane array 64-byte aligned; times: runs of a lane's ring
             c.p_cap = sched ? (p + 15) / 16 * 16 : uni_times_slot_runs(p);
             c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes(p, compositions);
-            c.slot_bytes = sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap, p <= kUniSmallProcs);
+            c.slot_bytes = sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap, compositions || p > kUniSmallProcs);
             int64_t g = blocks_per_cu(c.lds_bytes) * kCUs;
             if (!sched && g > n) g = n < 1 ? 1 : n;
             size_t bytes = static_cast<size_t>(g) * c.slot_bytes;

@@ -88,7 +88,7 @@ hipError_t launch_bi_group(const BiGroupLaunch &L);
 // uni-greedy: all classes of a batch in one launch
 size_t uni_times_lds_bytes(int32_t p_max, bool compositions);
 int32_t uni_times_slot_runs(int32_t p_max);
-size_t uni_times_slot_bytes(int32_t runs, bool small);
+size_t uni_times_slot_bytes(int32_t runs, bool packed);
 hipError_t launch_uni_times(const UniLaunch &L);
 size_t uni_sched_lds_bytes();
 size_t uni_sched_slot_bytes(int32_t p_cap);

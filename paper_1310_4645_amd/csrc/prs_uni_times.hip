@@ -75,7 +75,9 @@ int32_t uni_times_slot_runs(int32_t p_max)
     const int32_t runs = p_max + 3 + kMaxChunk;
     return runs <= SmallRings<false>::kRing ? 0 : (runs + 1) / 2 * 2;
 }
-size_t uni_times_slot_bytes(int32_t runs, bool small) { return static_cast<size_t>(kWave) * static_cast<size_t>(runs) * (small ? 10 : kRunBytes); }
+// Packed like the large rings for compositions as well, many of which start again (the two loads of a run whose count lies apart
+// cost 78 x 2048 of them 2.01 ms against 1.85); apart where few do and there are the most wavefronts.
+size_t uni_times_slot_bytes(int32_t runs, bool packed) { return static_cast<size_t>(kWave) * static_cast<size_t>(runs) * (packed ? kRunBytes : 10); }
 
 // v, or a value above every time of a schedule (those stay below 4e18 and 1e300: schedule_fits) if v is not there.  Only
 // the upper half is exchanged.
@@ -90,7 +92,7 @@ template <typename T> __device__ __forceinline__ T or_absent(bool there, T v)
 }
 
 // Runs in LDS by the byte address of their place.  kSmall: the value there, the count among the 16-bit ones behind all
-// values (in the workspace slot as well); otherwise both packed into 12 bytes.
+// values; otherwise both packed into 12 bytes.
 template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) T *lds_at(int32_t at)
 {
     return reinterpret_cast<__attribute__((address_space(3))) T *>(static_cast<uint32_t>(at));
@@ -127,22 +129,22 @@ template <int G, bool kSmall> __device__ __forceinline__ Ring lds_ring(int l, co
     r.end = r.base + runs * r.stride;
     return r;
 }
-template <bool kSmall> __device__ __forceinline__ Ring slot_ring(int l, int32_t slot_runs)
+template <bool kPacked> __device__ __forceinline__ Ring slot_ring(int l, int32_t slot_runs)
 {
-    constexpr int kBytes = kSmall ? 8 : kRunBytes;
+    constexpr int kBytes = kPacked ? kRunBytes : 8;
     Ring r;
     r.base = l * slot_runs * kBytes; r.stride = kBytes; r.end = r.base + slot_runs * kBytes;
     return r;
 }
-// runs in the workspace slot; `counts`: where the 16-bit counts begin
-template <typename T, bool kSmall> __device__ __forceinline__ void slot_load(const char *slot, int32_t counts, int32_t at, T &v, int32_t &n)
+// runs in the workspace slot, packed or with their 16-bit counts from `counts` on
+template <typename T, bool kPacked> __device__ __forceinline__ void slot_load(const char *slot, int32_t counts, int32_t at, T &v, int32_t &n)
 {
-    if (kSmall) { v = *reinterpret_cast<const T *>(slot + at); n = *reinterpret_cast<const uint16_t *>(slot + counts + (at >> 2)); }
+    if (!kPacked) { v = *reinterpret_cast<const T *>(slot + at); n = *reinterpret_cast<const uint16_t *>(slot + counts + (at >> 2)); }
     else { const auto *e = reinterpret_cast<const Run<T> *>(slot + at); v = e->v; n = e->n; }
 }
-template <typename T, bool kSmall> __device__ __forceinline__ void slot_store(char *slot, int32_t counts, int32_t at, T v, int32_t n)
+template <typename T, bool kPacked> __device__ __forceinline__ void slot_store(char *slot, int32_t counts, int32_t at, T v, int32_t n)
 {
-    if (kSmall) { *reinterpret_cast<T *>(slot + at) = v; *reinterpret_cast<uint16_t *>(slot + counts + (at >> 2)) = static_cast<uint16_t>(n); }
+    if (!kPacked) { *reinterpret_cast<T *>(slot + at) = v; *reinterpret_cast<uint16_t *>(slot + counts + (at >> 2)) = static_cast<uint16_t>(n); }
     else { auto *e = reinterpret_cast<Run<T> *>(slot + at); e->v = v; e->n = n; }
 }
 __device__ __forceinline__ int32_t ring_next(const Ring &r, int32_t at)
@@ -159,6 +161,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
                                                int part, char *slot, int32_t slot_runs, bool help = false)
 {
     constexpr int kGroups = kWave / G, kSmallRuns = kSmall ? SmallRings<kComp>::kRuns : 0;
+    constexpr bool kPacked = kComp || !kSmall;      // runs in the workspace slot
     // a new configuration is fetched (a path every lane waits for) when this many groups have nothing to do
     constexpr int kFetchGroups = kGroups >= 8 ? kGroups / 8 : 1;
     // steps between two looks for room in the ring and for the end of a segment (small groups have short segments)
@@ -168,7 +171,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
     const uint64_t gmask = (G == 64 ? ~UINT64_C(0) : ((UINT64_C(1) << G) - 1)) << gbase;
     // part of the class this pass works on: all of it, its giant configurations only, or the rest after those
     const int set = cls >= kLargeClass ? 1 : 0;
-    const int32_t counts = kWave * 8 * slot_runs;                     // kSmall: where they begin in the slot
+    const int32_t counts = kWave * 8 * slot_runs;                     // unless kPacked: where they begin in the slot
     int32_t count = plan->class_count[cls], begin = plan->class_begin[cls];
     unsigned long long *tickets = &plan->ticket[cls];
     if (part == kGiantPart) { count = plan->giant_count[set]; tickets = &plan->ticket_giant[set]; }
@@ -202,7 +205,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
 
     auto put = [&](auto to_slot, int32_t at, T v, int n) {
         if (decltype(to_slot)::value) {
-            slot_store<T, kSmall>(slot, counts, at, v, n);
+            slot_store<T, kPacked>(slot, counts, at, v, n);
         } else {
             lds_store<T, kSmallRuns>(at, v, n);
         }
@@ -296,8 +299,8 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
                     int na, nb;
                     if (kSlots && in_slot) {
                         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");      // stores of earlier steps have landed
-                        slot_load<T, kSmall>(slot, counts, aat, va, na);
-                        slot_load<T, kSmall>(slot, counts, bat, vb, nb);
+                        slot_load<T, kPacked>(slot, counts, aat, va, na);
+                        slot_load<T, kPacked>(slot, counts, bat, vb, nb);
                     } else {
                         lds_load<T, kSmallRuns>(aat, va, na);
                         lds_load<T, kSmallRuns>(bat, vb, nb);
@@ -363,7 +366,7 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
                     have = active = false; left = 0;
                 } else {
                     in_slot = true;
-                    own = slot_ring<kSmall>(lane, slot_runs); in = slot_ring<kSmall>(prod, slot_runs);
+                    own = slot_ring<kPacked>(lane, slot_runs); in = slot_ring<kPacked>(prod, slot_runs);
                     start_configuration(BoolConst<true>());
                 }
             }
