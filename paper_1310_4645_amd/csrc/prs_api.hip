@@ -441,11 +441,11 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
             // 255 us; 500 machines of 2 to 1024 processors and up to 512 segments 18.5 -> 10.7 ms, of 2 to 64 processors
             // 16.8 -> 7.1; 500 equal ones of 1024 and 512 10.4 -> 11.5, of 40 and 8 with schedules 1.25 -> 0.52).
             // With 64 or 32 groups to a wavefront that ends at one wavefront per SIMD, more only share its cycles (20,000
-            // machines of 60 to 64 processors and 500 to 512 segments: 13.4 ms on 313 wavefronts, 8.8 on 512 or 1024, 22 on 2048),
-            // and at one for two SIMDs with more than four configurations each (10,000 equal ones of 12 and 512: 6.1 ms on
-            // 157, 6.0 on 512, 6.9 on 1024; 3000 of them 6.0 on 47, 6.6 on 512, 5.9 on 1024).  With at most 16 groups it goes
-            // on to all resident ones (3000 machines of 250 to 256 processors: 20.4 -> 13.7 ms, 15.4 on 1024).
-            const int waves = n <= 4 * kSIMDs ? kSIMDs : kSIMDs / 2, spread[2] = {total < waves ? total : waves, total};
+            // machines of 60 to 64 processors and 500 to 512 segments: 13.4 ms on 313 wavefronts, 8.8 on 1024, 22 on 2048; 25,019
+            // of 2 to 49 and 1 to 37 1.07 times as long on 512 as on 1024; 10,000 equal ones of 12 and 512 6.1 ms on 157, 6.0
+            // on 512, 6.9 on 1024).  With at most 16 groups it goes on to all resident ones (3000 machines of 250 to 256
+            // processors: 20.4 -> 13.7 ms, 15.4 on 1024).
+            const int spread[2] = {total < kSIMDs ? total : kSIMDs, total};
             for (int k = 0; k < 2; ++k)
                 G.parts.per_wave[k] = static_cast<int>(n > static_cast<int64_t>(spread[k]) * kWave ? kWave : (n + spread[k] - 1) / spread[k]);
             G.stream = st;
