@@ -70,14 +70,16 @@ hipError_t launch_offsets(const OffsetsLaunch &L)
 // A batch is split into classes, each run by the kernel and the LDS allocation that fit it:
 //   uni-greedy times:                 by number of pairs; 1, 2, 4, 8, 16, 32 or 64 lanes per configuration in one launch, machines
 //                                     of more than kUniSmallProcs processors in another;
-//   uni-greedy schedules:             by number of pairs; 1, 8, 16, 32 or 64 lanes per configuration, all in one launch;
+//   uni-greedy schedules:             by processors and number of pairs; 1, 2, 4, 8, 16 or 32 lanes per configuration in one launch,
+//                                     machines of more than kUniListProcs processors (8 to 64 lanes) in another;
 //   bi-greedy:                        1, 2, 4, 8 or 16 lanes per configuration for p <= 64 / 128 / 256 / 512 / 1024 and
 //                                     q <= 1023; the general kernel for the rest and for reruns.
-enum ClassKind { kUniTimes, kUniSched, kBiGroup, kBiGeneral, kBiBlock, kUniWide };
+enum ClassKind { kUniTimes, kUniSched, kUniList, kBiGroup, kBiGeneral, kBiBlock, kUniWide };
 constexpr size_t kLdsPerCU = 160 * 1024, kLdsPerBlockMax = 64 * 1024, kBitmapLdsMax = 24 * 1024;
 constexpr int kCUs = 256, kSIMDs = 4 * kCUs, kMaxBlocksPerCU = 24, kGlobalClassGrid = 1024;
-// LDS is given out in units of 1280 bytes: six one-wavefront blocks of 26,880 bytes run on a CU side by side, five of 27,300.
-constexpr size_t kLdsUnit = 1280;
+// LDS is given out in units of 2560 bytes: six one-wavefront blocks of 25,600 bytes run on a CU side by side, five of 26,880
+// (3072 equal machines of 900 processors, two to a wavefront: 9.6 ms in one go, 16.7 in two).
+constexpr size_t kLdsUnit = 2560;
 static int64_t blocks_per_cu(size_t lds_bytes)
 {
     return static_cast<int64_t>(kLdsPerCU / ((lds_bytes + kLdsUnit - 1) / kLdsUnit * kLdsUnit));
@@ -93,7 +95,8 @@ constexpr int kUniGroupSizes = 3;        // group sizes below the largest; the c
 constexpr int64_t kUniTimesWork[kClasses - 1] = {256, 2048, 8192, 32768, 131072};
 constexpr int32_t kUniTimesProcs[kClasses - 1] = {36, 64, 128, 320, INT32_MAX};
 constexpr int kUniTimesGiantLog2 = 19;
-constexpr int64_t kUniWorkSched[kUniGroupSizes] = {1024, 65536, 262144};  // schedules: by 1, 8, 16 lanes (measured best on the sweep)
+constexpr int64_t kUniWorkSched[kUniGroupSizes] = {1024, 65536, 262144};  // schedules of large machines: by 1, 8, 16 lanes
+constexpr int64_t kUniWorkList[kClasses - 1] = {512, 2048, 8192, 32768, 131072};   // schedules of the others: by 1, 2, 4, 8, 16 lanes
 // uni-greedy completion times: machines of at least this many processors would get a block per configuration.  Off: on the
 // large-machine sweep it is 2 to 3 times slower than the segment pipeline was pair by pair, and that one is now more than 50
 // times faster; the kernel stays reachable through prs_tuning.
@@ -154,7 +157,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
     size_t off = L.retry + align256(static_cast<size_t>(n < 1 ? 1 : n) * 4);
     // which configurations go where
     const int32_t plim[kClasses - 1] = {64, 128, 256, 512, 1024};
-    for (int k = 0; k < kClasses - 1; ++k) L.limits.p[k] = plim[k];
+    for (int k = 0; k < kClasses - 1; ++k) L.limits.p[0][k] = L.limits.p[1][k] = plim[k];
     L.limits.q = kGroupQMax;
     L.limits.by_work = 0;
     L.limits.large_p = 0;
@@ -163,37 +166,48 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
         L.limits.giant_log2[set] = kGiantLog2;
         L.limits.lanes_log2[set] = 0;
     }
+    L.limits.lane_p = 0;
     L.limits.wide_p = 0;
     L.large.grid = 0;
     L.help = false;
     L.wide.grid = 0; L.wide.slot_bytes = 0; L.wide.slot_offset = 0;
     static const int group_lpc[kClasses - 1] = {1, 2, 4, 8, 16};
     if (model == PRS_UNI) {
-        // Classes by number of pairs (1, 2, 4, 8, 16 or 32 lanes per configuration; schedules 1, 8, 16 or 32), all run by
-        // one launch, described by class 0.  Completion times of machines with more than kUniSmallProcs processors take a
-        // launch of their own, whose wavefronts have larger rings: a bound p_max above the machines of a batch, or one large
-        // machine among them, does not cost the others their wavefronts (100,000 machines of up to 1024 processors with
-        // p_max = 16384: 15.5 ms with the large rings for all, one wavefront per CU).
+        // Classes by number of pairs (1, 2, 4, 8, 16 or 32 lanes per configuration), all run by one launch, described by class 0.
+        // Machines with more than kUniSmallProcs processors take a launch of their own.  Completion times: its wavefronts have
+        // larger rings: a bound p_max above the machines of a batch, or one large machine among them, does not cost the others
+        // their wavefronts (100,000 machines of up to 1024 processors with p_max = 16384: 15.5 ms with the large rings for all,
+        // one wavefront per CU).  Schedules: the lists of the others have their processors in LDS, those of the large ones lie in
+        // the workspace (1, 8, 16 or 32 lanes per configuration).
         L.limits.by_work = 1;
-        const bool has_large = !sched && p_max > kUniSmallProcs;
+        const bool has_large = p_max > kUniSmallProcs;
         if (has_large) L.limits.large_p = kUniSmallProcs;
         const int32_t p_small = has_large ? kUniSmallProcs : p_max;
-        for (int k = 0; k < kClasses - 1; ++k) L.limits.p[k] = sched || compositions ? INT32_MAX : kUniTimesProcs[k];
+        if (sched) {
+            // Room for so many processors per lane: 16 lanes for the largest machine, the group size up to which most lanes of a
+            // pipeline have something to do, but no more than lets six wavefronts share a CU.  Machines that do not fit 32 lanes then
+            // run alone on a wavefront.
+            L.limits.lane_p = std::min(std::max((p_small + 15) / 16, 8), kUniListLaneProcs);
+            if (p_small > 32 * L.limits.lane_p) L.limits.wide_p = 32 * L.limits.lane_p + 1;
+        }
         for (int set = 0; set < 2; ++set) {
+            const bool lists = sched && set == 0, rings = sched && set == 1;
             int64_t *const work = L.limits.work[set];
-            for (int k = 0; k < kClasses - 1; ++k)
-                work[k] = sched ? kUniWorkSched[k < kUniGroupSizes ? k : kUniGroupSizes - 1] : kUniTimesWork[k];
-            if (!sched) {
-                L.limits.giant_log2[set] = kUniTimesGiantLog2;
+            for (int k = 0; k < kClasses - 1; ++k) {
+                L.limits.p[set][k] = sched || compositions ? INT32_MAX : kUniTimesProcs[k];
+                work[k] = rings ? kUniWorkSched[k < kUniGroupSizes ? k : kUniGroupSizes - 1] : lists ? kUniWorkList[k] : kUniTimesWork[k];
+            }
+            if (!rings) {
                 // A batch that leaves lanes without a configuration gives each of its configurations more of them.
-                const int64_t lanes = blocks_per_cu(uni_times_lds_bytes(set ? p_max : p_small, compositions)) * kCUs * kWave;
+                const size_t lds = lists ? uni_list_lds_bytes(L.limits.lane_p) : uni_times_lds_bytes(set ? p_max : p_small, compositions);
+                const int64_t lanes = blocks_per_cu(lds) * kCUs * kWave;
                 for (int k = 0; k < kClasses - 1; ++k)
                     if (n << (k + 1) <= lanes) work[k] = 0;
-                if (n << 6 <= lanes) L.limits.giant_log2[set] = 0;
+                if (!lists) L.limits.giant_log2[set] = kUniTimesGiantLog2;
+                if (!lists && n << 6 <= lanes) L.limits.giant_log2[set] = 0;
                 else L.limits.lanes_log2[set] = 1;
             } else {
-                // The same for schedules: 64, 32, 16 or 8 lanes where the batch leaves that many idle (one machine of 256
-                // processors and 64 segments 3.2 -> 2.6 ms, a few hundred machines 3.3 -> 2.1 ms).
+                // The same for schedules of large machines: 64, 32, 16 or 8 lanes where the batch leaves that many idle.
                 const int64_t lanes = blocks_per_cu(uni_sched_lds_bytes()) * kCUs * kWave;
                 static const int more[kUniGroupSizes] = {3, 4, 5};            // the next group size: 8, 16, 32 lanes
                 for (int k = 0; k < kClasses - 1; ++k)
@@ -203,10 +217,10 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             if (tuning) {                                              // never changes a result, only who runs what
                 L.limits.lanes_log2[set] = 0;
                 L.limits.giant_log2[set] = sched ? kGiantLog2 : kUniTimesGiantLog2;
-                for (int k = 0; k < kClasses - 1; ++k) L.limits.p[k] = INT32_MAX;
+                for (int k = 0; k < kClasses - 1; ++k) L.limits.p[set][k] = INT32_MAX;
                 const int64_t a = tuning->uni_group_pairs[0], b = tuning->uni_group_pairs[1], c3 = tuning->uni_group_pairs[2];
                 if (a >= 0 && b >= a && c3 >= b) {
-                    if (sched) {
+                    if (rings) {
                         work[0] = a; work[1] = b;
                         for (int k = 2; k < kClasses - 1; ++k) work[k] = c3;
                     } else {                                           // 1, 4 and 16 lanes; nothing for 2 and 8
@@ -220,13 +234,22 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
         }
         auto uni_spec = [&](ClassSpec &c, int32_t p) {                 // one launch for machines of up to p processors
             c.q_cap = q_max;
-            c.kind = sched ? kUniSched : kUniTimes; c.lpc = 0; c.rows_per_group = 0; c.lds = true; c.lds_bitmap_bytes = 0;
-            // schedules: keeps every per-lane array 64-byte aligned; times: runs of a lane's ring
-            c.p_cap = sched ? (p + 15) / 16 * 16 : uni_times_slot_runs(p);
-            c.lds_bytes = sched ? uni_sched_lds_bytes() : uni_times_lds_bytes(p, compositions);
-            c.slot_bytes = sched ? uni_sched_slot_bytes(c.p_cap) : uni_times_slot_bytes(c.p_cap, compositions || p > kUniSmallProcs);
+            c.lpc = 0; c.rows_per_group = 0; c.lds = true; c.lds_bitmap_bytes = 0;
+            if (sched && p <= kUniListProcs) {                         // everything in LDS
+                c.kind = kUniList;
+                c.p_cap = L.limits.lane_p; c.lds_bytes = uni_list_lds_bytes(c.p_cap); c.slot_bytes = 0;
+            } else if (sched) {
+                c.kind = kUniSched;
+                c.p_cap = (p + 15) / 16 * 16;                          // keeps every per-lane array 64-byte aligned
+                c.lds_bytes = uni_sched_lds_bytes(); c.slot_bytes = uni_sched_slot_bytes(c.p_cap);
+            } else {
+                c.kind = kUniTimes;
+                c.p_cap = uni_times_slot_runs(p);                      // runs of a lane's ring
+                c.lds_bytes = uni_times_lds_bytes(p, compositions);
+                c.slot_bytes = uni_times_slot_bytes(c.p_cap, compositions || p > kUniSmallProcs);
+            }
             int64_t g = blocks_per_cu(c.lds_bytes) * kCUs;
-            if (!sched && g > n) g = n < 1 ? 1 : n;
+            if (c.kind != kUniSched && g > n) g = n < 1 ? 1 : n;
             size_t bytes = static_cast<size_t>(g) * c.slot_bytes;
             if (sched) {
                 while (g > 1 && static_cast<size_t>(g) * c.slot_bytes > kMaxWorkspace) g /= 2;
@@ -245,8 +268,8 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             // A batch whose small machines leave lanes idle is bound by its longest chains: these begin beside the large
             // machines (3000 machines, 81 of them of 1024 to 20000 processors: 5.9 -> 4.0 ms).  A larger one is bound by how many
             // run at once, which is one wavefront per CU there and five in the launch that follows (30000 machines: 5.9 -> 6.4).
-            L.help = n << 4 <= blocks_per_cu(uni_times_lds_bytes(p_small, compositions)) * kCUs * kWave;
-            if (p_max > kUniMidProcs) slots = std::max(slots, uni_spec(L.large, kUniMidProcs));   // more wavefronts: no less than for that bound
+            L.help = !sched && n << 4 <= blocks_per_cu(uni_times_lds_bytes(p_small, compositions)) * kCUs * kWave;
+            if (!sched && p_max > kUniMidProcs) slots = std::max(slots, uni_spec(L.large, kUniMidProcs));   // more wavefronts: no less than for that bound
             slots = std::max(slots, uni_spec(L.large, p_max));
         }
         // completion times of machines with thousands of processors: a block per configuration
@@ -274,10 +297,10 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
     for (int k = 0; k < kClasses; ++k) {
         ClassSpec &c = L.cls[k];
         const bool last = k == kClasses - 1;
-        c.p_cap = last ? p_max : (L.limits.p[k] < p_max ? L.limits.p[k] : p_max);
+        c.p_cap = last ? p_max : (L.limits.p[0][k] < p_max ? L.limits.p[0][k] : p_max);
         c.q_cap = q_max;
         c.lds = false; c.lds_bytes = 0; c.lds_bitmap_bytes = 0; c.slot_bytes = 0; c.lpc = 0; c.rows_per_group = 0;
-        const bool possible = last || k == 0 || L.limits.p[k - 1] < p_max;   // can a configuration land here?
+        const bool possible = last || k == 0 || L.limits.p[0][k - 1] < p_max;   // can a configuration land here?
         if (!last) {
             // several configurations per wavefront; the slot of a wavefront holds the sent-bit rows of its groups
             c.kind = kBiGroup;
@@ -287,7 +310,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             const int32_t q_cap = q_max < kGroupQMax ? q_max : kGroupQMax;
             c.rows_per_group = static_cast<size_t>(q_cap) * c.lpc;
             c.slot_bytes = c.rows_per_group * 8 * (64 / c.lpc);
-        } else if (p_max > L.limits.p[kClasses - 2] && bi_block_lds_bytes(c.p_cap) <= kLdsPerBlockMax) {
+        } else if (p_max > L.limits.p[0][kClasses - 2] && bi_block_lds_bytes(c.p_cap) <= kLdsPerBlockMax) {
             // thousands of processors: one block of 8 wavefronts per configuration
             c.kind = kBiBlock;
             c.lds_bytes = bi_block_lds_bytes(c.p_cap);
@@ -330,7 +353,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
     // reruns come from the group classes only: at most 1024 processors and 1023 segments
     {
         ClassSpec &c = L.rerun;
-        general_spec(c, p_max < L.limits.p[kClasses - 2] ? p_max : L.limits.p[kClasses - 2], q_max < kGroupQMax ? q_max : kGroupQMax);
+        general_spec(c, p_max < L.limits.p[0][kClasses - 2] ? p_max : L.limits.p[0][kClasses - 2], q_max < kGroupQMax ? q_max : kGroupQMax);
         int64_t g = kGlobalClassGrid;
         if (c.lds) {
             int64_t per_cu = static_cast<int64_t>(kLdsPerCU / (c.lds_bytes < 1024 ? 1024 : c.lds_bytes));
@@ -380,7 +403,7 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
     int32_t *retry = reinterpret_cast<int32_t *>(ws + lay.retry);
     auto general = [&](const ClassSpec &c, const int32_t *order, int cls) {          // batch / general kernels
         UniLaunch L;
-        L.cfg = P.cfg;
+        L.cfg = P.cfg; L.n = n;
         L.p_max = p_max; L.q_max = q_max; L.model = model; L.cost = cost;
         L.want_schedule = call == PRS_CALL_SCHEDULE;
         L.times = times; L.sched = sched;
@@ -395,13 +418,14 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
         L.grid = c.grid;
         L.stream = st;
         if (c.kind == kUniTimes) return launch_uni_times(L);
+        if (c.kind == kUniList) return launch_uni_list(L);
         if (c.kind == kUniSched) return launch_uni_sched(L);
         if (c.kind == kBiBlock) return launch_bi_block(L);
         if (c.kind == kUniWide) return launch_uni_wide(L);
         return launch_bi(L);
     };
     // the class with the longest-running configurations first; a class without configurations ends at once
-    if (lay.limits.wide_p > 0 && general(lay.wide, P.order, kWideClass) != hipSuccess) return PRS_EDEVICE;
+    if (lay.wide.grid > 0 && lay.limits.wide_p > 0 && general(lay.wide, P.order, kWideClass) != hipSuccess) return PRS_EDEVICE;
     if (lay.large.grid > 0 && general(lay.large, P.order, kLargeClass) != hipSuccess) return PRS_EDEVICE;
     bool groups_done = false;
     for (int k = kClasses - 1; k >= 0; --k) {

@@ -168,6 +168,24 @@ template <> __device__ __forceinline__ int64_t wrap_add<int64_t>(int64_t a, int6
 }
 template <> __device__ __forceinline__ double wrap_add<double>(double a, double b) { return a + b; }
 
+// v, or a value above every time of a schedule (those stay below 4e18 and 1e300: schedule_fits) if v is not there.  Only
+// the upper half is exchanged.
+template <typename T> __device__ __forceinline__ T or_absent(bool there, T v)
+{
+    uint64_t bits;
+    __builtin_memcpy(&bits, &v, 8);
+    const uint32_t hi = there ? static_cast<uint32_t>(bits >> 32) : 0x7FEFFFFFu;
+    bits = (static_cast<uint64_t>(hi) << 32) | static_cast<uint32_t>(bits);
+    __builtin_memcpy(&v, &bits, 8);
+    return v;
+}
+
+// LDS by its byte address (kernels without LDS of their own besides what the launch asks for, which begins at 0)
+template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) T *lds_at(int32_t at)
+{
+    return reinterpret_cast<__attribute__((address_space(3))) T *>(static_cast<uint32_t>(at));
+}
+
 // keeps a branch a branch (its body is then not run speculatively on the other path)
 #ifndef PRS_KEEP_BRANCH
 #define PRS_KEEP_BRANCH() asm volatile("" ::: "memory")

@@ -29,6 +29,7 @@ constexpr int32_t kUniSmallProcs = 1024, kUniMidProcs = 8192;    // largest mach
 // slots then hold only what stays in global memory.  slot_p/slot_q size the slot arrays.
 struct UniLaunch {
     ConfigArrays cfg;
+    int64_t n;
     int32_t p_max, q_max;
     int model, cost;
     bool want_schedule;
@@ -93,6 +94,11 @@ hipError_t launch_uni_times(const UniLaunch &L);
 size_t uni_sched_lds_bytes();
 size_t uni_sched_slot_bytes(int32_t p_cap);
 hipError_t launch_uni_sched(const UniLaunch &L);
+// schedules of machines of up to kUniListProcs processors
+constexpr int32_t kUniListProcs = 1024;
+constexpr int32_t kUniListLaneProcs = 30;                    // most processors per lane, of which six wavefronts fit a CU
+size_t uni_list_lds_bytes(int32_t procs);                    // a wavefront's, with room for so many processors per lane
+hipError_t launch_uni_list(const UniLaunch &L);
 // uni-greedy completion times of machines with thousands of processors: one block per configuration
 size_t uni_wide_slot_bytes(int32_t p_cap);
 size_t uni_wide_lds_bytes();

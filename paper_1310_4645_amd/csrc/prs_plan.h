@@ -10,7 +10,7 @@ namespace prs {
 constexpr int kClasses = 6;          // bi-greedy: five group sizes and the general kernel; uni-greedy: six group sizes (schedules use 0, 1, 2 and the last)
 constexpr int kWorkBuckets = 40;     // floor(log2(work)) buckets, heaviest first
 constexpr int kRetryClass = kClasses; // pseudo class: configurations handed back to the general kernel
-constexpr int kWideClass = kClasses;  // uni-greedy completion times: machines large enough for a block of their own
+constexpr int kWideClass = kClasses;  // uni-greedy: machines large enough for a block (completion times) or a wavefront (schedules) of their own
 constexpr int kLargeClass = kClasses + 1;   // uni-greedy completion times: the classes 0 .. kClasses - 1 again, for machines of more than large_p processors
 constexpr int kPlanClasses = kLargeClass + kClasses;
 
@@ -29,19 +29,21 @@ struct PlanHeader {
 constexpr int kGiantLog2 = 23;
 enum ClassPart { kWholeClass = 0, kGiantPart = 1, kRestPart = 2 };
 
-// By size (by_work == 0): class k holds p <= limits.p[k]; the last class the rest and every configuration
+// By size (by_work == 0): class k holds p <= limits.p[0][k]; the last class the rest and every configuration
 // with more than q segments.
 // By work (by_work != 0): class k holds the configurations with at most work[k] pairs and p[k] processors, the last class
 // the rest.  Machines of more than large_p processors (0: none) have classes of their own, with the limits [1] instead of [0].
 struct ClassLimits {
-    int32_t p[kClasses - 1];
+    int32_t p[2][kClasses - 1];
     int32_t q;
     int32_t by_work;
     int32_t large_p;
     int64_t work[2][kClasses - 1];
     int32_t giant_log2[2];       // configurations of the last class with at least 2^giant_log2 pairs are "giant"
     int32_t lanes_log2[2];       // by_work only: 1: class k has 2^k lanes per configuration, and none gets more than it has segments
-    int32_t wide_p;              // by_work only: machines of at least this many processors form the class kWideClass (0: none)
+    int32_t lane_p;              // by_work only: the first set's class k holds at most 2^k times as many processors (0: no such limit)
+    int32_t wide_p;              // by_work only: machines of at least this many processors form the class kWideClass (0: none);
+                                 // with lane_p those of the first set only
 };
 
 struct PlanLaunch {

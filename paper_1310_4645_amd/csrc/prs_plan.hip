@@ -13,13 +13,14 @@ __device__ __forceinline__ int plan_bucket(const ConfigArrays &cfg, int64_t i, i
     if (lim.by_work) {
         const bool large = lim.large_p > 0 && c.p > lim.large_p;
         for (int k = kClasses - 2; k >= 0; --k)
-            if (work <= lim.work[large ? 1 : 0][k] && c.p <= lim.p[k]) cls = k;
+            if (work <= lim.work[large ? 1 : 0][k] && c.p <= lim.p[large ? 1 : 0][k]) cls = k;
         if (lim.lanes_log2[large ? 1 : 0]) { const int enough = ceil_log2(c.q); cls = cls < enough ? cls : enough; }
+        if (lim.lane_p > 0 && !large) { const int least = ceil_log2((c.p + lim.lane_p - 1) / lim.lane_p); cls = cls > least ? cls : least; }
         if (large) cls += kLargeClass;
-        if (lim.wide_p > 0 && c.p >= lim.wide_p && cfg.comp_m == 0) cls = kWideClass;
+        if (lim.wide_p > 0 && c.p >= lim.wide_p && cfg.comp_m == 0 && !(large && lim.lane_p > 0)) cls = kWideClass;
     } else {
         for (int k = kClasses - 2; k >= 0; --k)
-            if (c.p <= lim.p[k] && c.q <= lim.q) cls = k;
+            if (c.p <= lim.p[0][k] && c.q <= lim.q) cls = k;
     }
     int lg = 63 - __builtin_clzll(static_cast<unsigned long long>(work) | 1ULL);
     if (lg > kWorkBuckets - 1) lg = kWorkBuckets - 1;

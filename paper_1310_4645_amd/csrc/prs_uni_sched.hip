@@ -1,6 +1,7 @@
-// Uni-greedy schedules (Lowery & Langou, Algorithm 1, Section 5) on gfx950: the segment pipeline of the
-// completion-time kernel with processor identities.  It emits the pairs of every segment in the order of
-// Algorithm 1 (ties by processor index, the root never sending) with their start times.
+// Uni-greedy schedules (Lowery & Langou, Algorithm 1, Section 5) of machines of more than 1024 processors on gfx950: the segment
+// pipeline of the completion-time kernel with processor identities, its streams in LDS rings backed by the workspace.  It
+// emits the pairs of every segment in the order of Algorithm 1 (ties by processor index, the root never sending) with their
+// start times.  (Smaller machines keep all of their streams in LDS: prs_uni_list.hip.)
 //
 // Differences to the value-only pipeline:
 //  - stream entries are (value, sender index) and must reach the next segment sorted by both.  Senders
@@ -15,13 +16,10 @@
 //  - B needs the receiver's index per pair, kept in a per-lane array; its values are still S + tcomp.
 //    Equal B values are kept in index order by the same insertion.
 //
-// What bounds it: 25.7 million wavefront iterations on the 100,000-configuration sweep (60 % of their lanes form a pair), each
-// about 300 vector and 150 scalar instructions and 2 us, half of it waiting, above all for the entries that the first lane of
-// a group reads from the workspace.  Rows that have been read by the time they would leave LDS stay out of the workspace,
-// and what is left at the end of a segment leaves with the rows of the next one instead of entry by entry (those loops
-// ran in every fifth iteration, in all of them on small machines): 279 -> 155 million store instructions with the first
-// and the second half of the change, 54.1 -> 51.7 ms; one machine of 256 processors and 64 segments 2.61 -> 2.35 ms.
-// Measured and not taken: 16-bit indices with a ring of 16 and eight wavefronts per CU, 110 ms.
+// What bounds it: iterations of about 300 vector and 150 scalar instructions and 2 us, half of it waiting, above all for the
+// entries that the first lane of a group reads from the workspace.  Rows that have been read by the time they would leave LDS stay out of the
+// workspace, and what is left at the end of a segment leaves with the rows of the next one instead of entry by entry.
+// Measured and not taken: 16-bit indices with a ring of 16 and eight wavefronts per CU, twice the time.
 #include "prs_device.h"
 #include "prs_launch.h"
 
@@ -32,7 +30,6 @@ constexpr int kNearS = kRingS - 5;   // entries this close behind the writer are
 // Rows of eight leave LDS when this many entries wait, one row every four iterations.  Six more entries can come before (four
 // pairs, the held entry and the root's), four more while the last, shorter row of a segment leaves.
 constexpr int kKeepS = 16;
-constexpr int kTailP = 32;           // with fewer processors the rest of a segment leaves at its end
 static_assert(kKeepS + 10 <= kNearS && kKeepS >= 8, "entries that are read from the workspace have to be there");
 
 constexpr int kStage = 8;            // pairs per lane waiting in LDS for their 16-byte stores
@@ -135,8 +132,8 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
     // part of the class this pass works on: all of it, its giant configurations only, or the rest after those
     int32_t count = plan->class_count[cls], begin = plan->class_begin[cls];
     unsigned long long *tickets = &plan->ticket[cls];
-    if (part == kGiantPart) { count = plan->giant_count[0]; tickets = &plan->ticket_giant[0]; }
-    else if (part == kRestPart) { begin += plan->giant_count[0]; count -= plan->giant_count[0]; }
+    if (part == kGiantPart) { count = plan->giant_count[1]; tickets = &plan->ticket_giant[1]; }
+    else if (part == kRestPart) { begin += plan->giant_count[1]; count -= plan->giant_count[1]; }
     if (count == 0) return;
     const T kInf = CostTraits<T>::inf();
 
@@ -331,38 +328,24 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
                 put(tr, 0, runStart);
                 // Entries that still wait in LDS leave with the rows of the next segment, if nobody has read them by then;
                 // nobody reads the last segment.
-                if (p < kTailP) {
-                    for (int j = fW; j < w; j += 8)
-                        if (readTo < segBase + j + 8) store_row(myX, myI, segBase, j);
-                } else if (k < q - 1) {
-                    tailFrom = segBase + fW; tailTo = wtot;
-                }
+                if (k < q - 1) { tailFrom = segBase + fW; tailTo = wtot; }
                 // the last pairs: rows of four, the last one reaching back if need be
                 while (fO < n1) {
-                    const int j0 = n1 < 4 ? fO : (fO < n1 - 4 ? fO : n1 - 4);
+                    const int j0 = fO < n1 - 4 ? fO : n1 - 4;
                     const int64_t o4 = out_base + static_cast<int64_t>(k) * n1 + j0;
-                    if (n1 < 4) {
-                        const int slot = lane * kStage + (j0 & (kStage - 1));
-                        if (sched.src) sched.src[o4] = stS[slot];
-                        if (sched.dst) sched.dst[o4] = stD[slot];
-                        if (sched.seg) sched.seg[o4] = k;
-                        if (sched.tstart) static_cast<T *>(sched.tstart)[o4] = stT[slot];
-                        ++fO;
-                    } else {
-                        int32_t s4[4], d4[4];
-                        T t4[4];
-                        const int32_t k4[4] = {k, k, k, k};
+                    int32_t s4[4], d4[4];
+                    T t4[4];
+                    const int32_t k4[4] = {k, k, k, k};
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int slot = lane * kStage + ((j0 + i) & (kStage - 1));
-                            s4[i] = stS[slot]; d4[i] = stD[slot]; t4[i] = stT[slot];
-                        }
-                        if (sched.src) __builtin_memcpy(sched.src + o4, s4, 16);
-                        if (sched.dst) __builtin_memcpy(sched.dst + o4, d4, 16);
-                        if (sched.seg) __builtin_memcpy(sched.seg + o4, k4, 16);
-                        if (sched.tstart) __builtin_memcpy(static_cast<T *>(sched.tstart) + o4, t4, 32);
-                        fO += 4;
+                    for (int i = 0; i < 4; ++i) {
+                        const int slot = lane * kStage + ((j0 + i) & (kStage - 1));
+                        s4[i] = stS[slot]; d4[i] = stD[slot]; t4[i] = stT[slot];
                     }
+                    if (sched.src) __builtin_memcpy(sched.src + o4, s4, 16);
+                    if (sched.dst) __builtin_memcpy(sched.dst + o4, d4, 16);
+                    if (sched.seg) __builtin_memcpy(sched.seg + o4, k4, 16);
+                    if (sched.tstart) __builtin_memcpy(static_cast<T *>(sched.tstart) + o4, t4, 32);
+                    fO += 4;
                 }
                 fW = fB = fO = 0;
                 if (k == q - 1 && sched.T_greedy) static_cast<T *>(sched.T_greedy)[ci] = tr;
@@ -440,15 +423,15 @@ __global__ __launch_bounds__(kWave) void uni_sched_kernel(ConfigArrays cfg, int3
 {
     PRS_DYNAMIC_LDS(lds_raw);
     char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
-    uni_sched_body<T, 64>(lds_raw, cfg, p_max, q_max, sched, plan, order, kClasses - 1, kGiantPart, slot, slot_p);
+    uni_sched_body<T, 64>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + kClasses - 1, kGiantPart, slot, slot_p);
     __syncthreads();
-    uni_sched_body<T, 32>(lds_raw, cfg, p_max, q_max, sched, plan, order, kClasses - 1, kRestPart, slot, slot_p);
+    uni_sched_body<T, 32>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + kClasses - 1, kRestPart, slot, slot_p);
     __syncthreads();
-    uni_sched_body<T, 16>(lds_raw, cfg, p_max, q_max, sched, plan, order, 2, kWholeClass, slot, slot_p);
+    uni_sched_body<T, 16>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + 2, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_sched_body<T, 8>(lds_raw, cfg, p_max, q_max, sched, plan, order, 1, kWholeClass, slot, slot_p);
+    uni_sched_body<T, 8>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + 1, kWholeClass, slot, slot_p);
     __syncthreads();
-    uni_sched_body<T, 1>(lds_raw, cfg, p_max, q_max, sched, plan, order, 0, kWholeClass, slot, slot_p);
+    uni_sched_body<T, 1>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass, kWholeClass, slot, slot_p);
 }
 
 hipError_t launch_uni_sched(const UniLaunch &L)

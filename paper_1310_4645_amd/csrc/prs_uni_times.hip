@@ -79,24 +79,8 @@ int32_t uni_times_slot_runs(int32_t p_max)
 // cost 78 x 2048 of them 2.01 ms against 1.85); apart where few do and there are the most wavefronts.
 size_t uni_times_slot_bytes(int32_t runs, bool packed) { return static_cast<size_t>(kWave) * static_cast<size_t>(runs) * (packed ? kRunBytes : 10); }
 
-// v, or a value above every time of a schedule (those stay below 4e18 and 1e300: schedule_fits) if v is not there.  Only
-// the upper half is exchanged.
-template <typename T> __device__ __forceinline__ T or_absent(bool there, T v)
-{
-    uint64_t bits;
-    __builtin_memcpy(&bits, &v, 8);
-    const uint32_t hi = there ? static_cast<uint32_t>(bits >> 32) : 0x7FEFFFFFu;
-    bits = (static_cast<uint64_t>(hi) << 32) | static_cast<uint32_t>(bits);
-    __builtin_memcpy(&v, &bits, 8);
-    return v;
-}
-
 // Runs in LDS by the byte address of their place.  kSmall: the value there, the count among the 16-bit ones behind all
 // values; otherwise both packed into 12 bytes.
-template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) T *lds_at(int32_t at)
-{
-    return reinterpret_cast<__attribute__((address_space(3))) T *>(static_cast<uint32_t>(at));
-}
 // kSmallRuns: how many runs a wavefront keeps, 0 if they are packed
 template <typename T, int kSmallRuns> __device__ __forceinline__ void lds_load(int32_t at, T &v, int32_t &n)
 {

@@ -376,6 +376,44 @@ def test_uni_schedules_with_long_runs_of_equal_values(prs):
     _check_schedules(prs, full.take(idx), 0, 1024, 512)
 
 
+@pytest.mark.parametrize("cost", ["i64", "f64"])
+@pytest.mark.parametrize("p_max", [16, 240, 480, 960, 1024, 1100])
+def test_uni_schedules_at_the_edges_of_the_lists(prs, p_max, cost):
+    """Largest and next machine of every group size (8, 15 or 30 processors per lane by the bound, 1 to 32 lanes), machines alone on a
+    wavefront (961 to 1024) and those that use the workspace (1025 on), one segment to more than lanes, costs that vanish
+    against the clock, blocks of eight pairs that begin and end anywhere: pair for pair.  Then with gaps between the configurations."""
+    import torch
+    rng = np.random.default_rng(p_max)
+    lane = min(max((min(p_max, 1024) + 15) // 16, 8), 30)
+    sizes = sorted({v for g in (1, 2, 4, 8, 16, 32) for v in (lane * g, lane * g + 1)} | {2, 3, 5, 960, 961, 1023, 1024, 1025, p_max})
+    p = np.repeat([v for v in sizes if v <= p_max], 4)
+    q = np.tile([1, 2, 5, 37], len(p) // 4)
+    q = np.where(p * p * q > 4_000_000, np.minimum(q, 3), q)
+    n, m = len(p), q * 3 - rng.integers(0, 2, len(p)) * (q > 1)
+    if cost == "i64":
+        costs = [rng.choice([1, 2, 10], n), rng.integers(0, 3, n), rng.integers(0, 3, n)]
+    else:
+        costs = [rng.choice([0.1, 1e-5, 0.3], n), rng.choice([0.1, 1e-6, 0.0], n), rng.choice([0.0, 1e-20, 0.1, 3e-6], n)]
+    number = np.int64 if cost == "i64" else np.float64
+    host = prs_inputs.SweepConfigs(p.astype(np.int32), q.astype(np.int32), m.astype(np.int64), *[c.astype(number) for c in costs], cost)
+    _check_schedules(prs, host, 0, p_max, 40)
+    refs = _oracle_schedules(host, 0)
+    lengths = np.array([len(r.src) for r in refs])
+    start = np.cumsum(np.concatenate([[3], lengths[:-1] + rng.integers(0, 4, n - 1)]))
+    total = int(start[-1] + lengths[-1] + 5)
+    bufs = [torch.full((total,), -7, dtype=torch.int32, device="cuda") for _ in range(3)]
+    t = torch.full((total,), -7, dtype=torch.int64 if cost == "i64" else torch.float64, device="cuda")
+    off = torch.from_numpy(np.append(start, total)).cuda()
+    prs.greedy_schedule_batch(prs.DeviceConfigs.from_host(host), 0, p_max, 40, off, total, bufs[0], bufs[1], bufs[2], t)
+    _sync()
+    want = [np.full(total, -7) for _ in range(3)] + [np.full(total, -7, number)]
+    for i, r in enumerate(refs):
+        for w, v in zip(want, (r.src, r.dst, r.seg, r.t)):
+            w[start[i]:start[i] + lengths[i]] = v
+    for got, w in zip(bufs + [t], want):
+        assert np.array_equal(_np(got), w)
+
+
 @pytest.mark.parametrize("n", [1, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193])
 def test_uni_schedules_of_small_batches(prs, n):
     """Schedules pair for pair at the batch sizes where a configuration gets 64, 32, 16 or 8 lanes or as many as its pairs ask for."""
