@@ -1,15 +1,20 @@
 // Bi-greedy schedules (Lowery & Langou, Algorithm 2, Section 6.2) for machines of thousands of processors on
-// gfx950: one block of eight wavefronts per configuration.
+// gfx950: one block of eight wavefronts per configuration, or one of its wavefronts.
 //
 // Every list of Algorithm 2 is a bit set over the processors, list lengths are population counts, "first k entries" a
 // rank select inside a word, list positions prefix sums.  run_bi_wide keeps the sets in registers and the running transfers in a
 // list; run_bi_block, which keeps times per processor in the workspace slot, does what does not fit there: more than 64
 // transfers running at once.
 //
-// What bounds it: the chain of visits of the longest configuration (about 33,000 on 65536 processors and 1000 segments), each
-// one or two sums over the block.  64 machines of 1024 to 65536 processors, completion times: 263 ms with times per processor
-// (about 14 barriers a visit, scattered updates of S, R and C1, all of them read again at every event), 41 ms with
-// run_bi_wide.
+// What bounds it: the chain of visits of the longest configuration, 24 a segment, three quarters of which pair somebody, at 4600
+// cycles each on eight wavefronts: sums inside and between the wavefronts, and 400 instructions that depend on each
+// other.  On one wavefront a visit needs neither a barrier nor a sum over the block, so machines of up to 16384 processors (four
+// words of every set per lane; with six or eight the registers spill, 12.6 -> 17.4 and 28.6 ms on 16 of up to 22,709) run on one: 19 of
+// up to 5006 processors and 495 segments 14.6 -> 7.5 ms, 26 of up to 2223 4.76 -> 2.23.  64 machines of 1024 to 65536 processors, completion
+// times: 263 ms with times per processor (about 14 barriers a visit, scattered updates of S, R and C1, all of them read
+// again at every event), 41.0 with two sums over the block and a loop over the wavefronts' parts, 38.8 so.  Measured and not
+// taken: what a visit writes held back until the next one has its row (no change), eight entries of the list at a time
+// (41.0), four wavefronts with four words per thread (44.7).
 #include "prs_device.h"
 #include "prs_launch.h"
 
@@ -348,19 +353,20 @@ __device__ T run_bi_block(const Config<T> &c, char *lds, char *slot, const Block
 
 // ---- the usual path: sets in registers, running transfers as a list --------------------------------------------------
 //
-// Thread i of the block owns the words i kw .. i kw + kw - 1 of every bit set, kw = 1, 2 or 3, and keeps them in registers.  The
+// Thread i owns the words i kw .. i kw + kw - 1 of every bit set, kw = 1, 2 or 3 (up to 4 on one wavefront), and keeps them in registers.  The
 // kernel for three words serves batches whose bound passes 65536 processors (16 machines of 66,000, 8 segments: 14.6 ms on
 // run_bi_block, 2.1 so; its registers cost machines of two words a sixth, 20 segments on 16 of 40,000 3.7 -> 4.3 ms).
 // All pairs of a visit (time t, segment j) have the same end of send and end of combine, so the ports and computations
 // of Algorithm 2 are a list of groups (end of send, end of combine, set of senders, set of receivers): lane e of EVERY
 // wavefront holds the two times of entry e, the sets lie in the workspace slot, word by word written and read by the
 // thread that owns the word.  Nothing is kept per processor, and a visit needs one sum over the block (the lengths of the
-// three lists, the prefix counts of the free processors and a few yes/no questions travel in 16 bytes per
-// wavefront) and a second one only if a list has to be cut; a sum is one barrier, with two buffers in turn: a wavefront
-// that writes a buffer again has passed the barrier of the sum in between, which nobody reaches before it has read the first.
+// three lists, the prefix counts of their parts and a few yes/no questions travel in 16 bytes per wavefront); a sum is
+// one barrier, with two buffers in turn: a wavefront that writes a buffer again has passed the barrier of the sum in between,
+// which nobody reaches before it has read the first.
 // Processors that have sent everything stay in the sets: they hold no segment, so they never pair.
 constexpr int kWideWords = 65536 / 64 / kBlockThreads;     // words per thread on machines of up to 65536 processors
 constexpr int kWideProcs = kBlockThreads * kWideWords * 64;
+constexpr int kAloneWords = 4;                             // words per lane up to which one wavefront runs a machine by itself
 constexpr int kWideEntries = kWave;                        // running transfers, one per lane
 
 template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_rows(int v)
@@ -378,6 +384,33 @@ __device__ __forceinline__ int dpp_inclusive_scan(int v)
     v += dpp_rows<0x142, 0xA>(v);
     v += dpp_rows<0x143, 0xC>(v);
     return v;
+}
+// sum over the eight lanes of half a row: neighbours, pairs, the other quad
+__device__ __forceinline__ int dpp_sum8(int v)
+{
+    v += dpp_rows<0xB1, 0xF>(v);
+    v += dpp_rows<0x4E, 0xF>(v);
+    v += dpp_rows<0x141, 0xF>(v);
+    return v;
+}
+// lowest_bits where few lanes of a wavefront have to search, one in a list that all lanes hold words of: the whole wavefront looks
+// at that lane's word, a bit to a lane.
+__device__ __forceinline__ uint64_t lowest_bits_of_few(uint64_t mask, int k, int lane)
+{
+    const int n = __popcll(mask);
+    uint64_t some = k > 0 ? mask : 0;
+    uint64_t search = ballot64(k > 0 && k < n);
+    while (search != 0) {
+        const int who = __builtin_ctzll(search);
+        search &= search - 1;
+        const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(mask)), who),
+                       hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(mask >> 32)), who);
+        const uint64_t w = (static_cast<uint64_t>(hi) << 32) | lo;
+        const int kk = __builtin_amdgcn_readlane(k, who);
+        const uint64_t found = ballot64(rank_below(w) < kk) & w;
+        some = lane == who ? found : some;
+    }
+    return some;
 }
 template <int CTRL, typename T> __device__ __forceinline__ T dpp_min(T v)
 {
@@ -407,14 +440,16 @@ template <typename T> __device__ __forceinline__ T wave_min_dpp(T v)
 
 // Returns false if the list of running transfers would need more than `entries` entries: nothing of the configuration is
 // final then, and run_bi_block does it from the start.
-template <typename T, bool kSched, int K>
+// K words of every set per thread, kWaves wavefronts (1 or kBlockWaves).
+template <typename T, bool kSched, int K, int kWaves>
 __device__ bool run_bi_wide(const Config<T> &c, int4 *red, uint64_t *rows, uint64_t *sets, int entries, const SchedOut &sched,
                             int64_t out_base, T *result, int32_t *status)
 {
+    constexpr int kThreads = kWaves * kWave;
     const int tid = static_cast<int>(threadIdx.x), lane = lane_id();
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
     const int p = c.p, q = c.q;
-    const int W = (p + 63) >> 6, kw = (W + kBlockThreads - 1) / kBlockThreads, w0 = tid * kw;
+    const int W = (p + 63) >> 6, kw = (W + kThreads - 1) / kThreads, w0 = tid * kw;
     const uint64_t root = tid == 0 ? UINT64_C(1) : 0;                      // processor 0: bit 0 of word 0
     const bool ragged = c.sz_last != c.sz, guardL = ragged && c.g_last > 0;
     const T kInf = CostTraits<T>::inf();
@@ -544,25 +579,25 @@ __device__ bool run_bi_wide(const Config<T> &c, int4 *red, uint64_t *rows, uint6
             const int scanF = dpp_inclusive_scan(pf | (pm << 16)), sumO = dpp_inclusive_scan(pso | (pro << 16));
             const uint64_t some = ballot64(pu != 0);
             const int two = ballot64(pu > 1) != 0 ? 2 : (some == 0 ? 0 : ((some & (some - 1)) != 0 ? 2 : 1));
-            const int4 *const part = partial(scanF, sumO, (ballot64(as) != 0 ? 1 : 0) | (ballot64(ar) != 0 ? 2 : 0) |
-                                                              (ballot64(any) != 0 ? 4 : 0) | (ballot64(cand) != 0 ? 8 : 0) | (two << 8));
-            if (!past && j + 1 < q) fetch(j + 1);                          // on its way while this visit goes on
-            int nf_ = 0, remj = -1, ns_ = 0, nr_ = 0, either = 0, flags = 0, exF = (scanF & 0xFFFF) - pf;
-#pragma unroll
-            for (int w = 0; w < kBlockWaves; ++w) {
-                const int4 x = part[w];
-                if (w < wave) exF += x.x & 0xFFFF;
-                nf_ += x.x & 0xFFFF; remj += x.x >> 16; ns_ += x.y & 0xFFFF; nr_ += x.y >> 16;
-                flags |= x.w & 15; either += x.w >> 8;
+            const int mine4 = (ballot64(as) != 0 ? 1 : 0) | (ballot64(ar) != 0 ? 16 : 0) | (ballot64(any) != 0 ? 256 : 0) |
+                              (ballot64(cand) != 0 ? 4096 : 0) | (two << 16);
+            int4 theirs;
+            if (kWaves > 1) {
+                const int4 *const part = partial(scanF, sumO, mine4);
+                theirs = part[lane & (kWaves - 1)];                        // lane w of eight has wavefront w's sums
+            } else {
+                theirs = make_int4(__builtin_amdgcn_readlane(scanF, kWave - 1), __builtin_amdgcn_readlane(sumO, kWave - 1), 0, mine4);
             }
-            flags = __builtin_amdgcn_readfirstlane(flags); either = __builtin_amdgcn_readfirstlane(either);
-            nf_ = __builtin_amdgcn_readfirstlane(nf_); remj = __builtin_amdgcn_readfirstlane(remj);
-            ns_ = __builtin_amdgcn_readfirstlane(ns_); nr_ = __builtin_amdgcn_readfirstlane(nr_);
-            anySender = (flags & 4) != 0;
+            if (!past && j + 1 < q) fetch(j + 1);                          // on its way while this visit goes on
+            auto total = [&](int v) { return kWaves > 1 ? __builtin_amdgcn_readfirstlane(dpp_sum8(v)) : v; };
+            const int flags = total(theirs.w), either = flags >> 16;
+            const int nf_ = total(theirs.x & 0xFFFF), remj = total(static_cast<int>(static_cast<uint32_t>(theirs.x) >> 16)) - 1;
+            const int ns_ = total(theirs.y & 0xFFFF), nr_ = total(static_cast<int>(static_cast<uint32_t>(theirs.y) >> 16));
+            anySender = (flags & 0xF00) != 0;
             if (past) break;
             // a pair needs a free send port and a free receive port on two different processors: without them only the last
             // segment, whose shorter transfer is kept out by fewer pending computations, is left to try
-            if ((flags & 3) != 3 || either < 2) {
+            if ((flags & 0xF) == 0 || (flags & 0xF0) == 0 || either < 2) {
                 if (last) break;
                 j = q - 1;
                 continue;
@@ -597,37 +632,35 @@ __device__ bool run_bi_wide(const Config<T> &c, int4 *red, uint64_t *rows, uint6
             if (l == 0) {
                 // nobody paired although no candidate had already sent the segment: the candidates of later segments are a
                 // subset of these, so only the last one can still pair at this t
-                if ((flags & 8) == 0) {
+                if ((flags & 0xF000) == 0) {
                     if (last) break;
                     j = q - 1;
                 }
                 continue;
             }
+            // First l entries of each list.  Either the free processors even the lists out: the first of them receive, the last
+            // send, an odd one in between does neither.  Or there are too few of them: all join the shorter list, and the longer
+            // one, which has none, is cut.  So one search for a place is enough, and the places before my words are known
+            // without another sum over the block.
+            int exF = (scanF & 0xFFFF) - pf, exS = (sumO & 0xFFFF) - pso, exR = static_cast<int>(static_cast<uint32_t>(sumO) >> 16) - pro;
+            if (kWaves > 1) {
+                const bool before = (lane & (kWaves - 1)) < wave;
+                exF += dpp_sum8(before ? theirs.x & 0xFFFF : 0); exS += dpp_sum8(before ? theirs.y & 0xFFFF : 0);
+                exR += dpp_sum8(before ? static_cast<int>(static_cast<uint32_t>(theirs.y) >> 16) : 0);
+            }
             uint64_t sset[K], rset[K];
-            int ps = 0, pr = 0;
+            const bool cutS = sN > l, cutR = rN > l;
+            const int odd = nf_ - toSendLast - toRecvFirst;
+            const int posS = exS + (exF > nf_ - toSendLast ? exF - (nf_ - toSendLast) : 0), posR = exR + (exF < toRecvFirst ? exF : toRecvFirst);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const int n = __popcll(fr[k]);
-                sset[k] = so[k] | highest_bits(fr[k], exF + n - (nf_ - toSendLast));
-                rset[k] = ro[k] | lowest_bits(fr[k], toRecvFirst - exF);
-                exF += n;
-                ps += __popcll(sset[k]); pr += __popcll(rset[k]);
-            }
-            int exS = 0, exR = 0;
-            if (kSched || sN != l || rN != l) {                            // first l entries of each list
-                const int scan = dpp_inclusive_scan(ps | (pr << 16));
-                const int4 *const cut = partial(scan, 0, 0);
-                exS = (scan & 0xFFFF) - ps; exR = (scan >> 16) - pr;
-#pragma unroll
-                for (int w = 0; w < kBlockWaves; ++w)
-                    if (w < wave) { const int x = cut[w].x; exS += x & 0xFFFF; exR += x >> 16; }
-                int es = exS, er = exR;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const int ns1 = __popcll(sset[k]), nr1 = __popcll(rset[k]);
-                    sset[k] = lowest_bits(sset[k], l - es); rset[k] = lowest_bits(rset[k], l - er);
-                    es += ns1; er += nr1;
-                }
+                const uint64_t firsts = lowest_bits_of_few(cutS ? so[k] : (cutR ? ro[k] : fr[k]), cutS ? l - exS : (cutR ? l - exR : toRecvFirst - exF), lane);
+                uint64_t rest = fr[k] & ~firsts;
+                if (odd != 0 && exF <= toRecvFirst && toRecvFirst < exF + n) rest &= rest - 1;
+                sset[k] = cutS ? firsts : so[k] | (cutR ? fr[k] : rest);
+                rset[k] = cutR ? firsts : ro[k] | (cutS ? fr[k] : firsts);
+                exF += n; exS += __popcll(so[k]); exR += __popcll(ro[k]);
             }
             const T cj = last ? c.c_last : c.c_full, gj = last ? c.g_last : c.g_full;
             const T tc = t + cj, tr = tc + gj;
@@ -635,11 +668,11 @@ __device__ bool run_bi_wide(const Config<T> &c, int4 *red, uint64_t *rows, uint6
             if ((active & full) == full) return false;
             if (kSched) {                                                  // e-th sender pairs with e-th receiver
                 const int64_t o = out_base + emitted;
-                for (int e = tid; e < l; e += kBlockThreads) {
+                for (int e = tid; e < l; e += kThreads) {
                     if (sched.seg) sched.seg[o + e] = at;
                     if (sched.tstart) static_cast<T *>(sched.tstart)[o + e] = t;
                 }
-                int32_t *src = sched.src ? sched.src + (o + exS) : nullptr, *dst = sched.dst ? sched.dst + (o + exR) : nullptr;
+                int32_t *src = sched.src ? sched.src + (o + posS) : nullptr, *dst = sched.dst ? sched.dst + (o + posR) : nullptr;
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     const int base = (w0 + k) * 64;
@@ -684,6 +717,7 @@ __global__ __launch_bounds__(kBlockThreads) void bi_block_kernel(ConfigArrays cf
 {
     PRS_DYNAMIC_LDS(lds_raw);
     __shared__ long long s_ticket;
+    __shared__ int s_done;
     const int tid = static_cast<int>(threadIdx.x);
     char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
     const BlockSlot sl = bi_block_slot(state_p, state_q);
@@ -708,9 +742,22 @@ __global__ __launch_bounds__(kBlockThreads) void bi_block_kernel(ConfigArrays cf
         T result = CostTraits<T>::bad();
         if (status == PRS_CFG_OK) {
             bool done = false;
-            if (c.p <= kBlockThreads * K * 64)                             // always, where this kernel is launched
-                done = run_bi_wide<T, kSched, K>(c, red, reinterpret_cast<uint64_t *>(slot + sl.sent), reinterpret_cast<uint64_t *>(slot + sl.sets),
-                                                 entries, sched, base, &result, &status);
+            uint64_t *const rows = reinterpret_cast<uint64_t *>(slot + sl.sent), *const sets = reinterpret_cast<uint64_t *>(slot + sl.sets);
+            const int per_lane = (c.p + kWave * 64 - 1) / (kWave * 64);    // words of a set per lane of one wavefront
+            if (per_lane <= kAloneWords) {
+                if (tid < kWave) {
+                    if (per_lane <= 1) done = run_bi_wide<T, kSched, 1, 1>(c, red, rows, sets, entries, sched, base, &result, &status);
+                    else if (per_lane <= 2) done = run_bi_wide<T, kSched, 2, 1>(c, red, rows, sets, entries, sched, base, &result, &status);
+                    else done = run_bi_wide<T, kSched, kAloneWords, 1>(c, red, rows, sets, entries, sched, base, &result, &status);
+                    if (tid == 0) s_done = done ? 1 : 0;
+                }
+                __syncthreads();
+                done = s_done != 0;
+            } else if (c.p <= kBlockThreads * 64) {
+                done = run_bi_wide<T, kSched, 1, kBlockWaves>(c, red, rows, sets, entries, sched, base, &result, &status);
+            } else if (c.p <= kBlockThreads * K * 64) {                    // always, where this kernel is launched
+                done = run_bi_wide<T, kSched, K, kBlockWaves>(c, red, rows, sets, entries, sched, base, &result, &status);
+            }
             if (!done) {
                 __syncthreads();
                 result = run_bi_block<T, kSched>(c, lds_raw, slot, sl, Wc, sched, base, &status);

@@ -743,6 +743,29 @@ def test_bi_schedules_around_the_words_per_thread(prs, cost, entries):
 
 
 @pytest.mark.parametrize("entries", [0, 2])
+@pytest.mark.parametrize("cost", ["i64", "f64"])
+def test_bi_schedules_on_one_wavefront_and_on_eight(prs, cost, entries):
+    """Bi-greedy on thousands of processors: the last machine with one, two and four words of a set per lane of a wavefront of its own
+    and the next one each, the first on the whole block; equal and smaller last segments, lists that have to be cut and
+    lists that free processors even out, odd and even; handed over with the list of running transfers cut to two entries."""
+    p = np.array([1025, 4095, 4096, 4097, 8191, 8192, 8193, 16383, 16384, 16385, 3000, 5001], np.int32)
+    q = np.array([37, 5, 4, 6, 3, 4, 3, 2, 3, 3, 21, 12], np.int32)
+    per = np.array([4, 3, 5, 2, 6, 1, 7, 3, 4, 5, 9, 2], np.int64)
+    m = q * per - np.array([0, 2, 0, 1, 5, 0, 6, 1, 0, 3, 8, 0])
+    rng = np.random.default_rng(1313)
+    if cost == "i64":
+        al, be, ga = rng.integers(0, 6, 12), rng.integers(1, 4, 12), rng.integers(0, 4, 12)
+    else:
+        al, be, ga = 10.0 ** rng.uniform(-6, -4, 12), 10.0 ** rng.uniform(-7, -5, 12), 10.0 ** rng.uniform(-7, -5, 12)
+    host = prs_inputs.SweepConfigs(p, q, m, al, be, ga, cost)
+    tuning = {"bi_list_entries": entries} if entries else None
+    got = prs.simulate_completion_batch(prs.DeviceConfigs.from_host(host), 1, 16385, 64, tuning=tuning)
+    _sync()
+    _check_times(got, O.simulate_batch(host, 1), exact=cost == "i64")
+    _check_schedules(prs, host, 1, 16385, 64, tuning=tuning)
+
+
+@pytest.mark.parametrize("entries", [0, 2])
 def test_bi_three_words_per_thread(prs, entries):
     """The block kernel for batches whose bound passes 65536 processors: the first and the last machine with three words per
     thread, and machines with one and two in the same batch; with the list of running transfers cut to two entries they
