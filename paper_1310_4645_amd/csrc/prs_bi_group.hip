@@ -12,7 +12,9 @@
 //    candidate sets) is a bit-sliced counter: bit b of all 64 counts in one word;
 //  - M(i,j) "i has sent j" is one bit-set row per segment in the workspace;
 //  - pairing e-th sender with e-th receiver needs no lists: each sender writes its pair record at
-//    its rank among the senders, each receiver its own index at its rank among the receivers.
+//    its rank among the senders, each receiver its own index at its rank among the receivers.  One search for a place in a word
+//    finds both lists of a visit, one sum and one prefix sum their lengths and places (four searches, two sums and two prefix
+//    sums: 15.9 instead of 14.7 ms on the 100,000-configuration sweep, schedules 27.0 instead of 26.4).
 // The visit itself is the same sequence of set operations as in the one-configuration kernel.
 // All lanes run one flat loop in which a group either visits the next segment or advances time, so
 // groups at different times and segments share the same instructions.
@@ -352,17 +354,16 @@ __device__ __forceinline__ void bi_group_body(char *lds_raw, int block, const Co
                 const uint64_t comp = last ? compL : compF;
                 const uint64_t sOK = memb & ~comp & sfree, rOK = memb & ~comp & rfree & ~(last ? lateL : UINT64_C(0));
                 const uint64_t fr = sOK & rOK, so = sOK ^ fr, ro = rOK ^ fr;
-                const int pf = __popcll(fr);
-                // counts of up to 1024 processors travel two to a sum
-                const int memb_free = group_sum<LPC>(__popcll(memb & ~rootbit) | (pf << 16));
-                int remj = memb_free & 0xFFFF;
-                const int nf_ = memb_free >> 16;
+                // The three lists have no processor in common and the root, which never sends, is in neither of the first two: their
+                // counts (up to 1023, 1023 and 1024) travel in one sum.
+                const int pf = __popcll(fr), lists = pf | (__popcll(so) << 10) | static_cast<int>(static_cast<unsigned>(__popcll(ro)) << 20);
+                int remj = group_sum<LPC>(__popcll(memb & ~rootbit));
                 if (remj == 0) {                                          // everybody has sent segment j
                     if (j == segStart) ++segStart;
                     ++j;
                 } else {
-                    const int send_recv = group_sum<LPC>(__popcll(so) | (__popcll(ro) << 16));
-                    const int ns_ = send_recv & 0xFFFF, nr_ = send_recv >> 16;
+                    const unsigned all = static_cast<unsigned>(group_sum<LPC>(lists));
+                    const int nf_ = static_cast<int>(all & 1023), ns_ = static_cast<int>((all >> 10) & 1023), nr_ = static_cast<int>(all >> 20);
                     int toSendLast, toRecvFirst;                          // free processors go to the shorter list
                     if (ns_ == nr_) {
                         toSendLast = toRecvFirst = nf_ / 2;
@@ -376,14 +377,20 @@ __device__ __forceinline__ void bi_group_body(char *lds_raw, int block, const Co
                     const int sN = ns_ + toSendLast, rN = nr_ + toRecvFirst;
                     const int l = sN < rN ? sN : rN;
                     if (l > 0) {
-                        const int exF = group_exclusive_scan<LPC>(pf, gl);
-                        const uint64_t frR = lowest_bits(fr, toRecvFirst - exF);
-                        const uint64_t frS = highest_bits(fr, exF + pf - (nf_ - toSendLast));
-                        uint64_t sset = so | frS, rset = ro | frR;
-                        const int exSR = group_exclusive_scan<LPC>(__popcll(sset) | (__popcll(rset) << 16), gl);
-                        const int exS = exSR & 0xFFFF, exR = exSR >> 16;
-                        sset = lowest_bits(sset, l - exS);                // first l entries of each list
-                        rset = lowest_bits(rset, l - exR);
+                        // First l entries of each list.  Either the free processors even the lists out: the first of them receive,
+                        // the last send, an odd one in between does neither.  Or there are too few of them: all join the shorter
+                        // list, and the longer one, which has none, is cut.  So one search for a place is enough.
+                        const unsigned before = static_cast<unsigned>(group_exclusive_scan<LPC>(lists, gl));
+                        const int exF = static_cast<int>(before & 1023), exSo = static_cast<int>((before >> 10) & 1023),
+                                  exRo = static_cast<int>(before >> 20);
+                        const bool cutS = sN > l, cutR = rN > l;
+                        const uint64_t firsts = lowest_bits(cutS ? so : (cutR ? ro : fr), cutS ? l - exSo : (cutR ? l - exRo : toRecvFirst - exF));
+                        uint64_t rest = fr & ~firsts;
+                        const bool odd = nf_ - toSendLast != toRecvFirst && exF <= toRecvFirst && toRecvFirst < exF + pf;
+                        rest = odd ? rest & (rest - 1) : rest;
+                        const uint64_t sset = cutS ? firsts : so | (cutR ? fr : rest), rset = cutR ? firsts : ro | (cutS ? fr : firsts);
+                        // places of the word's first entries in the two lists
+                        const int exS = exSo + (exF > nf_ - toSendLast ? exF - (nf_ - toSendLast) : 0), exR = exRo + (exF < toRecvFirst ? exF : toRecvFirst);
                         const T cj = last ? c.c_last : c.c_full, gj = last ? c.g_last : c.g_full;
                         const T tc = t + cj, tr = tc + gj;
                         if (!(tc > t)) status = PRS_CFG_STALLED;

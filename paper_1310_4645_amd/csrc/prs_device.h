@@ -264,25 +264,31 @@ __device__ __forceinline__ int64_t next_ticket(unsigned long long *counter)
 // keep the k lowest set bits of mask (k <= 0: none, k >= popcount: all)
 __device__ __forceinline__ uint64_t lowest_bits(uint64_t mask, int k)
 {
-    // all of them or none: the usual case for all but one word of a set, and a wavefront of such words skips the search
     const uint32_t lo = static_cast<uint32_t>(mask), hi = static_cast<uint32_t>(mask >> 32);
     const int plo = __builtin_popcount(lo), phi = __builtin_popcount(hi);
-    if (k <= 0) return 0;
-    if (k >= plo + phi) return mask;
-    // on the 32-bit half that holds the k-th set bit
-    const bool in_lo = k <= plo;
-    const uint32_t w = in_lo ? lo : hi;
-    int kk = in_lo ? k : k - plo;
-    uint32_t pos = 0;                  // after the loop: index of the kk-th set bit of w
+    const bool part = (k > 0) & (k < plo + phi);
+    uint64_t some = k > 0 ? mask : 0;
+    // all of them or none: the usual case for all but one word of a set, and a wavefront of such words skips the search
+    if (ballot64(part) != 0) {
+        PRS_KEEP_BRANCH();
+        // A search for the place of the k-th set bit in steps of 32, 16, .. 1 without comparisons: one that depends on a comparison
+        // costs a wavefront that is alone on its SIMD 19 cycles, other dependent instructions 7.  left = -(bits still to be passed);
+        // d = left + (bits in the lower half of the range) < 0: the place is in the upper half.
+        const int d0 = plo - k;
+        const uint32_t upper = static_cast<uint32_t>(d0 >> 31);                 // all ones: in hi
+        uint32_t w = (hi & upper) | (lo & ~upper);
+        uint32_t left = static_cast<uint32_t>(d0) > static_cast<uint32_t>(-k) ? static_cast<uint32_t>(d0) : static_cast<uint32_t>(-k);
+        uint32_t pos = 0;
 #pragma unroll
-    for (uint32_t width = 16; width > 0; width >>= 1) {
-        const int cnt = __builtin_popcount((w >> pos) & ((1u << width) - 1));
-        const bool up = cnt < kk;
-        pos += up ? width : 0;
-        kk -= up ? cnt : 0;
+        for (uint32_t width = 16; width > 0; width >>= 1) {
+            const uint32_t d = static_cast<uint32_t>(__builtin_popcount(__builtin_amdgcn_ubfe(w, pos, width))) + left;
+            left = d > left ? d : left;                                         // unsigned: d if it is negative, else left
+            pos |= static_cast<uint32_t>(static_cast<int32_t>(d) >> 31) & width;
+        }
+        const uint32_t upto = (2u << pos) - 1;
+        const uint64_t found = (static_cast<uint64_t>(hi & upto & upper) << 32) | (lo & (upto | upper));
+        some = part ? found : some;
     }
-    const uint32_t part = w & ((2u << pos) - 1);
-    const uint64_t some = in_lo ? static_cast<uint64_t>(part) : (static_cast<uint64_t>(part) << 32) | lo;
     return some;
 }
 
