@@ -87,6 +87,16 @@ template <typename T, int kSmallRuns> __device__ __forceinline__ void lds_load(i
     if (kSmallRuns > 0) { v = *lds_at<T>(at); n = *lds_at<uint16_t>((at >> 2) + kSmallRuns * 8); }
     else { const auto *e = lds_at<Run<T>>(at); v = e->v; n = e->n; }
 }
+template <typename T, int kSmallRuns> __device__ __forceinline__ void lds_value(int32_t at, T &v)
+{
+    if (kSmallRuns > 0) v = *lds_at<T>(at);
+    else v = lds_at<Run<T>>(at)->v;
+}
+template <typename T, int kSmallRuns> __device__ __forceinline__ void lds_count(int32_t at, int32_t &n)
+{
+    if (kSmallRuns > 0) n = *lds_at<uint16_t>((at >> 2) + kSmallRuns * 8);
+    else n = lds_at<Run<T>>(at)->n;
+}
 template <typename T, int kSmallRuns> __device__ __forceinline__ void lds_store(int32_t at, T v, int32_t n)
 {
     if (kSmallRuns > 0) { *lds_at<T>(at) = v; *lds_at<uint16_t>((at >> 2) + kSmallRuns * 8) = static_cast<uint16_t>(n); }
@@ -286,14 +296,18 @@ __device__ __forceinline__ void uni_times_body(const RingShape &shape, const Con
                         slot_load<T, kPacked>(slot, counts, aat, va, na);
                         slot_load<T, kPacked>(slot, counts, bat, vb, nb);
                     } else {
-                        lds_load<T, kSmallRuns>(aat, va, na);
-                        lds_load<T, kSmallRuns>(bat, vb, nb);
+                        lds_value<T, kSmallRuns>(aat, va);
+                        lds_value<T, kSmallRuns>(bat, vb);
+                        asm volatile("" ::: "memory");                // the values first: the counts come while they are compared (sweep 3.45 -> 3.41 ms)
+                        lds_count<T, kSmallRuns>(aat, na);
+                        lds_count<T, kSmallRuns>(bat, nb);
                     }
-                    asm volatile("" : "+v"(va), "+v"(vb), "+v"(na), "+v"(nb));       // the loads stay together, outside the branches below
+                    asm volatile("" : "+v"(va), "+v"(vb) : : "memory");              // the loads stay outside the branches below
                     const bool avail = aat != upto;                   // else va is the value of the open run: a bound of what follows
                     const T a = or_absent<T>(aleft > 0, va), b = or_absent<T>(bat != wat, wrap_add<T>(vb, gg));
                     const bool le = a <= b, ge = b <= a, go = room & (left > 0);
                     const bool takeA = go & avail & le, takeB = go & ge & (avail | !le);
+                    asm volatile("" : "+v"(na), "+v"(nb));
                     const int an = takeA ? na : 0, x = odd + an + (takeB ? nb : 0), pairs = x >> 1;
                     odd = x & 1;
                     aleft -= an;
