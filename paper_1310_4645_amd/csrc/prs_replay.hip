@@ -92,15 +92,14 @@ hipError_t replay_static_scratch(void **ptr)
     return hipSuccess;
 }
 
-__global__ void replay_clear_flags(int32_t *flags) { if (threadIdx.x < 3) flags[threadIdx.x] = 0; }
-
-// Segment offsets travel as kernel arguments, a chunk at a time: no host-to-device copy is enqueued.
+// Segment offsets travel as kernel arguments, a chunk at a time: no host-to-device copy is enqueued.  The first chunk clears the flags.
 constexpr int kOffsetChunk = 256;
 struct OffsetChunk { int64_t v[kOffsetChunk]; };
-__global__ void replay_store_offsets(OffsetChunk chunk, int base, int count, int64_t *dst)
+__global__ void replay_store_offsets(OffsetChunk chunk, int base, int count, int64_t *dst, int32_t *flags)
 {
     const int i = threadIdx.x;
     if (i < count) dst[base + i] = chunk.v[i];
+    if (base == 0 && i < 3) flags[i] = 0;
 }
 
 // One block per segment: tree of the segment's pairs -> linear program.  The eight work arrays of p entries
@@ -342,8 +341,10 @@ __device__ __forceinline__ void store_elems(E *ptr, const Acc<E, VEC> &a, int nv
 // (row | push << 20 | pops << 21), the same for every thread of a block.  The partial sums a push saves sit
 // in LDS ([depth][thread], 16 bytes per thread and level), so the registers are free for the loads: two
 // groups of kPrefetch rows are in flight while the group before them is added up.  The LDS allocation fixes
-// the depth D (8, 16 or 24 levels, the fewer the more blocks fit on a CU); every variant is launched and only
-// the one that fits the schedule's trees (flags[2], found by replay_build) runs.
+// the depth (8, 16 or 24 levels, the fewer the more blocks fit on a CU).  Where that matters every depth is launched and only
+// the one that fits the schedule's trees (flags[2], found by replay_build: more than `above`, at most `levels`) runs; where all
+// blocks of the grid are resident with 24 levels only that one is launched (three launches instead of seven, 33 -> 27 us on 37 x
+// 100,003 32-bit elements).  The first launch writes the status.
 template <typename E, int VEC, int OP>
 __device__ __forceinline__ void replay_step(Acc<E, VEC> &acc, int &sp, E *stk, uint32_t ent, const Acc<E, VEC> &val)
 {
@@ -366,16 +367,17 @@ __device__ __forceinline__ void replay_step(Acc<E, VEC> &acc, int &sp, E *stk, u
     }
 }
 
-template <typename E, int VEC, int D, int OP>
+template <typename E, int VEC, int OP>
 __global__ __launch_bounds__(kReplayThreads) void replay_kernel(int32_t p, const int64_t *__restrict__ offsets,
                                                                 const uint32_t *__restrict__ prog, const E *__restrict__ in,
                                                                 int64_t stride, E *__restrict__ out,
-                                                                const int32_t *__restrict__ flags)
+                                                                const int32_t *__restrict__ flags, int above, int levels, int32_t *status)
 {
     PRS_DYNAMIC_LDS(lds_raw);
+    if (status && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *status = flags[0] ? 1 : (flags[1] ? 2 : 0);
     if (flags[0] | flags[1]) return;
     const int need = flags[2];
-    if (need > D || need <= D - 8) return;                     // another depth variant takes this schedule
+    if (need > levels || need <= above) return;                // another launch takes this schedule
     // Workgroups go to the eight XCDs in turn (workgroup b to XCD b mod 8): the tiles are renumbered so that each
     // XCD streams one contiguous eighth of the (segment, chunk) tiles instead of every eighth 2 KB chunk.
     const unsigned tiles = gridDim.x * gridDim.y, b = blockIdx.y * gridDim.x + blockIdx.x;
@@ -437,6 +439,12 @@ __global__ void replay_write_status(const int32_t *flags, int32_t *status)
 }
 
 static size_t replay_lds_bytes(int vec, int depth, size_t elem) { return static_cast<size_t>(depth) * kReplayThreads * vec * elem; }
+// blocks that 256 CUs hold at once: 160 KB of LDS in units of 2560 bytes, 32 wavefronts
+static int64_t replay_resident_blocks(size_t lds)
+{
+    const int64_t by_lds = static_cast<int64_t>(160 * 1024 / ((lds + 2559) / 2560 * 2560)), by_waves = 32 * kWave / kReplayThreads;
+    return 256 * (by_lds < by_waves ? by_lds : by_waves);
+}
 
 template <typename E, int VEC, int OP>
 static void launch_replay_depths(const ReplayLaunch &L, const ReplayWs &w, int64_t max_len)
@@ -445,12 +453,17 @@ static void launch_replay_depths(const ReplayLaunch &L, const ReplayWs &w, int64
     E *out = static_cast<E *>(L.out);
     const int64_t groups = (max_len + VEC - 1) / VEC;
     dim3 grid(static_cast<unsigned>((groups + kReplayThreads - 1) / kReplayThreads), static_cast<unsigned>(L.q));
-    hipLaunchKernelGGL((replay_kernel<E, VEC, 8, OP>), grid, dim3(kReplayThreads), replay_lds_bytes(VEC, 8, sizeof(E)), L.stream, L.p,
-                       w.offsets, w.prog, in, L.stride_elems, out, w.flags);
-    hipLaunchKernelGGL((replay_kernel<E, VEC, 16, OP>), grid, dim3(kReplayThreads), replay_lds_bytes(VEC, 16, sizeof(E)), L.stream, L.p,
-                       w.offsets, w.prog, in, L.stride_elems, out, w.flags);
-    hipLaunchKernelGGL((replay_kernel<E, VEC, 24, OP>), grid, dim3(kReplayThreads), replay_lds_bytes(VEC, 24, sizeof(E)), L.stream, L.p,
-                       w.offsets, w.prog, in, L.stride_elems, out, w.flags);
+    auto launch = [&](int above, int levels, int32_t *status) {
+        hipLaunchKernelGGL((replay_kernel<E, VEC, OP>), grid, dim3(kReplayThreads), replay_lds_bytes(VEC, levels, sizeof(E)), L.stream, L.p,
+                           w.offsets, w.prog, in, L.stride_elems, out, w.flags, above, levels, status);
+    };
+    if (static_cast<int64_t>(grid.x) * grid.y <= replay_resident_blocks(replay_lds_bytes(VEC, kStackDepth, sizeof(E)))) {
+        launch(0, kStackDepth, L.status);
+    } else {
+        launch(0, 8, L.status);
+        launch(8, 16, nullptr);
+        launch(16, kStackDepth, nullptr);
+    }
 }
 
 template <typename E>
@@ -485,9 +498,8 @@ hipError_t launch_replay(const ReplayLaunch &L)
         OffsetChunk chunk;
         const int count = L.q + 1 - base < kOffsetChunk ? L.q + 1 - base : kOffsetChunk;
         for (int i = 0; i < count; ++i) chunk.v[i] = L.seg_elem_offset[base + i];
-        hipLaunchKernelGGL(replay_store_offsets, dim3(1), dim3(kOffsetChunk), 0, L.stream, chunk, base, count, w.offsets);
+        hipLaunchKernelGGL(replay_store_offsets, dim3(1), dim3(kOffsetChunk), 0, L.stream, chunk, base, count, w.offsets, w.flags);
     }
-    hipLaunchKernelGGL(replay_clear_flags, dim3(1), dim3(64), 0, L.stream, w.flags);
     const size_t build_lds = static_cast<size_t>(L.p) * 8 * 4;
     if (L.p <= kBuildLdsProcs)
         hipLaunchKernelGGL(replay_build<true>, dim3(static_cast<unsigned>(L.q)), dim3(kBuildThreads), build_lds, L.stream, L.p, L.q,
@@ -502,8 +514,8 @@ hipError_t launch_replay(const ReplayLaunch &L)
     case PRS_I64: err = launch_replay_t<int64_t>(L, w, max_len, vec_ok); break;
     default: err = launch_replay_t<int32_t>(L, w, max_len, vec_ok); break;
     }
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(replay_write_status, dim3(1), dim3(64), 0, L.stream, w.flags, L.status);
+    if (err != hipSuccess || max_len > 0) return err;
+    hipLaunchKernelGGL(replay_write_status, dim3(1), dim3(64), 0, L.stream, w.flags, L.status);   // no elements: nothing else writes it
     return hipGetLastError();
 }
 

@@ -1143,6 +1143,24 @@ def test_replay_of_baseline_trees(prs, tree):
             _replay_pairs(prs, p, q, build(p, q), off, dtype)
 
 
+@pytest.mark.parametrize("n", [4 * 128 * 3, 4 * 128 * 768, 4 * 128 * 768 + 4])
+@pytest.mark.parametrize("depth", [1, 8, 9, 16, 17, 24, 25])
+def test_replay_depths_in_one_launch_and_in_three(prs, depth, n):
+    """Trees that save `depth` partial results at once (a chain whose members each take in a leaf first), grids whose blocks are all
+    resident and the first one whose blocks are not: the result, and the status where it is too deep."""
+    import torch
+    p = 2 * depth
+    src = np.concatenate([np.arange(depth) + depth, np.arange(depth - 1, 0, -1)]).astype(np.int32)
+    dst = np.concatenate([np.arange(depth), np.arange(depth - 1, 0, -1) - 1]).astype(np.int32)
+    seg, off = np.zeros(p - 1, np.int32), np.array([0, n], np.int64)
+    buf = np.random.default_rng(depth).integers(-1000, 1000, (p, n)).astype(np.float32) * np.float32(1.1)
+    out, status = prs.replay_reduction(p, 1, off, *(torch.from_numpy(a).cuda() for a in (src, dst, seg, buf)))
+    _sync()
+    assert int(status.item()) == (2 if depth > 24 else 0)
+    if depth <= 24:
+        assert _np(out).tobytes() == O.replay(p, off, src, dst, seg, buf).tobytes()
+
+
 def test_replay_rejects_a_schedule_that_is_not_a_tree(prs):
     import torch
     p, q = 4, 1
