@@ -109,11 +109,76 @@ __global__ __launch_bounds__(kPlanThreads) void plan_scatter(ConfigArrays cfg, i
     if (i < n) order[local[b] + rank] = static_cast<int32_t>(i);
 }
 
+// All four steps in one block for batches of up to kPlanSmall configurations: three launches less, each of which is waited for
+// (960 machines, both port models: 249 -> 236 us in two calls).
+constexpr int kPlanSmallThreads = 1024, kPlanSmall = 4 * kPlanSmallThreads;
+template <typename T>
+__global__ __launch_bounds__(kPlanSmallThreads) void plan_small(ConfigArrays cfg, int n, int32_t p_max, int32_t q_max, ClassLimits lim, int n_classes,
+                                                                PlanHeader *h, int32_t *order)
+{
+    __shared__ int32_t place[kPlanBins + 1];
+    __shared__ int32_t several;
+    const int tid = static_cast<int>(threadIdx.x), lane = lane_id(), bins = n_classes * kWorkBuckets;
+    for (int k = tid; k <= kPlanBins; k += kPlanSmallThreads) place[k] = 0;
+    if (tid == 0) several = 0;
+    __syncthreads();
+    int b[kPlanSmall / kPlanSmallThreads];
+#pragma unroll
+    for (int u = 0; u < kPlanSmall / kPlanSmallThreads; ++u) {
+        const int i = tid + u * kPlanSmallThreads;
+        b[u] = 0;
+        if (i < n) {
+            b[u] = plan_bucket<T>(cfg, i, p_max, q_max, lim);
+            atomicAdd(&place[b[u]], 1);
+            if (!lim.by_work && cfg.q_req[i] > 1) several = 1;
+        }
+    }
+    __syncthreads();
+    if (tid < kWave) {                                                   // counts into places, the end of the last bin behind them
+        int32_t run = 0;
+        for (int at = 0; at < bins; at += kWave) {
+            const int k = at + lane;
+            const int32_t c = k < bins ? place[k] : 0, upto = run + wave_inclusive_scan(c);
+            if (k < bins) place[k] = upto - c;
+            run = __shfl(upto, kWave - 1, kWave);
+        }
+        if (lane == 0) place[bins] = run;
+    }
+    __syncthreads();
+    if (tid < kPlanClasses) {
+        const bool used = tid < n_classes;
+        const int32_t first = used ? place[tid * kWorkBuckets] : 0;
+        h->ticket[tid] = 0ULL;
+        h->class_begin[tid] = first;
+        h->class_count[tid] = used ? place[(tid + 1) * kWorkBuckets] - first : 0;
+    }
+    if (tid < 2) {
+        const int last = tid == 0 ? kClasses - 1 : kLargeClass + kClasses - 1, giants = kWorkBuckets - lim.giant_log2[tid];
+        h->ticket_giant[tid] = 0ULL;
+        h->giant_count[tid] = last < n_classes && giants > 0 ? place[last * kWorkBuckets + giants] - place[last * kWorkBuckets] : 0;
+    }
+    if (tid == 0) {
+        h->large_left = kLargeClass < n_classes ? place[bins] - place[kLargeClass * kWorkBuckets] : 0;
+        h->several = several;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPlanSmall / kPlanSmallThreads; ++u) {
+        const int i = tid + u * kPlanSmallThreads;
+        if (i < n) order[atomicAdd(&place[b[u]], 1)] = i;
+    }
+}
+
 template <typename T> static void launch_plan_as(const PlanLaunch &L)
 {
     const unsigned blocks = static_cast<unsigned>((L.n + kPlanThreads - 1) / kPlanThreads);
     const ClassLimits &lim = L.limits;
     const int classes = !lim.by_work ? kClasses : lim.large_p > 0 ? kPlanClasses : lim.wide_p > 0 ? kWideClass + 1 : kClasses;
+    if (L.n <= kPlanSmall) {
+        hipLaunchKernelGGL((plan_small<T>), dim3(1), dim3(kPlanSmallThreads), 0, L.stream, L.cfg, static_cast<int>(L.n), L.p_max, L.q_max, lim, classes,
+                           L.header, L.order);
+        return;
+    }
     hipLaunchKernelGGL(plan_clear, dim3(1), dim3(256), 0, L.stream, L.header);
     hipLaunchKernelGGL((plan_hist<T>), dim3(blocks), dim3(kPlanThreads), 0, L.stream, L.cfg, L.n, L.p_max, L.q_max, lim, classes * kWorkBuckets, L.header);
     hipLaunchKernelGGL(plan_scan, dim3(1), dim3(kWave), 0, L.stream, L.header, lim.giant_log2[0], lim.giant_log2[1], classes);

@@ -1143,6 +1143,28 @@ def test_replay_of_baseline_trees(prs, tree):
             _replay_pairs(prs, p, q, build(p, q), off, dtype)
 
 
+@pytest.mark.parametrize("model", [0, 1])
+@pytest.mark.parametrize("n", [1, 1023, 1025, 4096, 4097])
+def test_plan_in_one_block_and_in_several_kernels(prs, model, n):
+    """Batches around the sizes at which one thread of the plan takes the next configuration and at which the plan takes several kernels:
+    every group size, machines above 1024 processors, configurations that are refused; times bit for bit, status of each."""
+    rng = np.random.default_rng(n + model)
+    p = np.minimum(2 ** rng.integers(1, 7, n) + rng.integers(0, 3, n), 60).astype(np.int32)
+    q = rng.integers(1, 7, n).astype(np.int32)
+    if n > 1:
+        p[:12] = [64, 65, 128, 129, 256, 257, 512, 513, 1024, 1025, 1100, 3]
+        q[:12] = [3, 2, 3, 2, 3, 2, 3, 2, 2, 2, 3, 1]
+        p[n // 2], q[n // 3] = 1, 0
+    host = prs_inputs.SweepConfigs(p, q, np.maximum(q, 1) * 2 - rng.integers(0, 2, n), rng.integers(0, 5, n), np.ones(n, np.int64),
+                                   rng.integers(0, 3, n), "i64")
+    got = prs.simulate_completion_batch(prs.DeviceConfigs.from_host(host), model, 1100, 8)
+    _sync()
+    ok = (p >= 2) & (q >= 1)
+    assert np.array_equal(_np(got["cfg_status"]) == 0, ok) and np.all(_np(got["greedy"])[~ok] == -1)
+    ref = O.simulate_batch(host.take(np.nonzero(ok)[0]), model)
+    assert np.array_equal(_np(got["greedy"])[ok], ref.T_greedy) and np.array_equal(_np(got["q_eff"])[ok], ref.q_eff)
+
+
 @pytest.mark.parametrize("n", [4 * 128 * 3, 4 * 128 * 768, 4 * 128 * 768 + 4])
 @pytest.mark.parametrize("depth", [1, 8, 9, 16, 17, 24, 25])
 def test_replay_depths_in_one_launch_and_in_three(prs, depth, n):
