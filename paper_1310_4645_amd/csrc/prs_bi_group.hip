@@ -14,7 +14,7 @@
 //  - pairing e-th sender with e-th receiver needs no lists: each sender writes its pair record at
 //    its rank among the senders, each receiver its own index at its rank among the receivers.  One search for a place in a word
 //    finds both lists of a visit, one sum and one prefix sum their lengths and places (four searches, two sums and two prefix
-//    sums: 15.9 instead of 14.7 ms on the 100,000-configuration sweep, schedules 27.0 instead of 26.4).
+//    sums: 15.9 instead of 14.7 ms on the 100,000-configuration sweep, schedules 27.4 instead of 27.0 on most machines, the same on others).
 // The visit itself is the same sequence of set operations as in the one-configuration kernel.
 // All lanes run one flat loop in which a group either visits the next segment or advances time, so
 // groups at different times and segments share the same instructions.
