@@ -180,11 +180,13 @@ template <typename T> __device__ __forceinline__ T or_absent(bool there, T v)
     return v;
 }
 
+#ifndef PRS_LDS_AT
 // LDS by its byte address (kernels without LDS of their own besides what the launch asks for, which begins at 0)
 template <typename T> __device__ __forceinline__ __attribute__((address_space(3))) T *lds_at(int32_t at)
 {
     return reinterpret_cast<__attribute__((address_space(3))) T *>(static_cast<uint32_t>(at));
 }
+#endif
 
 // keeps a branch a branch (its body is then not run speculatively on the other path)
 #ifndef PRS_KEEP_BRANCH

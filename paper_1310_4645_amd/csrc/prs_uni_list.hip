@@ -129,6 +129,7 @@ __device__ __forceinline__ void list_flush(const ListRole &role, const ListLds &
         if (pend && rank >= from && rank < from + kDescL)
             *lds_at<uint64_t>(lds.blocks + (rank - from) * 8) = (static_cast<uint64_t>(last >> 3) << 12) |
                                                             static_cast<uint32_t>(lane << 6 | lo << 3 | (static_cast<int>(last) & 7));
+        __builtin_amdgcn_wave_barrier();                                   // other lanes read what this one wrote
         const int n = total - from < kDescL ? total - from : kDescL;
         for (int i0 = 0; i0 < n; i0 += kFlushL) {
             const int i = i0 + (lane >> 3);
@@ -465,6 +466,10 @@ __global__ __launch_bounds__(kWave) void uni_list_kernel(ConfigArrays cfg, int64
 {
     // LDS is addressed from 0: the kernel has no other LDS than what the launch asks for
     const ListLds lds(procs);
+    // Lanes without a machine read and follow the links of their place like all others (refresh): every link names a processor of the
+    // wavefront from the start, whatever the LDS held before.
+    for (int32_t at = lane_id() * 16; at < ListLds::bytes(procs); at += kWave * 16) *lds_at<ListVec>(at) = ListVec{0, 0, 0, 0};
+    __syncthreads();
     // machines of more than 32 * procs processors: one to a wavefront, in the room of two
     uni_list_body<T, 32, true>(lds, procs, cfg, p_max, q_max, sched, plan, order, kWideClass);
     __syncthreads();
