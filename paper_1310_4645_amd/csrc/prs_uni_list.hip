@@ -65,6 +65,7 @@ size_t uni_list_lds_bytes(int32_t procs) { return static_cast<size_t>(ListLds::b
 
 typedef uint32_t __attribute__((ext_vector_type(4), may_alias)) ListVec;           // staged pairs are written one by one
 typedef uint32_t __attribute__((ext_vector_type(4), aligned(4))) ListRow;
+typedef uint32_t __attribute__((ext_vector_type(2), may_alias)) ListBlock;         // its place holds links between the flushes: none of them may move past it
 
 // Lanes of a group are 64 / G (G = 32) or 16 / G lanes apart inside a row of 16, so that the lane before is one rotation away.
 template <int G> struct ListLanes {
@@ -126,15 +127,17 @@ __device__ __forceinline__ void list_flush(const ListRole &role, const ListLds &
 {
     const int rank = rank_below(ready), total = __builtin_popcountll(ready);
     for (int from = 0; from < total; from += kDescL) {
-        if (pend && rank >= from && rank < from + kDescL)
-            *lds_at<uint64_t>(lds.blocks + (rank - from) * 8) = (static_cast<uint64_t>(last >> 3) << 12) |
-                                                            static_cast<uint32_t>(lane << 6 | lo << 3 | (static_cast<int>(last) & 7));
+        if (pend && rank >= from && rank < from + kDescL) {
+            const uint64_t d = (static_cast<uint64_t>(last >> 3) << 12) | static_cast<uint32_t>(lane << 6 | lo << 3 | (static_cast<int>(last) & 7));
+            *lds_at<ListBlock>(lds.blocks + (rank - from) * 8) = ListBlock{static_cast<uint32_t>(d), static_cast<uint32_t>(d >> 32)};
+        }
         __builtin_amdgcn_wave_barrier();                                   // other lanes read what this one wrote
         const int n = total - from < kDescL ? total - from : kDescL;
         for (int i0 = 0; i0 < n; i0 += kFlushL) {
             const int i = i0 + (lane >> 3);
-            const uint64_t d = *lds_at<uint64_t>(lds.blocks + i * 8);
-            const int bits = static_cast<int>(static_cast<uint32_t>(d)), owner = (bits >> 6) & 63, from_e = (bits >> 3) & 7, to_e = bits & 7;
+            const ListBlock listed = *lds_at<ListBlock>(lds.blocks + i * 8);
+            const uint64_t d = static_cast<uint64_t>(listed[1]) << 32 | listed[0];
+            const int bits = static_cast<int>(listed[0]), owner = (bits >> 6) & 63, from_e = (bits >> 3) & 7, to_e = bits & 7;
             const ListVec staged = *lds_at<ListVec>(role.lds + (owner << role.shift));
             ListRow v;
 #pragma unroll

@@ -1,6 +1,6 @@
 """The kernel of uni-greedy schedules of up to 1024 processors, compiled from its own source for the CPU and run on emulated
-wavefronts (tests/wavefront): its reads and writes of LDS stay inside the allocation and see only what has been written; pairs and
-start times are the oracle's."""
+wavefronts (tests/wavefront): its reads and writes of LDS stay inside the allocation and see only what has been written, and
+a byte is used as one type unless it may alias another; pairs and start times are the oracle's."""
 from __future__ import annotations
 
 import ctypes as C
@@ -35,7 +35,7 @@ def _ptr(a):
     return None if a is None else a.ctypes.data
 
 
-def _run(lib, host, p_max, q_max, gaps, limit=20_000_000, backwards=False, types=False, poke=(0, 0, 0)):
+def _run(lib, host, p_max, q_max, gaps, limit=20_000_000, backwards=False, types=True, poke=(0, 0, 0)):
     """greedy_schedule_batch on the emulated wavefronts; outputs with a margin around every configuration."""
     n, cost = len(host), B.PRS_COST_I64 if host.cost == "i64" else B.PRS_COST_F64
     number = np.int64 if host.cost == "i64" else np.float64
