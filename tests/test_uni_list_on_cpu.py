@@ -1,6 +1,6 @@
 """The kernel of uni-greedy schedules of up to 1024 processors, compiled from its own source for the CPU and run on emulated
 wavefronts (tests/wavefront): its reads and writes of LDS stay inside the allocation and see only what has been written, and
-a byte is used as one type unless it may alias another; pairs and start times are the oracle's."""
+a byte is used as one type unless it may alias another; pairs and start times are the oracle's; lists that are broken on purpose end with a status."""
 from __future__ import annotations
 
 import ctypes as C
@@ -14,6 +14,7 @@ import oracle as O
 import prs_inputs
 from paper_1310_4645_amd import binding as B
 
+STALLED = 3                                          # PRS_CFG_STALLED
 HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "wavefront", "uni_list.cpp")
 
@@ -35,7 +36,7 @@ def _ptr(a):
     return None if a is None else a.ctypes.data
 
 
-def _run(lib, host, p_max, q_max, gaps, limit=20_000_000, backwards=False, types=True, poke=(0, 0, 0)):
+def _run(lib, host, p_max, q_max, gaps, limit=20_000_000, backwards=False, types=True, poke=(0, 0, 0, 2)):
     """greedy_schedule_batch on the emulated wavefronts; outputs with a margin around every configuration."""
     n, cost = len(host), B.PRS_COST_I64 if host.cost == "i64" else B.PRS_COST_F64
     number = np.int64 if host.cost == "i64" else np.float64
@@ -102,3 +103,24 @@ _BATCHES = {"one machine": (1024, [5], [3]),
 def test_lists_stay_inside_lds_and_give_the_oracles_pairs(emu, batch, cost):
     p_max, p, q = _BATCHES[batch]
     _check(emu, _machines(p, q, cost, 5), p_max, max(q), 7, backwards=cost == "f64")
+
+
+def test_broken_lists_end_with_a_status(emu):
+    """A link of the one machine names another of its processors all of a sudden, or a ready time becomes infinite, at any time: the
+    kernel comes to an end, inside its LDS, and says so if a list was out of order or no pair could be formed any more."""
+    host = _machines([40], [30], "f64", 3)
+    gaps = np.zeros(1, np.int64)
+    _run(emu, host, 1024, 30, gaps)
+    waits = emu.emu_waits()
+    times = 64 * 30 * 2                                          # where the ready times begin: behind the links, 30 processors a lane
+    rng = np.random.default_rng(11)
+    seen = set()
+    for k in range(60):
+        when, i, to = rng.integers(waits // 10, waits - waits // 10), rng.integers(0, 40), rng.integers(0, 40)
+        word = (2 * (to if k % 3 == 0 else i), 2 * to, 2) if k % 4 else (times + 8 * i, 0x7FF0000000000000, 8)
+        *_, T, status = _run(emu, host, 1024, 30, gaps, limit=4 * waits, poke=(when, *word))
+        assert not emu.emu_stopped(), k
+        assert emu.emu_faults() == 0, emu.emu_first_fault().decode()
+        assert status[0] in (0, STALLED)
+        seen.add((int(status[0]), bool(np.isnan(T[0]))))
+    assert (STALLED, True) in seen and (STALLED, False) in seen        # given up, and marked on the way

@@ -58,9 +58,10 @@ inline void (*body)(void *);
 inline void *body_arg;
 
 // ---- what a test asks for and learns
-inline int64_t waits, wait_limit;        // operations; most of them a launch may take
+inline int64_t waits, reads, wait_limit;  // operations, reads of LDS by one lane since the last of its own; most operations a launch may take
+constexpr int64_t kReadLimit = 1 << 20;  // most such reads
 inline bool backwards;                   // lanes between two operations run in falling order
-inline int64_t poke_at, poke_link, poke_value;   // after so many operations a 16-bit word of LDS is overwritten (0: never)
+inline int64_t poke_at, poke_place, poke_value, poke_size;   // after so many operations (0: never) some bytes of LDS are overwritten
 inline bool types;                                   // report bytes used as two types
 inline int faults;
 inline char first_fault[256];
@@ -132,7 +133,9 @@ inline void run_wavefront()
             const int i = backwards ? kLanes - 1 - k : k;
             if (!(next >> i & 1)) continue;
             self = i; threadIdx.x = static_cast<unsigned>(i);
+            reads = 0;
             swap_stacks(&scheduler_sp, lanes[i].sp);
+            if (stopped) return;
         }
         int first = -1;
         next = 0;
@@ -143,7 +146,7 @@ inline void run_wavefront()
             if (c <= 0) next |= uint64_t(1) << i;
         }
         ++waits;
-        if (poke_at != 0 && waits == poke_at) memcpy(lds.data() + poke_link, &poke_value, 2);
+        if (poke_at != 0 && waits == poke_at) memcpy(lds.data() + poke_place, &poke_value, static_cast<size_t>(poke_size));
         if (waits > wait_limit) { stopped = true; return; }
     }
 }
@@ -176,6 +179,7 @@ template <typename T> struct Ref {
     int64_t at;
     operator T() const
     {
+        if (++reads > kReadLimit) { stopped = true; swap_stacks(&lanes[self].sp, scheduler_sp); }      // and never comes back
         T v{};
         if (!reachable<T>(at, "read past the end")) return v;
         for (size_t i = 0; i < sizeof(T); ++i) {

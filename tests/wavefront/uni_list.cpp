@@ -65,11 +65,11 @@ size_t bi_block_lds_bytes(int32_t) { return 0; }
 
 extern "C" {
 // types: report bytes of LDS used as two types;
-// limit: operations between lanes a call may take; poke: after poke_at of them the 16-bit word at poke_link becomes poke_value (0: never)
-void emu_begin(int types, int64_t limit, int backwards, int64_t poke_at, int64_t poke_link, int64_t poke_value)
+// limit: operations between lanes a call may take; poke: after poke_at of them (0: never) so many bytes of LDS are overwritten
+void emu_begin(int types, int64_t limit, int backwards, int64_t poke_at, int64_t poke_place, int64_t poke_value, int64_t poke_size)
 {
     emu::types = types != 0; emu::waits = 0; emu::wait_limit = limit; emu::backwards = backwards != 0; emu::faults = 0; emu::first_fault[0] = 0; emu::stopped = false;
-    emu::poke_at = poke_at; emu::poke_link = poke_link; emu::poke_value = poke_value;
+    emu::poke_at = poke_at; emu::poke_place = poke_place; emu::poke_value = poke_value; emu::poke_size = poke_size;
 }
 int64_t emu_waits() { return emu::waits; }
 int emu_stopped() { return emu::stopped; }
