@@ -65,7 +65,7 @@ static_assert(kDescL * 8 >= kWave * 2, "a link for every lane");
 size_t uni_list_lds_bytes(int32_t procs) { return static_cast<size_t>(ListLds::bytes(procs)); }
 
 typedef uint32_t __attribute__((ext_vector_type(4), may_alias)) ListVec;           // staged pairs are written one by one
-typedef uint32_t __attribute__((ext_vector_type(4), aligned(4))) ListRow;
+typedef uint32_t __attribute__((ext_vector_type(4), aligned(4), may_alias)) ListRow;   // rows of the output arrays
 typedef uint32_t __attribute__((ext_vector_type(2), may_alias)) ListBlock;         // its place holds links between the flushes: none of them may move past it
 
 // Lanes of a group are 64 / G (G = 32) or 16 / G lanes apart inside a row of 16, so that the lane before is one rotation away.
@@ -468,14 +468,16 @@ __device__ __forceinline__ void list_rest(const ConfigArrays &cfg, int64_t n, in
             int s = 4 * lane / n1, r = 4 * lane - s * n1;
             const int ds = step / n1, dr = step - ds * n1;
             for (int64_t j = 4 * lane; j < pairs; j += step) {
-                int32_t v[4];
+                ListRow v;
                 int sv = s, rv = r;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) { v[b] = sv; const bool wrap = ++rv == n1; sv += wrap ? 1 : 0; rv = wrap ? 0 : rv; }
+                for (int b = 0; b < 4; ++b) { v[b] = static_cast<uint32_t>(sv); const bool wrap = ++rv == n1; sv += wrap ? 1 : 0; rv = wrap ? 0 : rv; }
                 if (j + 4 <= pairs) {
-                    __builtin_memcpy(out + j, v, 16);
+                    *reinterpret_cast<ListRow *>(out + j) = v;
                 } else {
-                    for (int b = 0; j + b < pairs; ++b) out[j + b] = v[b];
+#pragma unroll
+                    for (int b = 0; b < 3; ++b)
+                        if (j + b < pairs) out[j + b] = static_cast<int32_t>(v[b]);
                 }
                 s += ds; r += dr;
                 if (r >= n1) { r -= n1; ++s; }
@@ -490,7 +492,8 @@ template <typename T>
 __global__ __launch_bounds__(kWave) void uni_list_kernel(ConfigArrays cfg, int64_t n, int32_t p_max, int32_t q_max, SchedOut sched,
                                                          PlanHeader *plan, const int32_t *order, int32_t procs)
 {
-    // LDS is addressed from 0: the kernel has no other LDS than what the launch asks for
+    // LDS is addressed from 0: the kernel has no other LDS than what the launch asks for.  Private arrays that are indexed by a variable
+    // would change that: the compiler moves them to LDS, to address 0.
     const ListLds lds(procs);
     // Lanes without a machine read and follow the links of their place like all others (refresh): every link names a processor of the
     // wavefront from the start, whatever the LDS held before.

@@ -380,7 +380,8 @@ __global__ __launch_bounds__(kWave) void uni_times_kernel(RingShape shape, Confi
                                                           TimesOut times, PlanHeader *plan, const int32_t *order, char *slots,
                                                           size_t slot_bytes, int32_t slot_runs, bool help)
 {
-    // LDS is addressed from 0: the kernel has no other LDS than what the launch asks for
+    // LDS is addressed from 0: the kernel has no other LDS than what the launch asks for (no private array indexed by a variable, which the
+    // compiler would move there)
     if (kSmall) shape = RingShape{SmallRings<kComp>::kRuns, SmallRings<kComp>::kRing};
     constexpr int kFirst = kSmall ? 0 : kLargeClass;
     char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
