@@ -77,9 +77,8 @@ hipError_t launch_offsets(const OffsetsLaunch &L)
 enum ClassKind { kUniTimes, kUniSched, kUniList, kBiGroup, kBiGeneral, kBiBlock, kUniWide };
 constexpr size_t kLdsPerCU = 160 * 1024, kLdsPerBlockMax = 64 * 1024, kBitmapLdsMax = 24 * 1024;
 constexpr int kCUs = 256, kSIMDs = 4 * kCUs, kMaxBlocksPerCU = 24, kGlobalClassGrid = 1024;
-// LDS is given out in units of 2560 bytes: six one-wavefront blocks of 25,600 bytes run on a CU side by side, five of 26,880
-// (3072 equal machines of 900 processors, two to a wavefront: 9.6 ms in one go, 16.7 in two).
-constexpr size_t kLdsUnit = 2560;
+// LDS is given out in units of 1280 bytes: six one-wavefront blocks of 26,880 bytes run on a CU side by side, five of 27,300.
+constexpr size_t kLdsUnit = 1280;
 static int64_t blocks_per_cu(size_t lds_bytes)
 {
     return static_cast<int64_t>(kLdsPerCU / ((lds_bytes + kLdsUnit - 1) / kLdsUnit * kLdsUnit));
@@ -185,10 +184,8 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
         const int32_t p_small = has_large ? kUniSmallProcs : p_max;
         if (sched) {
             // Room for so many processors per lane: 16 lanes for the largest machine, the group size up to which most lanes of a
-            // pipeline have something to do, but no more than lets six wavefronts share a CU.  Machines that do not fit 32 lanes then
-            // run alone on a wavefront.
+            // pipeline have something to do, but no more than lets six wavefronts share a CU.
             L.limits.lane_p = std::min(std::max((p_small + 15) / 16, 8), kUniListLaneProcs);
-            if (p_small > 32 * L.limits.lane_p) L.limits.wide_p = 32 * L.limits.lane_p + 1;
         }
         for (int set = 0; set < 2; ++set) {
             const bool lists = sched && set == 0, rings = sched && set == 1;
@@ -425,7 +422,7 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
         return launch_bi(L);
     };
     // the class with the longest-running configurations first; a class without configurations ends at once
-    if (lay.wide.grid > 0 && lay.limits.wide_p > 0 && general(lay.wide, P.order, kWideClass) != hipSuccess) return PRS_EDEVICE;
+    if (lay.limits.wide_p > 0 && general(lay.wide, P.order, kWideClass) != hipSuccess) return PRS_EDEVICE;
     if (lay.large.grid > 0 && general(lay.large, P.order, kLargeClass) != hipSuccess) return PRS_EDEVICE;
     bool groups_done = false;
     for (int k = kClasses - 1; k >= 0; --k) {

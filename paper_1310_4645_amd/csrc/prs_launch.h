@@ -96,7 +96,8 @@ size_t uni_sched_slot_bytes(int32_t p_cap);
 hipError_t launch_uni_sched(const UniLaunch &L);
 // schedules of machines of up to kUniListProcs processors
 constexpr int32_t kUniListProcs = 1024;
-constexpr int32_t kUniListLaneProcs = 30;                    // most processors per lane, of which six wavefronts fit a CU
+constexpr int32_t kUniListLaneProcs = 32;                    // most processors per lane, of which six wavefronts fit a CU
+static_assert(32 * kUniListLaneProcs >= kUniListProcs, "the largest machine fits half a wavefront");
 size_t uni_list_lds_bytes(int32_t procs);                    // a wavefront's, with room for so many processors per lane
 hipError_t launch_uni_list(const UniLaunch &L);
 // uni-greedy completion times of machines with thousands of processors: one block per configuration

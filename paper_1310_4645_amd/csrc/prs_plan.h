@@ -10,7 +10,7 @@ namespace prs {
 constexpr int kClasses = 6;          // bi-greedy: five group sizes and the general kernel; uni-greedy: six group sizes (schedules use 0, 1, 2 and the last)
 constexpr int kWorkBuckets = 40;     // floor(log2(work)) buckets, heaviest first
 constexpr int kRetryClass = kClasses; // pseudo class: configurations handed back to the general kernel
-constexpr int kWideClass = kClasses;  // uni-greedy: machines large enough for a block (completion times) or a wavefront (schedules) of their own
+constexpr int kWideClass = kClasses;  // uni-greedy completion times: machines large enough for a block of their own
 constexpr int kLargeClass = kClasses + 1;   // uni-greedy completion times: the classes 0 .. kClasses - 1 again, for machines of more than large_p processors
 constexpr int kPlanClasses = kLargeClass + kClasses;
 
@@ -42,8 +42,7 @@ struct ClassLimits {
     int32_t giant_log2[2];       // configurations of the last class with at least 2^giant_log2 pairs are "giant"
     int32_t lanes_log2[2];       // by_work only: 1: class k has 2^k lanes per configuration, and none gets more than it has segments
     int32_t lane_p;              // by_work only: the first set's class k holds at most 2^k times as many processors (0: no such limit)
-    int32_t wide_p;              // by_work only: machines of at least this many processors form the class kWideClass (0: none);
-                                 // with lane_p those of the first set only
+    int32_t wide_p;              // by_work only: machines of at least this many processors form the class kWideClass (0: none)
 };
 
 struct PlanLaunch {

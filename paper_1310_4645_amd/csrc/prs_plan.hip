@@ -17,7 +17,7 @@ __device__ __forceinline__ int plan_bucket(const ConfigArrays &cfg, int64_t i, i
         if (lim.lanes_log2[large ? 1 : 0]) { const int enough = ceil_log2(c.q); cls = cls < enough ? cls : enough; }
         if (lim.lane_p > 0 && !large) { const int least = ceil_log2((c.p + lim.lane_p - 1) / lim.lane_p); cls = cls > least ? cls : least; }
         if (large) cls += kLargeClass;
-        if (lim.wide_p > 0 && c.p >= lim.wide_p && cfg.comp_m == 0 && !(large && lim.lane_p > 0)) cls = kWideClass;
+        if (lim.wide_p > 0 && c.p >= lim.wide_p && cfg.comp_m == 0) cls = kWideClass;
     } else {
         for (int k = kClasses - 2; k >= 0; --k)
             if (c.p <= lim.p[0][k] && c.q <= lim.q) cls = k;

@@ -439,10 +439,10 @@ __global__ void replay_write_status(const int32_t *flags, int32_t *status)
 }
 
 static size_t replay_lds_bytes(int vec, int depth, size_t elem) { return static_cast<size_t>(depth) * kReplayThreads * vec * elem; }
-// blocks that 256 CUs hold at once: 160 KB of LDS in units of 2560 bytes, 32 wavefronts
+// blocks that 256 CUs hold at once: 160 KB of LDS in units of 1280 bytes, 32 wavefronts
 static int64_t replay_resident_blocks(size_t lds)
 {
-    const int64_t by_lds = static_cast<int64_t>(160 * 1024 / ((lds + 2559) / 2560 * 2560)), by_waves = 32 * kWave / kReplayThreads;
+    const int64_t by_lds = static_cast<int64_t>(160 * 1024 / ((lds + 1279) / 1280 * 1280)), by_waves = 32 * kWave / kReplayThreads;
     return 256 * (by_lds < by_waves ? by_lds : by_waves);
 }
 

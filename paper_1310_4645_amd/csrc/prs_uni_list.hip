@@ -165,8 +165,7 @@ __device__ __forceinline__ void list_flush(const ListRole &role, const ListLds &
 // the others (list_one_segment; 20,000 machines of 1000 processors 9.5 -> 0.5 ms, on rings 1.5).
 template <typename T> __device__ __forceinline__ bool list_single(const Config<T> &c) { return c.q == 1 && c.p > kWave; }
 
-// kAlone: one configuration per wavefront, the other groups stay without.
-template <typename T, int G, bool kAlone>
+template <typename T, int G>
 __device__ __forceinline__ void uni_list_body(const ListLds &lds, int32_t procs, const ConfigArrays &cfg, int32_t p_max, int32_t q_max, const SchedOut &sched,
                                               PlanHeader *plan, const int32_t *order, int cls)
 {
@@ -184,7 +183,7 @@ __device__ __forceinline__ void uni_list_body(const ListLds &lds, int32_t procs,
     huge = or_absent<T>(false, huge);
 
     // ---- per-group state (the same in all lanes of a group)
-    bool have = false, exhausted = kAlone && Lanes::group(lane) != 0;
+    bool have = false, exhausted = false;
     int64_t ci = 0, out_base = 0;
     int p = 2, q = 1;
     T c_full = 0, g_full = 0, c_last = 0, g_last = 0;
@@ -499,20 +498,17 @@ __global__ __launch_bounds__(kWave) void uni_list_kernel(ConfigArrays cfg, int64
     // wavefront from the start, whatever the LDS held before.
     for (int32_t at = lane_id() * 16; at < ListLds::bytes(procs); at += kWave * 16) *lds_at<ListVec>(at) = ListVec{0, 0, 0, 0};
     __syncthreads();
-    // machines of more than 32 * procs processors: one to a wavefront, in the room of two
-    uni_list_body<T, 32, true>(lds, procs, cfg, p_max, q_max, sched, plan, order, kWideClass);
+    uni_list_body<T, 32>(lds, procs, cfg, p_max, q_max, sched, plan, order, 5);
     __syncthreads();
-    uni_list_body<T, 32, false>(lds, procs, cfg, p_max, q_max, sched, plan, order, 5);
+    uni_list_body<T, 16>(lds, procs, cfg, p_max, q_max, sched, plan, order, 4);
     __syncthreads();
-    uni_list_body<T, 16, false>(lds, procs, cfg, p_max, q_max, sched, plan, order, 4);
+    uni_list_body<T, 8>(lds, procs, cfg, p_max, q_max, sched, plan, order, 3);
     __syncthreads();
-    uni_list_body<T, 8, false>(lds, procs, cfg, p_max, q_max, sched, plan, order, 3);
+    uni_list_body<T, 4>(lds, procs, cfg, p_max, q_max, sched, plan, order, 2);
     __syncthreads();
-    uni_list_body<T, 4, false>(lds, procs, cfg, p_max, q_max, sched, plan, order, 2);
+    uni_list_body<T, 2>(lds, procs, cfg, p_max, q_max, sched, plan, order, 1);
     __syncthreads();
-    uni_list_body<T, 2, false>(lds, procs, cfg, p_max, q_max, sched, plan, order, 1);
-    __syncthreads();
-    uni_list_body<T, 1, false>(lds, procs, cfg, p_max, q_max, sched, plan, order, 0);
+    uni_list_body<T, 1>(lds, procs, cfg, p_max, q_max, sched, plan, order, 0);
     __syncthreads();
     list_rest<T>(cfg, n, p_max, q_max, sched, &plan->ticket_giant[0]);
 }

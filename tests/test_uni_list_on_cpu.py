@@ -89,12 +89,12 @@ def _machines(p, q, cost, seed):
     return prs_inputs.SweepConfigs(p, q, m, *[c.astype(number) for c in costs], cost)
 
 
-# bound on the machines, then processors and segments: every group size, groups without a configuration, machines alone on a wavefront,
+# bound on the machines, then processors and segments: every group size, groups without a configuration, the largest machines,
 # one segment, more segments than lanes
 _BATCHES = {"one machine": (1024, [5], [3]),
             "one of one segment": (64, [64], [1]),
             "few": (256, [2, 3, 17, 33, 65, 129, 256], [9, 1, 40, 3, 2, 5, 34]),
-            "alone": (1024, [961, 3, 960], [2, 1, 1]),
+            "large": (1024, [961, 3, 1024], [2, 1, 1]),
             "pairs only": (16, [2] * 70, list(range(1, 71)))}
 
 
