@@ -145,6 +145,30 @@ static void general_spec(ClassSpec &c, int32_t p_cap, int32_t q_cap)
     c.slot_bytes = bi_slot_bytes(p_cap, q_cap, c.lds);
 }
 
+// Schedules of few segments: lanes beyond the segments have nothing to do (the first segment takes none), so what counts is how many
+// lanes that have something to do fit a CU: with g lanes for the largest machine, groups and wavefronts that find room, of which
+// more than seven only share cycles.  Machines of more than 16 processors are not run by one lane, and one segment alone goes no
+// further than 20 processors a lane: the lanes of a group lay the first one down together.  100,000 equal machines, us, with 1, 2, 4, 8 and 16
+// lanes: 31 processors and 2 segments 237, 150, 191, 271, -; 100 and 2 -, 532, 565, 761, 1372; 64 and 1 294, 174, 114, 119, 147; 481 and 2 of 8 and 16
+// lanes 6340, 6998.  Four wavefronts at least if the segments are more than a few (20,000 of 480 and 8, 8 and 16 lanes: 5034, 4450).
+constexpr int32_t kFewSegments = 16;
+// Most wavefronts of the list kernel per CU: small machines find room for more, which only share cycles and have to be started (us with
+// 10, 12 and 16: 20,000 machines of 5 processors and 30 segments 134, 136, 194; of 100 and 30 1459, 1277, 1459).
+constexpr int32_t kListWavesPerCU = 12;
+static int32_t few_segments_lane_p(int32_t p, int32_t q)
+{
+    int32_t best = kUniListLaneProcs;
+    int64_t most = 0;
+    for (int lanes = p <= 16 ? 1 : 2; lanes <= 32; lanes *= 2) {
+        const int32_t room = std::max((p + lanes - 1) / lanes, 4);
+        const int64_t waves = std::min<int64_t>(blocks_per_cu(uni_list_lds_bytes(room)), 7);
+        if (room > (q == 1 ? 20 : 64) || (q > 4 && waves < 4)) continue;
+        const int64_t busy = waves * (kWave / lanes) * std::min(lanes, std::max(q - 1, 1));
+        if (busy > most) { most = busy; best = room; }
+    }
+    return best;
+}
+
 static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t q_max, const prs_tuning *tuning = nullptr,
                           bool compositions = false)
 {
@@ -186,6 +210,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             // Room for so many processors per lane: 16 lanes for the largest machine, the group size up to which most lanes of a
             // pipeline have something to do, but no more than lets six wavefronts share a CU.
             L.limits.lane_p = std::min(std::max((p_small + 15) / 16, 8), kUniListLaneProcs);
+            if (q_max <= kFewSegments) L.limits.lane_p = few_segments_lane_p(p_small, q_max);
         }
         for (int set = 0; set < 2; ++set) {
             const bool lists = sched && set == 0, rings = sched && set == 1;
@@ -246,6 +271,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
                 c.slot_bytes = uni_times_slot_bytes(c.p_cap, compositions || p > kUniSmallProcs);
             }
             int64_t g = blocks_per_cu(c.lds_bytes) * kCUs;
+            if (c.kind == kUniList && g > kListWavesPerCU * kCUs) g = kListWavesPerCU * kCUs;
             if (c.kind != kUniSched && g > n) g = n < 1 ? 1 : n;
             size_t bytes = static_cast<size_t>(g) * c.slot_bytes;
             if (sched) {

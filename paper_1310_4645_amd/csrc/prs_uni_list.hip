@@ -7,7 +7,8 @@
 // 10 bytes of LDS, for all its streams and all B together, and nothing of them lies in global memory (rings of 32 entries per
 // lane backed by the workspace, which larger machines still use, wrote and read 83 bytes a pair there and waited for them half of
 // the time).  A configuration is run by G lanes (1 to 32); lane l runs segments l, l + G, ... and reads the stream of the lane
-// before it (lane 0 that of the last lane, a round behind; its first stream is the machine at time 0).
+// before it (lane 0 that of the last lane, a round behind).  The first segment needs no pipeline: its pairs and its stream have a closed
+// form (ListRound), which the lanes of the group write side by side when they take a machine.
 //
 // One iteration of a lane forms one pair from the two smallest keys (ready time, index) among the heads of its input stream A and
 // of B.  The sender joins the running group of the lane's stream, the senders with the newest value: sorted by index, not yet
@@ -29,12 +30,13 @@
 // Segment numbers are runs of p - 1 equal ones; wavefronts that have nothing else left write them.
 //
 // What bounds it: the latency of a step, about 240 instructions that depend on each other in 0.7 us, at six wavefronts per CU, which is what
-// the LDS holds; 3072 machines at once take hardly longer than 512 (9.6 and 8.6 ms).  Measured (rings -> lists): 100,000 machines
-// of up to 1024 processors 51.6 -> 25.2 ms, 27,320 of up to 826 processors and 93 segments 19.8 -> 6.6, one machine of 256
-// and 64 segments 2.35 -> 1.55.  The sweep in steps: first version 46.0; selects and dummy writes instead of branches 31.7;
-// four steps between two looks for finished blocks 29.5; fewer pairs per lane in the classes of few lanes 26.5; six wavefronts per CU
-// instead of five 25.2.  Not taken: idle groups that help with the class below (33.7: its machines run on lanes that wait), wave
-// priorities by size (no change), tickets drawn several at a time (no change).
+// the LDS holds; 3072 machines at once take hardly longer than 512.  Measured (rings -> lists): 100,000 machines of up to 1024 processors
+// 51.6 -> 22.4 ms, 27,320 of up to 826 processors and 93 segments 19.8 -> 6.6, one machine of 256 and 64 segments 2.35 -> 1.57.  The sweep
+// in steps: first version 46.0; selects and dummy writes instead of branches 31.7; four steps between two looks for finished blocks
+// 29.5; fewer pairs per lane in the classes of few lanes 26.5; two machines of 1024 processors to a wavefront 23.9; first segments in closed
+// form 22.4.  Few segments (rings, lists as they were, now): 20,000 machines of 1024 processors and two segments 10.6, 14.6, 5.8 ms;
+// 100,000 of 31 and two 203, 391, 170 us; 100,000 of 2 and one 65, 260, 52 us.  Not taken: idle groups that help with the class below (33.7: its machines run on lanes that wait), wave priorities by size (no change), tickets drawn
+// several at a time (no change).
 #include "prs_device.h"
 #include "prs_launch.h"
 
@@ -44,6 +46,8 @@ constexpr int kStageL = 8;                                   // pairs of a block
 constexpr int kFlushL = 8;                                   // blocks a pass of the flush writes, eight lanes each
 constexpr int kDescL = 32;                                   // blocks listed at a time
 constexpr int kStepsL = 4;                                   // steps between two looks for finished blocks and configurations
+constexpr int kSharedL = 4096;                               // pairs a wavefront, on average, up to which machines are shared out without tickets
+constexpr int kFewL = 32;                                    // pairs of a machine up to which one lane writes its segment numbers
 constexpr int kLookL = 64;                                   // such looks between two looks for groups that do not move
 
 // LDS of a wavefront: room for `procs` processors per lane.  A processor goes by the address of its link.
@@ -161,19 +165,61 @@ __device__ __forceinline__ void list_flush(const ListRole &role, const ListLds &
     }
 }
 
-// One segment on many processors gives one lane of a group something to do; a whole wavefront does it round by round instead, after
-// the others (list_one_segment; 20,000 machines of 1000 processors 9.5 -> 0.5 ms, on rings 1.5).
-template <typename T> __device__ __forceinline__ bool list_single(const Config<T> &c) { return c.q == 1 && c.p > kWave; }
+// The first segment, from time 0, goes in rounds: the processors that are left pair up with their neighbours, all at one time, and
+// receivers are left.  Their list at the beginning of a round is
+//     [extra] 0 first first+step first+2step ...      (count processors in all)
+// where `extra`, if there is one, is the last processor of the round before, which found no partner: it is ready earlier and so
+// comes first, and its index is the largest.  The root never sends (Lemma 1 (ii)).  All start times differ from round to round (tcomm > 0
+// and no sum is smaller than its terms), so no order but this one can arise.
+struct ListRound {
+    int first, step, count, extra;             // extra -1: none
+    __device__ __forceinline__ int pairs() const { return count >> 1; }
+    // Pair e of the round: the processor that sends and the one that receives and is left.
+    __device__ __forceinline__ void pair(int e, int &snd, int &rcv) const
+    {
+        const int at = first + (2 * e - (extra >= 0 ? 2 : 1)) * step;                // for e > 0: the neighbours at, at + step
+        snd = e > 0 ? at : (extra >= 0 ? extra : first);
+        rcv = e > 0 ? at + step : 0;
+    }
+    // Senders by index: place i of the round's part of the stream (the extra one comes last).
+    __device__ __forceinline__ int sender(int i) const
+    {
+        if (extra >= 0) return i == pairs() - 1 ? extra : first + 2 * i * step;
+        return i > 0 ? first + (2 * i - 1) * step : first;
+    }
+    __device__ __forceinline__ void next()
+    {
+        const int regular = count - (extra >= 0 ? 1 : 0), last = regular > 1 ? first + (regular - 2) * step : 0;   // of the list
+        const int alone = (count & 1) != 0 ? last : -1;
+        first += extra >= 0 ? step : 2 * step;
+        step *= 2;
+        count = pairs() + (count & 1);
+        extra = alone;
+    }
+};
 
 template <typename T, int G>
-__device__ __forceinline__ void uni_list_body(const ListLds &lds, int32_t procs, const ConfigArrays &cfg, int32_t p_max, int32_t q_max, const SchedOut &sched,
-                                              PlanHeader *plan, const int32_t *order, int cls)
+__device__ __forceinline__ void uni_list_body(const ListLds &lds, int32_t procs, const ConfigArrays &cfg, int64_t n, int32_t p_max, int32_t q_max, const SchedOut &sched,
+                                              PlanHeader *plan, const int32_t *order, int cls, bool roomy, bool &first)
 {
     typedef ListLanes<G> Lanes;
+    constexpr int kGroups = kWave / G;
     const int32_t count = plan->class_count[cls], begin = plan->class_begin[cls];
     if (count == 0) return;
+    // Tickets come from one address for the whole chip, which serves a wavefront about every 20 ns.  All wavefronts come to the first
+    // class that has machines at one time: there each group has its first ticket without asking, and all of its tickets if these are
+    // all or the machines are small.  A wavefront that has seen the end of a class asks no more.
+    // First tickets go to one group of every wavefront before the next group has one if that leaves the other classes their wavefronts
+    // or most machines are of this class, otherwise to wavefront by wavefront (20,000 machines of up to 64 processors and 24 segments, us: 327
+    // and 382; 60,000 of up to 64 and 64: 1025 and 776).
+    const uint32_t at_once = gridDim.x * kGroups;
+    const bool shared = first && (static_cast<uint32_t>(count) <= at_once || sched.pair_capacity / gridDim.x <= kSharedL);
+    bool given = first, over = false;
     const int lane = lane_id(), gl = Lanes::in_group(lane), leader = Lanes::leader(lane);
     const uint64_t gmask = Lanes::mask(lane);
+    // the next ticket that the group has without asking, or the first one that is asked for
+    uint32_t mine = !first ? 0 : roomy || count >= n / 2 ? Lanes::group(lane) * gridDim.x + blockIdx.x : Lanes::group(lane) + blockIdx.x * kGroups;
+    first = false;
     const ListRole role(sched, lds, lane);
     const int32_t root = Lanes::group(lane) * (G * 2) * procs;         // link of processor 0 of the group's machine
     const int32_t unread = lds.blocks + lane * 2, stage_t = lds.times + lane * (kStageL * 8), stage_i = lds.pairs + lane * (kStageL * 4);
@@ -195,7 +241,7 @@ __device__ __forceinline__ void uni_list_body(const ListLds &lds, int32_t procs,
     uint32_t news = root;               // the last publication: its first processor, and how many (upper half)
     T newsV = 0;                        // and its ready time
     int32_t tail = root;                   // last processor published
-    int apos = 0, aleft = 0;            // entries of my input stream taken; those still to be taken in this segment
+    int apos = 0, aleft = 0;            // entries of my input stream taken (the first segment's none); those still to be taken in this segment
     int32_t ah = root;                     // head of A
     T xa0 = 0;                          // its ready time
     int32_t gf = root, gt = root, gi = root, gs = root;   // running group: first, last, the one inserted last, the one after that
@@ -255,11 +301,15 @@ __device__ __forceinline__ void uni_list_body(const ListLds &lds, int32_t procs,
             }
         }
         if (ballot64(!have && !exhausted) != 0) {
-            if (!have && !exhausted) {
-                const unsigned long long got = atomicAdd(&plan->ticket[cls], gl == 0 ? 1ULL : 0ULL);
+            int64_t ticket = over ? count : mine;
+            if (!given && !over) {
+                const unsigned long long got = atomicAdd(&plan->ticket[cls], !have && !exhausted && gl == 0 ? 1ULL : 0ULL);
                 const uint32_t l32 = __shfl(static_cast<uint32_t>(got), leader), h32 = __shfl(static_cast<uint32_t>(got >> 32), leader);
-                const int64_t ticket = static_cast<int64_t>((static_cast<uint64_t>(h32) << 32) | l32);
+                ticket += static_cast<int64_t>((static_cast<uint64_t>(h32) << 32) | l32);
+            }
+            if (!have && !exhausted) {
                 left = 0;
+                if (given) mine = shared ? mine + at_once : at_once;
                 if (ticket >= count) {
                     exhausted = true;
                 } else {
@@ -275,22 +325,68 @@ __device__ __forceinline__ void uni_list_body(const ListLds &lds, int32_t procs,
                         if (sched.cfg_status) sched.cfg_status[ci] = status;
                         if (status != PRS_CFG_OK && sched.T_greedy) static_cast<T *>(sched.T_greedy)[ci] = CostTraits<T>::bad();
                     }
-                    if (status == PRS_CFG_OK && !list_single(c)) {
+                    if (status == PRS_CFG_OK) {
                         have = true;
                         p = c.p; q = c.q;
                         c_full = c.c_full; g_full = c.g_full; c_last = c.c_last; g_last = c.g_last;
-                        const int32_t end = root + 2 * (p - 1);
-                        k = gl; left = k < q ? p - 1 : 0; orel = k * (p - 1); seen = -1; pub = 0; news = root;
-                        tail = gl == G - 1 ? end : root;                         // the reader of the last lane comes from the machine at time 0
-                        apos = gl == 0 ? -p : 0; aleft = p;
+                        k = gl; pub = 0; news = root; seen = -1;
+                        tail = root;
+                        apos = 0; aleft = p;
                         ah = bh = bt = gf = gt = gi = gs = root; a1 = b1 = root; xa0 = 0; newsV = 0;
                         gn = 0; lastS = T(-1); bn = 0;
+                        const T c0 = q == 1 ? c_last : c_full, g0 = q == 1 ? g_last : g_full;
+                        ListRound round = {1, 1, p, -1};
+                        int32_t from = root;                                 // first of the stream
+                        T t = 0;
+                        for (int done = 0; round.count > 1;) {
+                            const int pairs = round.pairs();
+                            const T tc = wrap_add<T>(t, c0), tr = wrap_add<T>(tc, g0);
+                            const int64_t o = out_base + done;
+                            // the root ends the stream, before the last sender if both are ready at one time
+                            const bool final = round.count == 2, with = final && tr == tc;
+                            ListRound after = round;
+                            after.next();
+                            const T tc1 = wrap_add<T>(tr, c0);
+                            const bool root_next = after.count == 2 && wrap_add<T>(tc1, g0) == tc1;
+                            const int32_t then = final || root_next ? root : root + 2 * after.sender(0);
+                            if (done == 0) { from = with ? root : root + 2; newsV = with ? tr : tc; }
+                            for (int e = gl; e < pairs; e += G) {
+                                int snd, rcv;
+                                round.pair(e, snd, rcv);
+                                if (sched.src) sched.src[o + e] = snd;
+                                if (sched.dst) sched.dst[o + e] = rcv;
+                                if (sched.tstart) static_cast<T *>(sched.tstart)[o + e] = t;
+                                const int32_t x = root + 2 * round.sender(e);
+                                *X(x) = e + 1 < pairs ? tc : final ? tr : tc1;             // of the next one
+                                *N(x) = static_cast<uint16_t>(e + 1 < pairs ? root + 2 * round.sender(e + 1) : then);
+                            }
+                            if (final && gl == 0) {
+                                const int32_t x = root + 2 * round.sender(0);
+                                *X(root) = tc;
+                                *N(root) = static_cast<uint16_t>(with ? x : root);
+                                tail = with ? x : root;
+                            }
+                            done += pairs;
+                            t = tr;
+                            round = after;
+                        }
+                        // the first lane is through with it, and its reader finds all of it published at once
+                        if (gl == 0) {
+                            if (q == 1 && sched.T_greedy) static_cast<T *>(sched.T_greedy)[ci] = t;
+                            k = G; pub = p;
+                            news = static_cast<uint32_t>(from) | static_cast<uint32_t>(p) << 16;
+                        } else {
+                            newsV = 0;
+                        }
+                        left = k < q ? p - 1 : 0; orel = k * (p - 1);
                         cc = k == q - 1 ? c_last : c_full; gg = k == q - 1 ? g_last : g_full;
-                        for (int32_t i = root + 2 * gl; i <= end; i += 2 * G) { *X(i) = T(0); *N(i) = static_cast<uint16_t>(i < end ? i + 2 : root); }
                     }
                 }
             }
+            given = shared;
+            over = !shared && (over || ballot64(exhausted) != 0);
             if (ballot64(have) == 0 && ballot64(!exhausted) == 0) break;
+            if (ballot64(left > 0) == 0) continue;                      // machines of one segment are done
             refresh();
         }
 
@@ -300,9 +396,8 @@ __device__ __forceinline__ void uni_list_body(const ListLds &lds, int32_t procs,
             const int32_t a0 = ah, b0 = bh;
             const int32_t a2 = *N(a1), b2 = *N(b1);                                // what comes after them, for the next step
             const T xa2 = *X(a1), xb2 = *X(b1);
-            const int there = k == 0 ? p : ahead;
-            const bool complete = there >= aleft;
-            const int avail = complete ? aleft : there;
+            const bool complete = ahead >= aleft;
+            const int avail = complete ? aleft : ahead;
             const T va0 = or_absent<T>(avail > 0, xa0), va1 = or_absent<T>(avail > 1, xa1);
             const T vb0 = or_absent<T>(bn > 0, xb0), vb1 = or_absent<T>(bn > 1, xb1);
             // entries not published yet are >= the running value of the producer
@@ -415,58 +510,60 @@ __device__ __forceinline__ void uni_list_body(const ListLds &lds, int32_t procs,
     }
 }
 
-// One segment from time 0: in every round the processors that remain, in the order of their indices behind the one left over from the
-// round before, pair up with their neighbours, all at the same time; receivers remain.
+// Segment numbers, runs of p - 1 equal ones, by whole wavefronts.  A wavefront takes several machines at a time, looked up by a lane
+// each.
 template <typename T>
-__device__ __forceinline__ void list_one_segment(const Config<T> &c, const SchedOut &sched, int64_t i, int64_t base)
+__device__ __forceinline__ void list_segments(const ConfigArrays &cfg, int64_t n, int32_t p_max, int32_t q_max, const SchedOut &sched,
+                                              unsigned long long *tickets)
 {
+    if (!sched.seg) return;
     const int lane = lane_id();
-    T t = 0;
-    int32_t cur = 0, next = kUniListProcs * 2;                            // 16-bit indices in LDS
-    for (int e = lane; e < c.p; e += kWave) *lds_at<uint16_t>(cur + e * 2) = static_cast<uint16_t>(e);
-    for (int n = c.p; n > 1;) {
-        __builtin_amdgcn_wave_barrier();
-        const int pairs = n >> 1, odd = n & 1;
-        for (int e = lane; e < pairs; e += kWave) {
-            const int32_t a = *lds_at<uint16_t>(cur + e * 4), b = *lds_at<uint16_t>(cur + e * 4 + 2);
-            const int32_t snd = a == 0 ? b : a, rcv = a == 0 ? 0 : b;     // the root never sends (Lemma 1 (ii))
-            *lds_at<uint16_t>(next + (odd + e) * 2) = static_cast<uint16_t>(rcv);
-            if (sched.src) sched.src[base + e] = snd;
-            if (sched.dst) sched.dst[base + e] = rcv;
-            if (sched.tstart) static_cast<T *>(sched.tstart)[base + e] = t;
-        }
-        if (odd && lane == 0) *lds_at<uint16_t>(next) = *lds_at<uint16_t>(cur + (n - 1) * 2);
-        t = wrap_add<T>(wrap_add<T>(t, c.c_last), c.g_last);
-        base += pairs;
-        n = pairs + odd;
-        const int32_t swap = cur; cur = next; next = swap;
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (lane == 0 && sched.T_greedy) static_cast<T *>(sched.T_greedy)[i] = t;
-}
-
-// What is left for whole wavefronts: machines with one segment, and segment numbers, runs of p - 1 equal ones.
-template <typename T>
-__device__ __forceinline__ void list_rest(const ConfigArrays &cfg, int64_t n, int32_t p_max, int32_t q_max, const SchedOut &sched,
-                                          unsigned long long *tickets)
-{
-    const int lane = lane_id();
-    constexpr int kTake = 8;
-    for (;;) {
-        const int64_t from = next_ticket(tickets) * kTake;
+    // Long ones are left to the wavefronts that come first (a machine more or less is as long as a ticket takes); short ones are shared
+    // out beforehand, without tickets.
+    const bool shared = sched.pair_capacity / gridDim.x <= 65536;
+    const int64_t share = shared ? (n + gridDim.x - 1) / gridDim.x : n / (static_cast<int64_t>(gridDim.x) * 4), most = shared ? kWave : 16;
+    const int take = share < 1 ? 1 : static_cast<int>(share > most ? most : share);
+    for (int64_t round = blockIdx.x;; round += gridDim.x) {
+        const int64_t from = (shared ? round : next_ticket(tickets)) * take;
         if (from >= n) break;
-        for (int64_t i = from; i < from + kTake && i < n; ++i) {
-            const Config<T> c = decode_config<T>(cfg, i, p_max, q_max);
-            if (c.status != PRS_CFG_OK || c.p > kUniListProcs) continue;
-            const int64_t base = sched.pair_offset[i], pairs = static_cast<int64_t>(c.p - 1) * c.q;
-            if (base < 0 || base + pairs > sched.pair_capacity) continue;
-            if (list_single(c)) list_one_segment<T>(c, sched, i, base);
-            if (!sched.seg) continue;
-            const int n1 = c.p - 1, step = 4 * kWave;
+        int64_t base = 0;
+        int32_t procs = 0, segments = 0;
+        if (lane < take && from + lane < n) {
+            const Config<T> c = decode_config<T>(cfg, from + lane, p_max, q_max);
+            base = sched.pair_offset[from + lane];
+            if (c.status == PRS_CFG_OK && c.p <= kUniListProcs && base >= 0 && base + static_cast<int64_t>(c.p - 1) * c.q <= sched.pair_capacity) {
+                procs = c.p; segments = c.q;
+            }
+        }
+        // the shortest by their lanes
+        const int few = (procs - 1) * segments;
+        if (few > 0 && few <= kFewL) {
             int32_t *const out = sched.seg + base;
+            int s = 0, r = 0;
+            for (int j = 0; j < few; j += 4) {
+                ListRow v;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) { v[b] = static_cast<uint32_t>(s); const bool wrap = ++r == procs - 1; s += wrap ? 1 : 0; r = wrap ? 0 : r; }
+                if (j + 4 <= few) {
+                    *reinterpret_cast<ListRow *>(out + j) = v;
+                } else {
+#pragma unroll
+                    for (int b = 0; b < 3; ++b)
+                        if (j + b < few) out[j + b] = static_cast<int32_t>(v[b]);
+                }
+            }
+            procs = 0;
+        }
+        for (int i = 0; i < take; ++i) {
+            const int n1 = __builtin_amdgcn_readlane(procs, i) - 1, pairs = n1 * __builtin_amdgcn_readlane(segments, i);    // below 2^30
+            if (n1 < 0) continue;
+            const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(base)), i)),
+                           hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(static_cast<uint64_t>(base) >> 32)), i));
+            int32_t *const out = sched.seg + static_cast<int64_t>(static_cast<uint64_t>(hi) << 32 | lo);
+            constexpr int step = 4 * kWave;
             int s = 4 * lane / n1, r = 4 * lane - s * n1;
             const int ds = step / n1, dr = step - ds * n1;
-            for (int64_t j = 4 * lane; j < pairs; j += step) {
+            for (int j = 4 * lane; j < pairs; j += step) {
                 ListRow v;
                 int sv = s, rv = r;
 #pragma unroll
@@ -498,19 +595,23 @@ __global__ __launch_bounds__(kWave) void uni_list_kernel(ConfigArrays cfg, int64
     // wavefront from the start, whatever the LDS held before.
     for (int32_t at = lane_id() * 16; at < ListLds::bytes(procs); at += kWave * 16) *lds_at<ListVec>(at) = ListVec{0, 0, 0, 0};
     __syncthreads();
-    uni_list_body<T, 32>(lds, procs, cfg, p_max, q_max, sched, plan, order, 5);
+    int64_t wanted = 0;                                                    // wavefronts that hold the whole batch
+    for (int k = 0; k < kClasses; ++k) wanted += plan->class_count[k] >> (kClasses - k);
+    const bool roomy = wanted <= gridDim.x;
+    bool first = true;
+    uni_list_body<T, 32>(lds, procs, cfg, n, p_max, q_max, sched, plan, order, 5, roomy, first);
     __syncthreads();
-    uni_list_body<T, 16>(lds, procs, cfg, p_max, q_max, sched, plan, order, 4);
+    uni_list_body<T, 16>(lds, procs, cfg, n, p_max, q_max, sched, plan, order, 4, roomy, first);
     __syncthreads();
-    uni_list_body<T, 8>(lds, procs, cfg, p_max, q_max, sched, plan, order, 3);
+    uni_list_body<T, 8>(lds, procs, cfg, n, p_max, q_max, sched, plan, order, 3, roomy, first);
     __syncthreads();
-    uni_list_body<T, 4>(lds, procs, cfg, p_max, q_max, sched, plan, order, 2);
+    uni_list_body<T, 4>(lds, procs, cfg, n, p_max, q_max, sched, plan, order, 2, roomy, first);
     __syncthreads();
-    uni_list_body<T, 2>(lds, procs, cfg, p_max, q_max, sched, plan, order, 1);
+    uni_list_body<T, 2>(lds, procs, cfg, n, p_max, q_max, sched, plan, order, 1, roomy, first);
     __syncthreads();
-    uni_list_body<T, 1>(lds, procs, cfg, p_max, q_max, sched, plan, order, 0);
+    uni_list_body<T, 1>(lds, procs, cfg, n, p_max, q_max, sched, plan, order, 0, roomy, first);
     __syncthreads();
-    list_rest<T>(cfg, n, p_max, q_max, sched, &plan->ticket_giant[0]);
+    list_segments<T>(cfg, n, p_max, q_max, sched, &plan->ticket_giant[0]);
 }
 
 hipError_t launch_uni_list(const UniLaunch &L)

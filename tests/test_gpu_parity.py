@@ -425,6 +425,34 @@ def test_uni_schedules_of_small_batches(prs, n):
     _check_schedules(prs, host, 0, 300, 70)
 
 
+@pytest.mark.parametrize("spare", [0, 1 << 40])
+@pytest.mark.parametrize("q_max", [1, 6, 40])
+def test_uni_schedules_of_many_small_machines(prs, q_max, spare):
+    """Tens of thousands of machines of few processors, more than have a place at one time: shared out beforehand, or by tickets if
+    the caller's arrays have room for long schedules (`spare`, which nobody touches); room for few segments and for many.  Every
+    schedule is the oracle's, pair for pair."""
+    import torch
+    rng = np.random.default_rng(q_max)
+    shapes = [(2, 1), (2, q_max), (3, 1), (9, q_max), (17, 2), (31, 3), (32, 1), (33, q_max), (64, 2), (65, 5), (128, 1), (300, 3), (16, 6), (8, 4)]
+    p = np.array([a for a, _ in shapes], np.int32)
+    q = np.minimum([b for _, b in shapes], q_max).astype(np.int32)
+    k, n = len(shapes), 45_000
+    host = prs_inputs.SweepConfigs(p, q, q.astype(np.int64) * 3 - (q > 1), rng.integers(0, 5, k).astype(np.int64), rng.integers(1, 3, k).astype(np.int64),
+                                   rng.integers(0, 3, k).astype(np.int64), "i64")
+    refs = _oracle_schedules(host, 0)
+    every = rng.integers(0, k, n)
+    dev = prs.DeviceConfigs.from_host(host.take(every))
+    off = prs.prs_pair_offsets(dev, 300, q_max)
+    total = int(off[-1])
+    out = [torch.full((total,), -7, dtype=torch.int32, device="cuda") for _ in range(3)] + [torch.full((total,), -7, dtype=torch.int64, device="cuda")]
+    got = prs.greedy_schedule_batch(dev, 0, 300, q_max, off, total + spare, *out)
+    _sync()
+    assert np.all(_np(got["cfg_status"]) == 0)
+    assert np.array_equal(_np(got["T_greedy"]), np.array([r.T for r in refs])[every])
+    for column, name in zip(out, ("src", "dst", "seg", "t")):
+        assert np.array_equal(_np(column), np.concatenate([getattr(refs[i], name) for i in every])), name
+
+
 @pytest.mark.parametrize("model", [0, 1])
 def test_fp64_rounding_ties(prs, model):
     # costs chosen so that sums produced at different times round to the same double

@@ -36,7 +36,7 @@ def _ptr(a):
     return None if a is None else a.ctypes.data
 
 
-def _run(lib, host, p_max, q_max, gaps, limit=20_000_000, backwards=False, types=True, poke=(0, 0, 0, 2)):
+def _run(lib, host, p_max, q_max, gaps, limit=2_000_000, backwards=False, types=True, poke=(0, 0, 0, 2)):
     """greedy_schedule_batch on the emulated wavefronts; outputs with a margin around every configuration."""
     n, cost = len(host), B.PRS_COST_I64 if host.cost == "i64" else B.PRS_COST_F64
     number = np.int64 if host.cost == "i64" else np.float64
@@ -94,7 +94,7 @@ def _machines(p, q, cost, seed):
 _BATCHES = {"one machine": (1024, [5], [3]),
             "one of one segment": (64, [64], [1]),
             "few": (256, [2, 3, 17, 33, 65, 129, 256], [9, 1, 40, 3, 2, 5, 34]),
-            "large": (1024, [961, 3, 1024], [2, 1, 1]),
+            "large": (1024, [961, 3], [17, 1]),
             "pairs only": (16, [2] * 70, list(range(1, 71)))}
 
 
