@@ -10,7 +10,8 @@
 // cycles each on eight wavefronts: sums inside and between the wavefronts, and 400 instructions that depend on each
 // other.  On one wavefront a visit needs neither a barrier nor a sum over the block, so machines of up to 16384 processors (four
 // words of every set per lane; with six or eight the registers spill, 12.6 -> 17.4 and 28.6 ms on 16 of up to 22,709) run on one: 19 of
-// up to 5006 processors and 495 segments 14.6 -> 7.5 ms, 26 of up to 2223 4.76 -> 2.23.  64 machines of 1024 to 65536 processors, completion
+// up to 5006 processors and 495 segments 14.6 -> 7.5 ms, 26 of up to 2223 4.76 -> 2.23.  Schedules, whose indices one wavefront writes more slowly than eight,
+// go to one up to 4096 processors only (16 machines of 16,384 and 64 segments 4.0 ms on eight wavefronts, 9.4 on one; of 8000 4.4 and 5.8).  64 machines of 1024 to 65536 processors, completion
 // times: 263 ms with times per processor (about 14 barriers a visit, scattered updates of S, R and C1, all of them read
 // again at every event), 41.0 with two sums over the block and a loop over the wavefronts' parts, 38.8 so.  Measured and not
 // taken: what a visit writes held back until the next one has its row (no change), eight entries of the list at a time
@@ -366,7 +367,7 @@ __device__ T run_bi_block(const Config<T> &c, char *lds, char *slot, const Block
 // Processors that have sent everything stay in the sets: they hold no segment, so they never pair.
 constexpr int kWideWords = 65536 / 64 / kBlockThreads;     // words per thread on machines of up to 65536 processors
 constexpr int kWideProcs = kBlockThreads * kWideWords * 64;
-constexpr int kAloneWords = 4;                             // words per lane up to which one wavefront runs a machine by itself
+constexpr int kAloneWords = 4, kAloneWordsSched = 1;       // words per lane up to which one wavefront runs a machine by itself
 constexpr int kWideEntries = kWave;                        // running transfers, one per lane
 
 template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_rows(int v)
@@ -744,9 +745,9 @@ __global__ __launch_bounds__(kBlockThreads) void bi_block_kernel(ConfigArrays cf
             bool done = false;
             uint64_t *const rows = reinterpret_cast<uint64_t *>(slot + sl.sent), *const sets = reinterpret_cast<uint64_t *>(slot + sl.sets);
             const int per_lane = (c.p + kWave * 64 - 1) / (kWave * 64);    // words of a set per lane of one wavefront
-            if (per_lane <= kAloneWords) {
+            if (per_lane <= (kSched ? kAloneWordsSched : kAloneWords)) {
                 if (tid < kWave) {
-                    if (per_lane <= 1) done = run_bi_wide<T, kSched, 1, 1>(c, red, rows, sets, entries, sched, base, &result, &status);
+                    if (kSched || per_lane <= 1) done = run_bi_wide<T, kSched, 1, 1>(c, red, rows, sets, entries, sched, base, &result, &status);
                     else if (per_lane <= 2) done = run_bi_wide<T, kSched, 2, 1>(c, red, rows, sets, entries, sched, base, &result, &status);
                     else done = run_bi_wide<T, kSched, kAloneWords, 1>(c, red, rows, sets, entries, sched, base, &result, &status);
                     if (tid == 0) s_done = done ? 1 : 0;
