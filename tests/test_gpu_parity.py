@@ -379,16 +379,20 @@ def test_uni_schedules_with_long_runs_of_equal_values(prs):
 @pytest.mark.parametrize("cost", ["i64", "f64"])
 @pytest.mark.parametrize("p_max", [16, 240, 480, 960, 1024, 1100])
 def test_uni_schedules_at_the_edges_of_the_lists(prs, p_max, cost):
-    """Largest and next machine of every group size (8, 15 or 30 processors per lane by the bound, 1 to 32 lanes), machines alone on a
-    wavefront (961 to 1024) and those that use the workspace (1025 on), one segment to more than lanes, costs that vanish
-    against the clock, blocks of eight pairs that begin and end anywhere: pair for pair.  Then with gaps between the configurations."""
+    """Largest and next machine of every group size (8, 15, 30 or 32 processors per lane by the bound, 1 to 32 lanes), the largest
+    machines (1024) and those that use the workspace (1025 on), one segment to more than lanes (33 and 65 where half a wavefront is the least
+    that the machine's lists fit), costs that vanish against the clock, blocks of eight pairs that begin and end anywhere: pair for
+    pair.  Then with gaps between the configurations."""
     import torch
     rng = np.random.default_rng(p_max)
-    lane = min(max((min(p_max, 1024) + 15) // 16, 8), 30)
+    lane = min(max((min(p_max, 1024) + 15) // 16, 8), 32)
     sizes = sorted({v for g in (1, 2, 4, 8, 16, 32) for v in (lane * g, lane * g + 1)} | {2, 3, 5, 960, 961, 1023, 1024, 1025, p_max})
     p = np.repeat([v for v in sizes if v <= p_max], 4)
     q = np.tile([1, 2, 5, 37], len(p) // 4)
     q = np.where(p * p * q > 4_000_000, np.minimum(q, 3), q)
+    most = {480, 481, 512, 513, 960, 961, 1023, 1024}
+    more = [(v, c) for v in sizes if v in most and v <= p_max for c in (33, 65)]
+    p, q = (np.concatenate([a, np.array([b[i] for b in more], a.dtype)]) for i, a in enumerate((p, q)))
     n, m = len(p), q * 3 - rng.integers(0, 2, len(p)) * (q > 1)
     if cost == "i64":
         costs = [rng.choice([1, 2, 10], n), rng.integers(0, 3, n), rng.integers(0, 3, n)]
@@ -396,7 +400,7 @@ def test_uni_schedules_at_the_edges_of_the_lists(prs, p_max, cost):
         costs = [rng.choice([0.1, 1e-5, 0.3], n), rng.choice([0.1, 1e-6, 0.0], n), rng.choice([0.0, 1e-20, 0.1, 3e-6], n)]
     number = np.int64 if cost == "i64" else np.float64
     host = prs_inputs.SweepConfigs(p.astype(np.int32), q.astype(np.int32), m.astype(np.int64), *[c.astype(number) for c in costs], cost)
-    _check_schedules(prs, host, 0, p_max, 40)
+    _check_schedules(prs, host, 0, p_max, 65)
     refs = _oracle_schedules(host, 0)
     lengths = np.array([len(r.src) for r in refs])
     start = np.cumsum(np.concatenate([[3], lengths[:-1] + rng.integers(0, 4, n - 1)]))
@@ -404,7 +408,7 @@ def test_uni_schedules_at_the_edges_of_the_lists(prs, p_max, cost):
     bufs = [torch.full((total,), -7, dtype=torch.int32, device="cuda") for _ in range(3)]
     t = torch.full((total,), -7, dtype=torch.int64 if cost == "i64" else torch.float64, device="cuda")
     off = torch.from_numpy(np.append(start, total)).cuda()
-    prs.greedy_schedule_batch(prs.DeviceConfigs.from_host(host), 0, p_max, 40, off, total, bufs[0], bufs[1], bufs[2], t)
+    prs.greedy_schedule_batch(prs.DeviceConfigs.from_host(host), 0, p_max, 65, off, total, bufs[0], bufs[1], bufs[2], t)
     _sync()
     want = [np.full(total, -7) for _ in range(3)] + [np.full(total, -7, number)]
     for i, r in enumerate(refs):
@@ -412,6 +416,77 @@ def test_uni_schedules_at_the_edges_of_the_lists(prs, p_max, cost):
             w[start[i]:start[i] + lengths[i]] = v
     for got, w in zip(bufs + [t], want):
         assert np.array_equal(_np(got), w)
+
+
+def _rings_and_lists(rng, number):
+    """Machines on both sides of 1024 processors, one segment to more than 64 lanes, some of the large ones with a smaller last segment."""
+    shapes = [(1025, 3), (1025, 1), (1025, 20), (1026, 40), (1030, 70), (1100, 140), (1099, 2), (1063, 12), (1027, 33), (1025, 17), (1088, 9), (1025, 65),
+              (2, 1), (5, 9), (64, 70), (1024, 3), (1024, 33), (300, 40), (17, 130)]
+    p, q = (np.array([s[i] for s in shapes], np.int32) for i in (0, 1))
+    m = q.astype(np.int64) * 4 - rng.integers(0, 3, len(p)) * (q > 1)
+    if number is np.int64:
+        costs = [rng.integers(0, 9, len(p)), rng.integers(1, 4, len(p)), rng.integers(0, 4, len(p))]
+    else:                                                    # sums that round to the same double, and costs that vanish
+        costs = [rng.choice([1.0, 0.75, 0.1], len(p)), rng.choice([0.0, 2.0 ** -54, 1e-6], len(p)), rng.choice([2.0 ** -52, 2.0 ** -51, 0.1, 1e-20], len(p))]
+    return prs_inputs.SweepConfigs(p, q, m, *[c.astype(number) for c in costs], "i64" if number is np.int64 else "f64")
+
+
+@pytest.mark.parametrize("cost", [np.int64, np.float64])
+@pytest.mark.parametrize("grouping", list(_GROUPINGS))
+def test_uni_schedules_above_1024_processors_every_group_size(prs, grouping, cost):
+    """Machines of more than 1024 processors, whose streams lie in the workspace, on 64, 32, 16, 8 and 1 lanes, most of them with more
+    segments than lanes, beside small machines on lists: pair for pair."""
+    tuning = dict(_GROUPINGS[grouping])
+    if grouping == "64 and 32 lanes":
+        tuning["uni_wave_log2"] = 15                          # some of the machines above 1024 processors stay below it
+    _check_schedules(prs, _rings_and_lists(np.random.default_rng(8), cost), 0, 1100, 140, tuning=tuning)
+
+
+@pytest.mark.parametrize("n,p_max", [(21, 1100), (900, 1100), (13_000, 1100), (13_000, 20_000)])
+@pytest.mark.parametrize("most", ["large", "small"])
+def test_uni_schedules_of_small_and_large_machines_in_one_batch(prs, n, p_max, most):
+    """Batches in which most machines are on either side of 1024 processors, from a few to more than there are lanes (then 1, 8, 16
+    and 32 lanes side by side on the large side), invalid configurations and one that does not fit the arrays among them, and a
+    bound that leaves few places in the workspace.  Every schedule is the oracle's, pair for pair."""
+    import torch
+    rng = np.random.default_rng(n)
+    few = [(1100, 260), (1025, 64), (1030, 70), (1024, 40), (300, 130)]
+    many = [(1025, 1), (1025, 2), (1040, 3)] if most == "large" else [(2, 1), (60, 9), (1024, 2), (333, 5)]
+    other = [(2, 1), (60, 9), (1024, 2), (1000, 20)] if most == "large" else [(1025, 1), (1025, 2), (1040, 5)]
+    shapes = few + other + many
+    p, q = (np.array([s[i] for s in shapes], np.int32) for i in (0, 1))
+    k = len(shapes)
+    host = prs_inputs.SweepConfigs(p, q, q.astype(np.int64) * 3 - (q > 1), rng.integers(0, 5, k).astype(np.int64), rng.integers(1, 3, k).astype(np.int64),
+                                   rng.integers(0, 3, k).astype(np.int64), "i64")
+    refs = _oracle_schedules(host, 0)
+    every = rng.integers(k - len(many), k, n)
+    place = rng.permutation(n)
+    every[place[:k]] = np.arange(k)
+    every[place[k:k + n // 10]] = rng.integers(0, k - len(many), len(place[k:k + n // 10])) if n < 1000 else \
+        rng.integers(len(few), k - len(many), len(place[k:k + n // 10]))
+    batch = host.take(every)
+    bad = np.zeros(n, np.int32)
+    bad[[3, n // 2]] = 2, 1
+    batch.p[3], batch.p[n // 2] = p_max + 1, 1
+    dev = prs.DeviceConfigs.from_host(batch)
+    off = prs.prs_pair_offsets(dev, p_max, 260)
+    offh = _np(off).copy()
+    lengths = np.where(bad > 0, 0, [len(refs[i].src) for i in every])
+    assert np.array_equal(offh, np.concatenate([[0], np.cumsum(lengths)]))
+    total = int(offh[-1])
+    far = int(np.nonzero((bad == 0) & (batch.p > 1024))[0][-1])       # a large machine that is told a place past the end
+    moved = offh.copy()
+    moved[far] = total
+    bad[far] = 2
+    off.copy_(torch.from_numpy(moved))
+    out = [torch.full((total,), -7, dtype=torch.int32, device="cuda") for _ in range(3)] + [torch.full((total,), -7, dtype=torch.int64, device="cuda")]
+    got = prs.greedy_schedule_batch(dev, 0, p_max, 260, off, total, *out)
+    _sync()
+    assert np.array_equal(_np(got["cfg_status"]), bad)
+    assert np.array_equal(_np(got["T_greedy"])[bad == 0], np.array([r.T for r in refs])[every][bad == 0])
+    for column, name in zip(out, ("src", "dst", "seg", "t")):
+        want = np.concatenate([getattr(refs[i], name) if ok else np.full(size, -7) for i, ok, size in zip(every, bad == 0, lengths)])
+        assert np.array_equal(_np(column), want), name
 
 
 @pytest.mark.parametrize("n", [1, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193])
