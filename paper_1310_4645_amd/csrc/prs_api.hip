@@ -112,6 +112,7 @@ struct ClassSpec {
     int32_t lds_bitmap_bytes;
     size_t slot_bytes, slot_offset;
     int grid;
+    int slots = 0;            // kUniSched: blocks of the grid that have a slot; the others only run lists
 };
 
 struct Layout {
@@ -120,8 +121,8 @@ struct Layout {
     ClassSpec cls[kClasses];
     ClassSpec rerun;              // bi-greedy: the one-wavefront kernel for configurations the group kernel hands back
     ClassSpec wide;               // uni-greedy completion times: the block-per-configuration kernel (grid 0: not used)
-    bool help;                    // its wavefronts begin with the small machines when they have no large ones left
-    ClassSpec large;              // uni-greedy completion times: machines of more than kUniSmallProcs processors (grid 0: none)
+    bool help;                    // completion times: wavefronts without a large machine begin with the small ones
+    ClassSpec large;              // uni-greedy: machines of more than kUniSmallProcs processors (grid 0: none)
     bool bi_on[kClasses - 1];     // bi-greedy group classes a configuration can fall into
 };
 
@@ -155,14 +156,15 @@ constexpr int32_t kFewSegments = 16;
 // Most wavefronts of the list kernel per CU: small machines find room for more, which only share cycles and have to be started (us with
 // 10, 12 and 16: 20,000 machines of 5 processors and 30 segments 134, 136, 194; of 100 and 30 1459, 1277, 1459).
 constexpr int32_t kListWavesPerCU = 12;
-static int32_t few_segments_lane_p(int32_t p, int32_t q)
+// Beside machines of more than 1024 processors (`large`) the lists also have to fit the LDS of their rings.
+static int32_t few_segments_lane_p(int32_t p, int32_t q, bool large)
 {
     int32_t best = kUniListLaneProcs;
     int64_t most = 0;
     for (int lanes = p <= 16 ? 1 : 2; lanes <= 32; lanes *= 2) {
         const int32_t room = std::max((p + lanes - 1) / lanes, 4);
         const int64_t waves = std::min<int64_t>(blocks_per_cu(uni_list_lds_bytes(room)), 7);
-        if (room > (q == 1 ? 20 : 64) || (q > 4 && waves < 4)) continue;
+        if (room > (q == 1 ? 20 : 64) || (q > 4 && waves < 4) || (large && uni_list_lds_bytes(room) > uni_sched_lds_bytes())) continue;
         const int64_t busy = waves * (kWave / lanes) * std::min(lanes, std::max(q - 1, 1));
         if (busy > most) { most = busy; best = room; }
     }
@@ -210,7 +212,7 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
             // Room for so many processors per lane: 16 lanes for the largest machine, the group size up to which most lanes of a
             // pipeline have something to do, but no more than lets six wavefronts share a CU.
             L.limits.lane_p = std::min(std::max((p_small + 15) / 16, 8), kUniListLaneProcs);
-            if (q_max <= kFewSegments) L.limits.lane_p = few_segments_lane_p(p_small, q_max);
+            if (q_max <= kFewSegments) L.limits.lane_p = few_segments_lane_p(p_small, q_max, has_large);
         }
         for (int set = 0; set < 2; ++set) {
             const bool lists = sched && set == 0, rings = sched && set == 1;
@@ -281,16 +283,18 @@ static Layout make_layout(int call, int model, int64_t n, int32_t p_max, int32_t
                 bytes = kMaxWorkspace;
                 g = static_cast<int64_t>(bytes / c.slot_bytes);
             }
-            c.grid = static_cast<int>(g);
+            c.grid = c.slots = static_cast<int>(g);
+            if (c.kind == kUniSched) c.grid = static_cast<int>(blocks_per_cu(c.lds_bytes) * kCUs);
             c.slot_offset = off;
             return align256(bytes);
         };
         size_t slots = uni_spec(L.cls[0], p_small);
         for (int k = 1; k < kClasses; ++k) { L.cls[k] = L.cls[0]; L.cls[k].grid = 0; L.cls[k].slot_bytes = 0; }
         if (has_large) {                                               // the launches follow each other and share the slots
-            // A batch whose small machines leave lanes idle is bound by its longest chains: these begin beside the large
+            // Completion times: a batch whose small machines leave lanes idle is bound by its longest chains: these begin beside the large
             // machines (3000 machines, 81 of them of 1024 to 20000 processors: 5.9 -> 4.0 ms).  A larger one is bound by how many
             // run at once, which is one wavefront per CU there and five in the launch that follows (30000 machines: 5.9 -> 6.4).
+            // Schedules: four and six wavefronts, so they always do (uni_sched_kernel).
             L.help = !sched && n << 4 <= blocks_per_cu(uni_times_lds_bytes(p_small, compositions)) * kCUs * kWave;
             if (!sched && p_max > kUniMidProcs) slots = std::max(slots, uni_spec(L.large, kUniMidProcs));   // more wavefronts: no less than for that bound
             slots = std::max(slots, uni_spec(L.large, p_max));
@@ -442,6 +446,7 @@ static int run_greedy(int call, const prs_configs *cfg, int64_t n, int model, in
         L.stream = st;
         if (c.kind == kUniTimes) return launch_uni_times(L);
         if (c.kind == kUniList) return launch_uni_list(L);
+        L.slot_count = c.slots; L.list_procs = lay.limits.lane_p;
         if (c.kind == kUniSched) return launch_uni_sched(L);
         if (c.kind == kBiBlock) return launch_bi_block(L);
         if (c.kind == kUniWide) return launch_uni_wide(L);

@@ -46,6 +46,8 @@ struct UniLaunch {
     char *slots;
     size_t slot_bytes;
     int32_t slot_p, slot_q;
+    int32_t slot_count;           // uni-greedy schedules of large machines: wavefronts that have a place in the workspace, and
+    int32_t list_procs;           // the room for processors per lane with which the others run small machines
     int grid;
     hipStream_t stream;
 };

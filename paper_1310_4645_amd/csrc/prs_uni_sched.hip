@@ -22,6 +22,7 @@
 // Measured and not taken: 16-bit indices with a ring of 16 and eight wavefronts per CU, twice the time.
 #include "prs_device.h"
 #include "prs_launch.h"
+#include "prs_uni_list.h"
 
 namespace prs {
 
@@ -202,6 +203,7 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
                 if (gl == 0) {
                     if (sched.cfg_status) sched.cfg_status[ci] = status;
                     if (status != PRS_CFG_OK && sched.T_greedy) static_cast<T *>(sched.T_greedy)[ci] = CostTraits<T>::bad();
+                    if (status != PRS_CFG_OK) atomicAdd(&plan->large_left, -1);
                 }
                 if (status == PRS_CFG_OK) {
                     have = true;
@@ -349,6 +351,7 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
                 }
                 fW = fB = fO = 0;
                 if (k == q - 1 && sched.T_greedy) static_cast<T *>(sched.T_greedy)[ci] = tr;
+                if (k == q - 1) atomicAdd(&plan->large_left, -1);
                 k += G; par ^= 1;
                 segBase = wtot; ns = 0; runStart = 0; brun = 0; bpos = wtot;
                 lastS = 0;
@@ -414,34 +417,45 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
     }
 }
 
-// One launch for the whole batch: every wavefront works through the classes from the heaviest
-// configurations (largest groups) to the lightest.
+// One launch for all large machines: every wavefront works through the classes from the heaviest
+// configurations (largest groups) to the lightest.  Wavefronts that have no large machine, and those beyond the places in the
+// workspace, then run the lists of the others until the large ones are done; what is left of them waits for the launch that follows,
+// where six wavefronts fit a CU instead of four.  ms, one launch for all machines on rings / rings, then lists / now: 3000 machines, half of them
+// of 1025 to 1500 processors, 30.7-33.6 / 50.7 / 35.3; 12,000 and a tenth of them 34.6 / 57.2 / 40.1; 300 and a tenth 23.5 / 30.2 / 17.2; 40,000 and
+// half 62.6 / 70.3 / 57.4; 300 of which 150 are of 1025 to 4096 and up to 300 segments 109 / 116 / 110.  Not taken: staying until nothing is
+// left (within 5 % either way).
 template <typename T>
-__global__ __launch_bounds__(kWave) void uni_sched_kernel(ConfigArrays cfg, int32_t p_max, int32_t q_max, SchedOut sched,
+__global__ __launch_bounds__(kWave) void uni_sched_kernel(ConfigArrays cfg, int64_t n, int32_t p_max, int32_t q_max, SchedOut sched,
                                                           PlanHeader *plan, const int32_t *order, char *slots, size_t slot_bytes,
-                                                          int32_t slot_p)
+                                                          int32_t slot_p, int32_t slot_count, int32_t list_procs)
 {
     PRS_DYNAMIC_LDS(lds_raw);
-    char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
-    uni_sched_body<T, 64>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + kClasses - 1, kGiantPart, slot, slot_p);
-    __syncthreads();
-    uni_sched_body<T, 32>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + kClasses - 1, kRestPart, slot, slot_p);
-    __syncthreads();
-    uni_sched_body<T, 16>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + 2, kWholeClass, slot, slot_p);
-    __syncthreads();
-    uni_sched_body<T, 8>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + 1, kWholeClass, slot, slot_p);
-    __syncthreads();
-    uni_sched_body<T, 1>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass, kWholeClass, slot, slot_p);
+    if (static_cast<int32_t>(blockIdx.x) < slot_count) {
+        char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
+        uni_sched_body<T, 64>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + kClasses - 1, kGiantPart, slot, slot_p);
+        __syncthreads();
+        uni_sched_body<T, 32>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + kClasses - 1, kRestPart, slot, slot_p);
+        __syncthreads();
+        uni_sched_body<T, 16>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + 2, kWholeClass, slot, slot_p);
+        __syncthreads();
+        uni_sched_body<T, 8>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + 1, kWholeClass, slot, slot_p);
+        __syncthreads();
+        uni_sched_body<T, 1>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass, kWholeClass, slot, slot_p);
+        __syncthreads();
+    }
+    if (__hip_atomic_load(&plan->large_left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+        uni_list_all<T>(list_procs, cfg, n, p_max, q_max, sched, plan, order, true, true);
 }
 
 hipError_t launch_uni_sched(const UniLaunch &L)
 {
+    if (L.lds_bytes < uni_sched_lds_bytes() || L.lds_bytes < uni_list_lds_bytes(L.list_procs)) return hipErrorInvalidValue;
     if (L.cost == PRS_COST_I64)
-        hipLaunchKernelGGL((uni_sched_kernel<int64_t>), dim3(L.grid), dim3(kWave), uni_sched_lds_bytes(), L.stream, L.cfg, L.p_max,
-                           L.q_max, L.sched, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p);
+        hipLaunchKernelGGL((uni_sched_kernel<int64_t>), dim3(L.grid), dim3(kWave), L.lds_bytes, L.stream, L.cfg, L.n, L.p_max,
+                           L.q_max, L.sched, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p, L.slot_count, L.list_procs);
     else
-        hipLaunchKernelGGL((uni_sched_kernel<double>), dim3(L.grid), dim3(kWave), uni_sched_lds_bytes(), L.stream, L.cfg, L.p_max,
-                           L.q_max, L.sched, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p);
+        hipLaunchKernelGGL((uni_sched_kernel<double>), dim3(L.grid), dim3(kWave), L.lds_bytes, L.stream, L.cfg, L.n, L.p_max,
+                           L.q_max, L.sched, L.plan, L.order, L.slots, L.slot_bytes, L.slot_p, L.slot_count, L.list_procs);
     return hipGetLastError();
 }
 

@@ -10,7 +10,7 @@ import pytest
 from paper_1310_4645_amd import build
 
 
-@pytest.mark.parametrize("source", ["prs_uni_list.hip", "prs_uni_times.hip"])
+@pytest.mark.parametrize("source", ["prs_uni_list.hip", "prs_uni_sched.hip", "prs_uni_times.hip"])
 def test_kernels_that_address_lds_from_zero_have_none_of_their_own(source):
     """These kernels reach the LDS that the launch asks for by its address, which is 0 only if the compiler puts nothing there itself:
     a private array indexed by a variable is moved to LDS, below what the launch asks for."""

@@ -105,6 +105,21 @@ def test_lists_stay_inside_lds_and_give_the_oracles_pairs(emu, batch, cost):
     _check(emu, _machines(p, q, cost, 5), p_max, max(q), 7, backwards=cost == "f64")
 
 
+@pytest.mark.parametrize("share", [0.02, 0.3, 0.7, 2.0])
+def test_machines_begun_beside_large_ones(emu, share):
+    """Wavefronts of the launch of large machines take small ones as long as a large one is not done, the launch that follows the rest:
+    none is left out or run twice, whenever that is."""
+    p, q = [2, 300, 17, 33, 1000, 65, 129, 256, 40, 5] * 2, [9, 1, 40, 3, 2, 5, 34, 2, 17, 1] * 2
+    host = _machines(p, q, "i64", 5)
+    try:
+        emu.emu_help(C.c_int64(1 << 40))
+        _check(emu, host, 1100, 40, 7)
+        emu.emu_help(C.c_int64(max(1, int(share * emu.emu_waits()))))
+        _check(emu, host, 1100, 40, 7)
+    finally:
+        emu.emu_help(C.c_int64(0))
+
+
 def test_broken_lists_end_with_a_status(emu):
     """A link of the one machine names another of its processors all of a sudden, or a ready time becomes infinite, at any time: the
     kernel comes to an end, inside its LDS, and says so if a list was out of order or no pair could be formed any more."""

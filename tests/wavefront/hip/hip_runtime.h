@@ -61,6 +61,8 @@ inline void *body_arg;
 inline int64_t waits, reads, wait_limit;  // operations, reads of LDS by one lane since the last of its own; most operations a launch may take
 constexpr int64_t kReadLimit = 1 << 20;  // most such reads
 inline bool backwards;                   // lanes between two operations run in falling order
+inline int32_t *clear;                    // a word of memory that becomes 0 after so many operations (null: none)
+inline int64_t clear_at;
 inline int64_t poke_at, poke_place, poke_value, poke_size;   // after so many operations (0: never) some bytes of LDS are overwritten
 inline bool types;                                   // report bytes used as two types
 inline int faults;
@@ -146,6 +148,7 @@ inline void run_wavefront()
             if (c <= 0) next |= uint64_t(1) << i;
         }
         ++waits;
+        if (clear != nullptr && waits >= clear_at) *clear = 0;
         if (poke_at != 0 && waits == poke_at) memcpy(lds.data() + poke_place, &poke_value, static_cast<size_t>(poke_size));
         if (waits > wait_limit) { stopped = true; return; }
     }

@@ -29,10 +29,32 @@ hipError_t launch_plan(const PlanLaunch &L)
     return hipSuccess;
 }
 
+// In place of the launch of large machines, of which there are none: what its idle wavefronts do, as long as a large one
+// would not be done (help_for operations, 0: no such launch).
+static int64_t help_for;
+template <typename T>
+__global__ void help_kernel(ConfigArrays cfg, int64_t n, int32_t p_max, int32_t q_max, SchedOut sched, PlanHeader *plan, const int32_t *order, int32_t procs)
+{
+    uni_list_all<T>(procs, cfg, n, p_max, q_max, sched, plan, order, true, true);
+}
+hipError_t launch_uni_sched(const UniLaunch &L)
+{
+    if (help_for == 0) return hipSuccess;
+    L.plan->class_count[kLargeClass] = 1;
+    L.plan->large_left = 1;
+    emu::clear = &L.plan->large_left;
+    emu::clear_at = help_for;
+    if (L.cost == PRS_COST_I64)
+        hipLaunchKernelGGL((help_kernel<int64_t>), dim3(2), dim3(kWave), L.lds_bytes, L.stream, L.cfg, L.n, L.p_max, L.q_max, L.sched, L.plan, L.order, L.list_procs);
+    else
+        hipLaunchKernelGGL((help_kernel<double>), dim3(2), dim3(kWave), L.lds_bytes, L.stream, L.cfg, L.n, L.p_max, L.q_max, L.sched, L.plan, L.order, L.list_procs);
+    emu::clear = nullptr;
+    return hipSuccess;
+}
+
 // not reached: everything but uni-greedy schedules of small machines
 #define PRS_NOT_HERE(what) { emu::fault(what, 0, 0); return 1; }
 hipError_t launch_uni_times(const UniLaunch &) PRS_NOT_HERE("uni_times")
-hipError_t launch_uni_sched(const UniLaunch &) PRS_NOT_HERE("uni_sched")
 hipError_t launch_uni_wide(const UniLaunch &) PRS_NOT_HERE("uni_wide")
 hipError_t launch_bi(const BiLaunch &) PRS_NOT_HERE("bi")
 hipError_t launch_bi_block(const BiLaunch &) PRS_NOT_HERE("bi_block")
@@ -71,6 +93,7 @@ void emu_begin(int types, int64_t limit, int backwards, int64_t poke_at, int64_t
     emu::types = types != 0; emu::waits = 0; emu::wait_limit = limit; emu::backwards = backwards != 0; emu::faults = 0; emu::first_fault[0] = 0; emu::stopped = false;
     emu::poke_at = poke_at; emu::poke_place = poke_place; emu::poke_value = poke_value; emu::poke_size = poke_size;
 }
+void emu_help(int64_t operations) { prs::help_for = operations; }
 int64_t emu_waits() { return emu::waits; }
 int emu_stopped() { return emu::stopped; }
 int emu_faults() { return emu::faults; }
