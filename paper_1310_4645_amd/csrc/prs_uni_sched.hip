@@ -112,7 +112,7 @@ __device__ __forceinline__ int make_room(int32_t *ring, int32_t *buf, int ringBa
 template <typename T, int G>
 __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays &cfg, int32_t p_max, int32_t q_max,
                                                const SchedOut &sched, PlanHeader *plan, const int32_t *order, int cls, int part,
-                                               char *slot, int32_t slot_p)
+                                               char *slot, int32_t slot_p, int32_t spread)
 {
     constexpr int M = kRingS - 1;
     T *ringX = reinterpret_cast<T *>(lds_raw);                                   // [kRingS][64] stream values
@@ -139,7 +139,7 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
     const T kInf = CostTraits<T>::inf();
 
     // ---- per-group state (the same in all lanes of a group)
-    bool have = false, exhausted = false;
+    bool have = false, exhausted = lane / G >= spread;
     int64_t ci = 0, out_base = 0;
     int p = 2, q = 1;
     T c_full = 0, g_full = 0, c_last = 0, g_last = 0;
@@ -421,9 +421,10 @@ __device__ __forceinline__ void uni_sched_body(char *lds_raw, const ConfigArrays
 // configurations (largest groups) to the lightest.  Wavefronts that have no large machine, and those beyond the places in the
 // workspace, then run the lists of the others until the large ones are done; what is left of them waits for the launch that follows,
 // where six wavefronts fit a CU instead of four.  ms, one launch for all machines on rings / rings, then lists / now: 3000 machines, half of them
-// of 1025 to 1500 processors, 30.7-33.6 / 50.7 / 35.3; 12,000 and a tenth of them 34.6 / 57.2 / 40.1; 300 and a tenth 23.5 / 30.2 / 17.2; 40,000 and
-// half 62.6 / 70.3 / 57.4; 300 of which 150 are of 1025 to 4096 and up to 300 segments 109 / 116 / 110.  Not taken: staying until nothing is
-// left (within 5 % either way).
+// of 1025 to 1500 processors, 32.0 / 50.7 / 27.3; 12,000 and a tenth of them 34.8 / 57.2 / 26.9; 300 and a tenth 23.3 / 30.2 / 17.0; 40,000 and
+// half 62.8 / 70.3 / 57.2; 300 of which 150 are of 1025 to 4096 and up to 300 segments 111 / 116 / 110.  The most that any of 75 mixes lost against
+// the one launch is 7 % (40,000 of which nine tenths are large, 81 / 94 / 86.4) and 4 to 15 % (12,000, a tenth of up to 4096, 151 / 177 /
+// 165).  Not taken: staying until nothing is left (within 5 % either way).
 template <typename T>
 __global__ __launch_bounds__(kWave) void uni_sched_kernel(ConfigArrays cfg, int64_t n, int32_t p_max, int32_t q_max, SchedOut sched,
                                                           PlanHeader *plan, const int32_t *order, char *slots, size_t slot_bytes,
@@ -432,15 +433,21 @@ __global__ __launch_bounds__(kWave) void uni_sched_kernel(ConfigArrays cfg, int6
     PRS_DYNAMIC_LDS(lds_raw);
     if (static_cast<int32_t>(blockIdx.x) < slot_count) {
         char *slot = slots + static_cast<size_t>(blockIdx.x) * slot_bytes;
-        uni_sched_body<T, 64>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + kClasses - 1, kGiantPart, slot, slot_p);
+        // Machines of a wavefront wait for each other's rows in the workspace: no more of them to a wavefront than let all run at once.  ms,
+        // all places of a wavefront filled first / so: 300 of 1025 to 16,384 processors among 3000 887-941 / 787-798, 1500 of up to 1500 among
+        // 3000 35.2 / 27.3, 1200 of them among 12,000 41.3 / 26.9, 400 among 40,000 40.8 / 24.7; nothing but large ones the same.
+        int32_t spread = slot_count - 1;
+        for (int k = kLargeClass; k < kPlanClasses; ++k) spread += plan->class_count[k];
+        spread /= slot_count;
+        uni_sched_body<T, 64>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + kClasses - 1, kGiantPart, slot, slot_p, spread);
         __syncthreads();
-        uni_sched_body<T, 32>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + kClasses - 1, kRestPart, slot, slot_p);
+        uni_sched_body<T, 32>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + kClasses - 1, kRestPart, slot, slot_p, spread);
         __syncthreads();
-        uni_sched_body<T, 16>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + 2, kWholeClass, slot, slot_p);
+        uni_sched_body<T, 16>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + 2, kWholeClass, slot, slot_p, spread);
         __syncthreads();
-        uni_sched_body<T, 8>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + 1, kWholeClass, slot, slot_p);
+        uni_sched_body<T, 8>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass + 1, kWholeClass, slot, slot_p, spread);
         __syncthreads();
-        uni_sched_body<T, 1>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass, kWholeClass, slot, slot_p);
+        uni_sched_body<T, 1>(lds_raw, cfg, p_max, q_max, sched, plan, order, kLargeClass, kWholeClass, slot, slot_p, spread);
         __syncthreads();
     }
     if (__hip_atomic_load(&plan->large_left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
