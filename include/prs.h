@@ -94,11 +94,13 @@ typedef struct prs_times {
  * configurations are spread over the lanes of a wavefront, never a result; tests use it to push one batch
  * through every code path.
  * uni_group_pairs[k]: a uni-greedy configuration of at most this many send/receive pairs is run by 1 (k=0),
- *   4 (k=1; 8 where schedules of more than 1024 processors are written) or 16 (k=2) lanes, larger ones by 32.  Used if the three are >= 0 and non-decreasing (all zero:
+ *   4 (k=1; 8 where schedules of more than 1024 processors are written) or 16 (k=2) lanes, larger ones by 32.
+ *   Used if the three are >= 0 and non-decreasing (all zero:
  *   everything on 32 lanes -- also what a zeroed struct selects); otherwise, e.g. with -1, the built-in limits.
  *   A batch that leaves lanes idle gives its configurations more of them: up to 32, without a prs_tuning a whole wavefront.
  *   Schedules of up to 1024 processors: never fewer lanes than their lists need in LDS, never more than 32.
- * uni_wave_log2: configurations of at least 2^uni_wave_log2 pairs get a whole wavefront (1..39; else built-in).
+ * uni_wave_log2: configurations of at least 2^uni_wave_log2 pairs get a whole wavefront (1..39; else built-in).  No effect on
+ *   schedules of up to 1024 processors.
  * uni_wide_procs: uni-greedy completion times of machines with at least this many processors are computed by a
  *   whole block per configuration, many pairs of a segment at once (>= 2; else built-in: never, the kernel is
  *   slower than the segment pipeline on every workload measured).

@@ -71,7 +71,8 @@ hipError_t launch_offsets(const OffsetsLaunch &L)
 //   uni-greedy times:                 by number of pairs; 1, 2, 4, 8, 16, 32 or 64 lanes per configuration in one launch, machines
 //                                     of more than kUniSmallProcs processors in another;
 //   uni-greedy schedules:             by processors and number of pairs; 1, 2, 4, 8, 16 or 32 lanes per configuration in one launch,
-//                                     machines of more than kUniListProcs processors (8 to 64 lanes) in another;
+//                                     machines of more than kUniListProcs processors (1, 8, 16, 32 or 64 lanes) in another, whose
+//                                     idle wavefronts begin with the first;
 //   bi-greedy:                        1, 2, 4, 8 or 16 lanes per configuration for p <= 64 / 128 / 256 / 512 / 1024 and
 //                                     q <= 1023; the general kernel for the rest and for reruns.
 enum ClassKind { kUniTimes, kUniSched, kUniList, kBiGroup, kBiGeneral, kBiBlock, kUniWide };

@@ -1,17 +1,18 @@
 // Work plan of a batch: configurations grouped into classes (by size or by number of pairs, so that each
 // class gets the kernel variant and group size that fit it) and, inside a class, ordered from most to least work, so the
-// longest-running configurations start first.  Built on the device by three small kernels; no host sync.
+// longest-running configurations start first.  Built on the device, in one block for small batches and by four
+// small kernels for larger ones; no host sync.
 #pragma once
 
 #include "prs_device.h"
 
 namespace prs {
 
-constexpr int kClasses = 6;          // bi-greedy: five group sizes and the general kernel; uni-greedy: six group sizes (schedules use 0, 1, 2 and the last)
+constexpr int kClasses = 6;          // bi-greedy: five group sizes and the general kernel; uni-greedy: six group sizes (schedules of large machines use 0, 1, 2 and the last)
 constexpr int kWorkBuckets = 40;     // floor(log2(work)) buckets, heaviest first
 constexpr int kRetryClass = kClasses; // pseudo class: configurations handed back to the general kernel
 constexpr int kWideClass = kClasses;  // uni-greedy completion times: machines large enough for a block of their own
-constexpr int kLargeClass = kClasses + 1;   // uni-greedy completion times: the classes 0 .. kClasses - 1 again, for machines of more than large_p processors
+constexpr int kLargeClass = kClasses + 1;   // uni-greedy: the classes 0 .. kClasses - 1 again, for machines of more than large_p processors
 constexpr int kPlanClasses = kLargeClass + kClasses;
 
 struct PlanHeader {

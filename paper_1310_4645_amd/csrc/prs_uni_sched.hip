@@ -1,7 +1,7 @@
 // Uni-greedy schedules (Lowery & Langou, Algorithm 1, Section 5) of machines of more than 1024 processors on gfx950: the segment
 // pipeline of the completion-time kernel with processor identities, its streams in LDS rings backed by the workspace.  It
 // emits the pairs of every segment in the order of Algorithm 1 (ties by processor index, the root never sending) with their
-// start times.  (Smaller machines keep all of their streams in LDS: prs_uni_list.hip.)
+// start times.  (Smaller machines keep all of their streams in LDS: prs_uni_list.h.)
 //
 // Differences to the value-only pipeline:
 //  - stream entries are (value, sender index) and must reach the next segment sorted by both.  Senders
