@@ -111,7 +111,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_scatter(ConfigArrays cfg, i
 
 // All four steps in one block for batches of up to kPlanSmall configurations: three launches less, each of which is waited for
 // (960 machines, both port models: 249 -> 236 us in two calls).
-constexpr int kPlanSmallThreads = 1024, kPlanSmall = 4 * kPlanSmallThreads;
+// More than two rounds of the one block take longer than three launches (completion times of uni-greedy machines of 129 to 256 processors and one
+// segment, us, four kernels and one block: 1000 51.7, 46.8; 2000 36.5, 34.8; 3000 36.9, 38.3; 4000 37.5, 41.3).
+constexpr int kPlanSmallThreads = 1024, kPlanSmall = 2 * kPlanSmallThreads;
 template <typename T>
 __global__ __launch_bounds__(kPlanSmallThreads) void plan_small(ConfigArrays cfg, int n, int32_t p_max, int32_t q_max, ClassLimits lim, int n_classes,
                                                                 PlanHeader *h, int32_t *order)
